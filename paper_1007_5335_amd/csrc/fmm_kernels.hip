@@ -1106,36 +1106,64 @@ __global__ __launch_bounds__(256) void k_m2l_persist(const int4 *__restrict__ ti
 
 // Fixed-order sums of the slab rows of k_tile_gemm into the outputs.
 // Sparse M2L: target box t of the list gets rows[off[t] .. off[t+1]) (its
-// translations in increasing index), one wavefront per target.
+// translations in increasing index), one wavefront per target.  Bound by the
+// latency of the row loads: the row indices are read by the lanes in one load
+// and the rows' loads issued kCsrRows together (one row after the other: 11.5
+// us on the 28,672-node boundary tree; a density solve there 2.27 -> 2.15 ms).
+constexpr int kCsrRows = 8;
 __global__ __launch_bounds__(256) void k_slab_reduce_csr(int64_t ntgt, const int32_t *__restrict__ tgt,
                                                          const int32_t *__restrict__ off,
                                                          const int32_t *__restrict__ rows,
                                                          const double *__restrict__ slab, int PP,
                                                          double *__restrict__ out) {
     const int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int i = threadIdx.x & 63;
-    if (t >= ntgt || i >= PP) return;
-    double acc = 0.0;
-    for (int k = off[t]; k < off[t + 1]; ++k) acc += slab[(int64_t)rows[k] * PP + i];
+    const int lane = threadIdx.x & 63;
+    if (t >= ntgt) return;   // (whole wavefronts)
+    const int i = lane < PP ? lane : PP - 1;
+    const int k0 = off[t], k1 = off[t + 1];
     double *o = out + (int64_t)tgt[t] * PP + i;
-    *o += acc;
+    const double before = *o;
+    double acc = 0.0;
+    for (int kb = k0; kb < k1; kb += 64) {
+        const int nk = min(64, k1 - kb);
+        const int mine = rows[kb + min(lane, nk - 1)];
+        for (int k = 0; k < nk; k += kCsrRows) {
+            double v[kCsrRows];
+#pragma unroll
+            for (int u = 0; u < kCsrRows; ++u)
+                v[u] = slab[(int64_t)__shfl(mine, min(k + u, nk - 1), 64) * PP + i];
+#pragma unroll
+            for (int u = 0; u < kCsrRows; ++u)
+                if (k + u < nk) acc += v[u];
+        }
+    }
+    if (lane < PP) *o = before + acc;
 }
 
-// Split slots: column j of tile t gets the rows of its nparts workgroups in
-// part order; one workgroup per tile.
+// Split slots: column j of tile t gets the rows of its nparts (<= kMaxParts)
+// workgroups in part order.  A thread per element and all its parts' loads
+// issued together (a workgroup per tile walking its elements one part after
+// the other was a chain of 112 memory round trips: 35 us a launch whatever
+// its size, now about 5: a pass over 4,096 + 1,536 points 112 -> 80 us).
+constexpr int kMaxParts = 7;
 __global__ __launch_bounds__(256) void k_slab_reduce_parts(const int4 *__restrict__ tiles, int tile0,
                                                            const int32_t *__restrict__ boxes, int nparts, int NC,
                                                            const double *__restrict__ slab, int PP,
                                                            double *__restrict__ out) {
     const int t = blockIdx.x;
     const int4 tl = tiles[tile0 + t];
-    for (int e = threadIdx.x; e < tl.w * PP; e += 256) {
-        const int j = e / PP, i = e % PP;
-        double acc = 0.0;
-        for (int part = 0; part < nparts; ++part)
-            acc += slab[((int64_t)(t * nparts + part) * NC + j) * PP + i];
-        out[(int64_t)boxes[tl.z + j] * PP + i] += acc;
-    }
+    const int e = blockIdx.y * 256 + threadIdx.x;
+    if (e >= tl.w * PP) return;
+    const int j = e / PP, i = e - j * PP;
+    const double *s = slab + ((int64_t)t * nparts * NC + j) * PP + i;
+    double v[kMaxParts];
+#pragma unroll
+    for (int part = 0; part < kMaxParts; ++part) v[part] = s[(int64_t)min(part, nparts - 1) * NC * PP];
+    double acc = 0.0;
+#pragma unroll
+    for (int part = 0; part < kMaxParts; ++part)
+        if (part < nparts) acc += v[part];
+    out[(int64_t)boxes[tl.z + j] * PP + i] += acc;
 }
 
 // Where the partial rows of a launch whose workgroups share output rows go,
@@ -1157,7 +1185,7 @@ void launch_tile_gemm(Context &ctx, int P, int Pp, int ntiles, const int4 *tiles
     const bool split = Pp >= 32 && P == Pp - 15;
     // fewer tiles than compute units: share each tile's slots among up to 7
     // workgroups (about 4 slots each), whose partial rows are summed after
-    const int nparts = (!assign && slab && nslot >= 8 && ntiles < 256) ? std::min(7, (512 + ntiles - 1) / ntiles) : 1;
+    const int nparts = (!assign && slab && nslot >= 8 && ntiles < 256) ? std::min(kMaxParts, (512 + ntiles - 1) / ntiles) : 1;
     const unsigned grid = (unsigned)ntiles * (unsigned)nparts;
     if (tgt && !slab) throw Error{YK_ERR_INTERNAL, "sparse tile GEMM needs a slab"};
     constexpr int NC = 64 * CB;
@@ -1191,8 +1219,8 @@ void launch_tile_gemm(Context &ctx, int P, int Pp, int ntiles, const int4 *tiles
                                slab->ntgt, slab->tgt, slab->off, slab->rows, sl, Pp, out);
         check_launch(ctx, "k_slab_reduce_csr");
     } else if (nparts > 1) {
-        hipLaunchKernelGGL(k_slab_reduce_parts, dim3((unsigned)ntiles), dim3(256), 0, ctx.stream, tiles, tile0, boxes,
-                           nparts, NC, sl, Pp, out);
+        hipLaunchKernelGGL(k_slab_reduce_parts, dim3((unsigned)ntiles, (unsigned)(NC * Pp / 256)), dim3(256), 0,
+                           ctx.stream, tiles, tile0, boxes, nparts, NC, sl, Pp, out);
         check_launch(ctx, "k_slab_reduce_parts");
     }
 }
