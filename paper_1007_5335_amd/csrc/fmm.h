@@ -57,6 +57,16 @@ struct ActiveSet {
     DevBuf<double> m2l_slab;
     DevBuf<int32_t> csr_tgt, csr_off, csr_rows;
     int64_t n_csr_tgt = 0, n_ptrans = 0;
+    // M2L by sibling groups (m2l_sym.hip) at the levels from sym_level on: per
+    // parent its 32 source boxes and 4 children (-1: none), tiles {level,
+    // first parent, parents, 0} of up to 16 parents, level-major
+    DevBuf<int32_t> sym_src, sym_tgt;
+    DevBuf<int4> sym_tiles;
+    int n_sym_tiles = 0, sym_level = 0;
+    // {box, level} of the coarser levels' active boxes when they are few (the
+    // launch takes them along, a workgroup each)
+    DevBuf<int2> sym_coarse;
+    int n_sym_coarse = 0;
     std::vector<int64_t> l2l_begin, l2l_count;   // per level: active boxes (children) list slices
     DevBuf<int32_t> l2l_boxes;         // active boxes of levels lmin+1..L (level-major)
     std::vector<int> tile_begin, tile_count;     // per level: slice of m2l_tiles
@@ -165,6 +175,7 @@ struct FmmPlan {
     // operators (double, column-major Pp x Pp blocks)
     DevBuf<double> m2m, l2l, m2l;      // [level][4][Pp*Pp], [level][4][Pp*Pp], [level][40][Pp*Pp]
     DevBuf<float> m2lf, l2lf;
+    DevBuf<double> symop;              // M2L by sibling groups: operator fragments of its levels
     DevBuf<double> invFY, dipa, dipb;  // [level][p+2]
     DevBuf<double> cnn;                // 1/((n+1)(n+2)), n = 0 .. p+3
 
@@ -234,6 +245,18 @@ void gpu_point_leaves_adaptive(Context &ctx, FmmPlan &pl, const uint32_t *dkeys)
 void gpu_ulists_adaptive(Context &ctx, FmmPlan &pl);
 void gpu_wlists(Context &ctx, FmmPlan &pl, std::vector<int32_t> &woff, std::vector<int32_t> &wl);
 void build_tables(Context &ctx, FmmPlan &pl, int p);
+// sources [n][32] and children [n][4] of the listed parents (boxes of level
+// l - 1, whose children are at level l), in the order k_m2l_sym takes them
+void gpu_sym_lists(Context &ctx, FmmPlan &pl, int l, int64_t n, const int32_t *dparents, int32_t *src,
+                   int32_t *tgt);
+// m2l_sym.hip: M2L by sibling groups.  The coarsest level it serves, its
+// operators (after build_tables; none unless Pp is 64) and the launch
+int sym_first_level(const FmmPlan &pl);
+void build_sym_ops(Context &ctx, FmmPlan &pl);
+void launch_m2l_sym(Context &ctx, FmmPlan &pl, ActiveSet &as);
+// leading entries of Lc that M2L adds to (to be cleared before it); it writes
+// the others
+int64_t m2l_clear_len(const FmmPlan &pl, const ActiveSet &as, bool f32);
 // terms of the near-field K0/K1 series for pairs with t = r^2/(4 alpha^2) <= tmax
 int near_series_terms(double tmax);
 // I_0(x) .. I_nmax(x) in extended precision

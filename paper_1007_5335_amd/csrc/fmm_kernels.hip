@@ -2501,6 +2501,19 @@ void fmm_m2m(Context &ctx, FmmPlan &pl) {
     }
 }
 
+// FP64 M2L of dense V lists with 64 padded coefficients goes by sibling groups
+// (its 98,304 multiply-adds per parent, empty lists or not, are below the
+// 442,368 of the dense tiles for every filling of the lists; below 64 padded
+// coefficients there is no such kernel)
+static bool use_sym(const FmmPlan &pl, const ActiveSet &as) {
+    return pl.Pp == 64 && !as.m2l_sparse && as.n_sym_tiles > 0;
+}
+
+int64_t m2l_clear_len(const FmmPlan &pl, const ActiveSet &as, bool f32) {
+    if (f32 || !use_sym(pl, as)) return (int64_t)pl.nbox * pl.Pp;
+    return as.n_sym_coarse > 0 ? 0 : pl.lev[as.sym_level].begin * (int64_t)pl.Pp;
+}
+
 // M2L of every level at once into the zeroed local expansions
 void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
     const int P = pl.P, Pp = pl.Pp;
@@ -2530,16 +2543,27 @@ void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
                                               as.m2l_boxes.p, kNumV, pl.vlist.p, pl.slot_oid.p,
                                               pl.m2lf.p, (int64_t)kNumOff * Pp * Pp, 0, pl.Mf.p, 0,
                                               pl.Lc.p, nullptr, &slab);
-        else if (Pp == 64 && P == 63 && as.n_tiles >= m2l_persist_grid(ctx)) {
-            hipLaunchKernelGGL(k_m2l_persist, dim3(m2l_persist_grid(ctx)), dim3(256), 0, ctx.stream,
-                               as.m2l_tiles.p, as.n_tiles, as.m2l_boxes.p, pl.vlist.p, pl.slot_oid.p,
-                               pl.m2l.p, (int64_t)kNumOff * Pp * Pp, pl.M.p, pl.Lc.p);
-            check_launch(ctx, "k_m2l_persist");
-        } else
-            launch_tile_gemm<double, double, 1>(ctx, P, Pp, as.n_tiles, as.m2l_tiles.p, 0,
-                                                as.m2l_boxes.p, kNumV, pl.vlist.p, pl.slot_oid.p, pl.m2l.p,
-                                                (int64_t)kNumOff * Pp * Pp, 0, pl.M.p, 0, pl.Lc.p, nullptr,
-                                                &slab);
+        else {
+            // sibling groups at the levels they serve, the dense products by
+            // box at the others (the leading tiles, which are level-major)
+            int nt = as.n_tiles;
+            if (use_sym(pl, as)) {
+                nt = 0;
+                if (as.n_sym_coarse == 0)
+                    for (int l = pl.lmin; l < as.sym_level && l <= pl.L; ++l) nt += as.tile_count[l];
+                launch_m2l_sym(ctx, pl, as);
+            }
+            if (Pp == 64 && P == 63 && nt >= m2l_persist_grid(ctx)) {
+                hipLaunchKernelGGL(k_m2l_persist, dim3(m2l_persist_grid(ctx)), dim3(256), 0, ctx.stream,
+                                   as.m2l_tiles.p, nt, as.m2l_boxes.p, pl.vlist.p, pl.slot_oid.p,
+                                   pl.m2l.p, (int64_t)kNumOff * Pp * Pp, pl.M.p, pl.Lc.p);
+                check_launch(ctx, "k_m2l_persist");
+            } else
+                launch_tile_gemm<double, double, 1>(ctx, P, Pp, nt, as.m2l_tiles.p, 0, as.m2l_boxes.p, kNumV,
+                                                    pl.vlist.p, pl.slot_oid.p, pl.m2l.p,
+                                                    (int64_t)kNumOff * Pp * Pp, 0, pl.M.p, 0, pl.Lc.p, nullptr,
+                                                    &slab);
+        }
     }
 }
 
@@ -2778,6 +2802,7 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
     };
     const size_t lvl = (size_t)(p + 2);
     bool lc_clear = false;   // Lc already cleared (by the cached P2M kernel)
+    const int64_t lc_len = m2l_clear_len(pl, as, prec == SUM_FP32);
     if (far && pl.adaptive) {
         // P2M at the leaves of every level from lmin on (one launch per level,
         // the level's tables; leaves coarser than lmin need no multipole)
@@ -2871,7 +2896,7 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
             hipLaunchKernelGGL(half, dim3((unsigned)((pl.nleaf + 15) / 16), 2), dim3(64), tabh, ctx.stream,
                                leaf_base, pl.nleaf, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs,
                                has_q, inv_alpha, 1.0 / pl.lev[L].R, pl.invFY.p + L * lvl, pl.cnn.p, pl.serc.p,
-                               pl.nser, Pp, pl.M.p, split_d, pl.Lc.p, (int64_t)pl.nbox * Pp);
+                               pl.nser, Pp, pl.M.p, split_d, pl.Lc.p, lc_len);
             lc_clear = true;
             if (keep_charge_m == 1 && has_q && !has_d) pl.mq_kept = true;
             if (split_d) dipole_leaves(has_q, 0, ctx.stream);
@@ -2903,7 +2928,7 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
         }
         // downward pass
         // a fill kernel rather than a memset node: this pass may be captured in a graph
-        if (!lc_clear) launch_fill(ctx, (int64_t)pl.nbox * Pp, 0.0, pl.Lc.p);
+        if (!lc_clear) launch_fill(ctx, lc_len, 0.0, pl.Lc.p);
         {
             fmm_m2l(ctx, pl, as, f32);
             if (pl.adaptive && pl.n_xbox > 0) {

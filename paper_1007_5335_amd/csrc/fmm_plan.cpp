@@ -813,6 +813,9 @@ void build_tables(Context &ctx, FmmPlan &pl, int p) {
     }
     pl.M.ensure((size_t)nb * Pp);
     pl.Lc.ensure((size_t)nb * Pp);
+    // (the padding entries of rows that M2L writes stay zero)
+    launch_fill(ctx, nb * (int64_t)Pp, 0.0, pl.Lc.p);
+    build_sym_ops(ctx, pl);
     YK_HIP(hipStreamSynchronize(ctx.stream));
     pl.tables_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
 }
@@ -1146,6 +1149,37 @@ ActiveSet &get_active(Context &ctx, FmmPlan &pl, int mask) {
             }
         }
     }
+    // dense V lists: sibling groups at the levels whose boxes are small enough
+    as->sym_level = sym_first_level(pl);
+    std::vector<int4> stiles;
+    std::vector<int32_t> sparents;
+    std::vector<int64_t> sbegin(L + 2, 0);
+    if (!as->m2l_sparse) {
+        for (int l = as->sym_level; l <= L; ++l) {
+            const int64_t first = sbegin[l] = (int64_t)sparents.size();
+            for (int64_t b = pl.lev[l].begin; b < pl.lev[l].end; ++b) {
+                const int32_t pr = pl.hparent[b];
+                if (cnt[b] > 0 && ((int64_t)sparents.size() == first || sparents.back() != pr)) sparents.push_back(pr);
+            }
+            for (int64_t s = first; s < (int64_t)sparents.size(); s += 16)
+                stiles.push_back(make_int4(l, (int)s, (int)std::min<int64_t>(16, (int64_t)sparents.size() - s), 0));
+        }
+        sbegin[L + 1] = (int64_t)sparents.size();
+    }
+    // the coarser levels' boxes: up to 512 go with that launch, one workgroup
+    // of 27 dense products each, 0.9 MB of operators from L2 (16 boxes in a
+    // launch of their own and the sum of its partial rows took 17 us); more are
+    // left to the tiles, which share the operators among 64 boxes
+    std::vector<int2> scoarse;
+    if (!stiles.empty()) {
+        for (int32_t b : mb) {
+            int l = pl.lmin;
+            while (b >= pl.lev[l].end) ++l;
+            if (l >= as->sym_level) break;   // (level-major)
+            scoarse.push_back(make_int2(b, l));
+        }
+        if (scoarse.size() > 512) scoarse.clear();
+    }
     as->tile_begin.assign(L + 1, 0);
     as->tile_count.assign(L + 1, 0);
     for (size_t t = 0; t < tiles.size(); ++t) {
@@ -1172,6 +1206,19 @@ ActiveSet &get_active(Context &ctx, FmmPlan &pl, int mask) {
     if (!small_tree && !mb.empty()) as->m2l_trans = gpu_count_slots(ctx, pl, as->m2l_boxes.p, (int64_t)mb.size());
     up(as->m2l_tiles, tiles);
     up(as->m2l_tiles_w, wtiles);
+    DevBuf<int32_t> dparents;
+    if (!stiles.empty()) {
+        up(as->sym_tiles, stiles);
+        up(dparents, sparents);
+        int32_t *ss = as->sym_src.ensure(sparents.size() * 32), *st = as->sym_tgt.ensure(sparents.size() * 4);
+        for (int l = as->sym_level; l <= L; ++l) {
+            const int64_t k = sbegin[l];
+            gpu_sym_lists(ctx, pl, l, sbegin[l + 1] - k, dparents.p + k, ss + k * 32, st + k * 4);
+        }
+    }
+    as->n_sym_tiles = (int)stiles.size();
+    as->n_sym_coarse = (int)scoarse.size();
+    if (!scoarse.empty()) up(as->sym_coarse, scoarse);
     if (as->m2l_sparse) {
         std::vector<int32_t> piota(ptgt.size());
         for (size_t k = 0; k < piota.size(); ++k) piota[k] = (int32_t)k;

@@ -111,6 +111,51 @@ __global__ void k_vlist(int64_t begin, int64_t nb, const uint32_t *__restrict__ 
         }
 }
 
+// Sibling groups: the boxes of level l (codes code[0, nb), global indices from
+// begin) around parent (box of level l - 1): entry s of src is box (dx, dy) of
+// the 6 x 6 block of the children of the parent's 3 x 3 neighbourhood, in half
+// child sides about the parent's centre: 8 o + 4 e + k: r^k s^e of (3,1),
+// (5,1), (5,3) for orbit o, then 24 + 4 o + k: r^k of (3,3), (5,5) (r: rotation
+// by 90 degrees, s: (x, y) -> (y, x)); entries 32 .. 35 are the children r^k
+// (1,1).
+__global__ void k_sym_lists(int64_t begin, int64_t nb, const uint32_t *__restrict__ code, int l, int64_t n,
+                            const int32_t *__restrict__ parents, const uint32_t *__restrict__ bcode,
+                            int32_t *__restrict__ src, int32_t *__restrict__ tgt) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = t / 36;
+    if (i >= n) return;
+    const int s = (int)(t % 36);
+    const uint32_t pc = bcode[parents[i]];
+    const int64_t cx = 2 * (int64_t)compact15d(pc), cy = 2 * (int64_t)compact15d(pc >> 1), ns = (int64_t)1 << l;
+    int x, y, k = s & 3, e = 0;
+    if (s < 24) {
+        const int o = s >> 3;
+        e = (s >> 2) & 1;
+        x = o == 0 ? 3 : 5;
+        y = o == 2 ? 3 : 1;
+    } else {
+        x = y = s < 28 ? 3 : s < 32 ? 5 : 1;
+    }
+    if (e) {
+        const int v = x;
+        x = y;
+        y = v;
+    }
+    for (int j = 0; j < k; ++j) {
+        const int v = x;
+        x = -y;
+        y = v;
+    }
+    const int64_t jx = cx + (x + 1) / 2, jy = cy + (y + 1) / 2;   // (odd coordinates: exact)
+    int32_t b = -1;
+    if (jx >= 0 && jy >= 0 && jx < ns && jy < ns) {
+        const int64_t j = find_sorted(code, nb, spread15d((uint32_t)jx) | (spread15d((uint32_t)jy) << 1));
+        if (j >= 0) b = (int32_t)(begin + j);
+    }
+    if (s < 32) src[i * 32 + s] = b;
+    else tgt[i * 4 + (s - 32)] = b;
+}
+
 // number of non-empty V-list slots of the listed boxes, one partial count per
 // block (summed on the host)
 __global__ __launch_bounds__(256) void k_count_slots(int64_t n, const int32_t *__restrict__ boxes,
@@ -369,6 +414,15 @@ void gpu_vlists(Context &ctx, FmmPlan &pl) {
         hipLaunchKernelGGL(k_vlist, dim3(nblk(nb, 256)), dim3(256), 0, ctx.stream, b0, nb, pl.bcode.p, l, vl);
         check_launch(ctx, "k_vlist");
     }
+}
+
+void gpu_sym_lists(Context &ctx, FmmPlan &pl, int l, int64_t n, const int32_t *dparents, int32_t *src,
+                   int32_t *tgt) {
+    if (n <= 0) return;
+    const int64_t b0 = pl.lev[l].begin, nb = pl.lev[l].end - b0;
+    hipLaunchKernelGGL(k_sym_lists, dim3(nblk(n * 36, 256)), dim3(256), 0, ctx.stream, b0, nb, pl.bcode.p + b0, l, n,
+                       dparents, pl.bcode.p, src, tgt);
+    check_launch(ctx, "k_sym_lists");
 }
 
 int64_t gpu_count_slots(Context &ctx, FmmPlan &pl, const int32_t *dboxes, int64_t n) {

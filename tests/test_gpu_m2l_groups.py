@@ -1,0 +1,63 @@
+"""M2L by sibling groups on the GPU, against the oracle's direct sums at sampled
+points: partly filled last tiles, absent boxes and children, levels too coarse
+for the groups (taken along box by box, or left to the dense tiles), both tree
+forms and the padded orders it serves."""
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def yk():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1007_5335_amd.yk as yk
+    yk.load_library()
+    return yk
+
+
+# alpha against the box sides 2^-l: groups serve sides of at most 4 alpha
+CASES = [
+    dict(n=700, leaf=16, alpha=0.3),                 # every level by groups, 16 + 4 parents
+    dict(n=20011, leaf=16, alpha=0.02),              # two coarser levels, box by box
+    dict(n=60013, leaf=16, alpha=0.0045),            # more than 512 coarser boxes: dense tiles
+    dict(n=9001, leaf=8, alpha=0.1, strip=True),     # a thin set: most groups incomplete, dense lists
+    dict(n=30011, leaf=32, alpha=0.03, tree=1, clustered=True),
+    dict(n=5003, leaf=16, alpha=0.1, p=24),
+    dict(n=5003, leaf=16, alpha=0.1, p=28),
+]
+
+
+@pytest.mark.parametrize("c", CASES, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+def test_sibling_groups_match_direct_sums(yk, c):
+    import torch
+    rng = np.random.default_rng(17)
+    n, alpha, p = c["n"], c["alpha"], c.get("p", 31)
+    xy = rng.random((n, 2))
+    if c.get("strip"):
+        xy[:, 1] = 0.3 + 0.06 * xy[:, 1]
+    if c.get("clustered"):
+        half = n // 2
+        xy[:half] = np.clip(0.4 + 0.01 * rng.standard_normal((half, 2)), 0, 1)
+    q = rng.standard_normal(n)
+    print(f"groups: {c}", flush=True)
+    ctx = yk.yk_create(leaf_size=c["leaf"], p=p, tree=c.get("tree", yk.YK_TREE_UNIFORM))
+    try:
+        out = torch.empty(n, dtype=torch.float64, device="cuda")
+        yk.yk_volume_potential(ctx, dev(xy), dev(q), None, alpha, out)
+        got = host(out)
+        again = torch.empty_like(out)
+        yk.yk_volume_potential(ctx, dev(xy), dev(q), None, alpha, again)
+        assert np.array_equal(got, host(again))
+    finally:
+        yk.yk_destroy(ctx)
+    idx = rng.choice(n, size=200, replace=False)
+    ref = oracle.volume_sum(xy, q, alpha, tgt_xy=xy[idx])
+    # truncation: a box's points lie within sqrt(2)/2 sides of its centre, the
+    # centres of a pair at least two sides apart: the ratio is below 0.547
+    assert np.max(np.abs(got[idx] - ref)) <= 0.547 ** (p + 1) * np.max(np.abs(ref))
