@@ -1659,6 +1659,46 @@ __global__ __launch_bounds__(64) void k_near_build(
 
 // NTB = 64, or 256 for trees with too few items to fill the GPU (the layout
 // of the values does not depend on how many lanes share a target)
+// Dipole values (pairs) of NU sources gs apart, one vector load each and all in
+// flight together, then the sums over them: acc += mx a + my b.
+template <int NU>
+__device__ __forceinline__ double dip_sum(const double *__restrict__ Mr, int64_t cs2, const double *a, const double *b,
+                                          int gs, double acc) {
+    yk_dpair m[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) m[u] = __builtin_nontemporal_load(reinterpret_cast<const yk_dpair *>(Mr + u * cs2));
+#pragma unroll
+    for (int u = 0; u < NU; ++u) acc = __builtin_fma(m[u].x, a[u * gs], __builtin_fma(m[u].y, b[u * gs], acc));
+    return acc;
+}
+template <int NU>
+__device__ __forceinline__ double dip_sum(const float *__restrict__ Mr, int64_t cs2, const double *a, const double *b,
+                                          int gs, double acc) {
+    yk_fpair m[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) m[u] = __builtin_nontemporal_load(reinterpret_cast<const yk_fpair *>(Mr + u * cs2));
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+        acc = __builtin_fma((double)m[u].x, a[u * gs], __builtin_fma((double)m[u].y, b[u * gs], acc));
+    return acc;
+}
+// Charge values of NU sources, likewise.
+template <int NU, typename VT>
+__device__ __forceinline__ double chg_sum(const VT *__restrict__ Mr, int64_t cs, const double *a, int gs, double acc) {
+    VT m[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) m[u] = __builtin_nontemporal_load(Mr + u * cs);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) acc = __builtin_fma((double)m[u], a[u * gs], acc);
+    return acc;
+}
+// sources per lane whose values are in flight together: an item of a densely
+// sampled curve (58 targets, 130 dipoles) is one wavefront's chain of such
+// batches (200,003 points: 176 us with 8 charges or 4 dipoles and two loads per
+// dipole, 144 us with 16 and 8; the symmetric kernel, whose registers five
+// wavefronts per SIMD share, takes 8 of either: 223 us with 16, 211 with 8)
+constexpr int kNearBatch = 16;
+
 template <typename VT, int NTB>
 __global__ __launch_bounds__(NTB) void k_near_apply(
     const int2 *__restrict__ items, const int32_t *__restrict__ lrange,
@@ -1697,32 +1737,18 @@ __global__ __launch_bounds__(NTB) void k_near_apply(
             if (set == 0) {
                 const VT *Mb = Mq + qoff[ib] + (int64_t)c0 * it.c + it.ti + (int64_t)it.sub * it.c;
                 int j = it.sub;
-                for (; j + 7 * gs < cn; j += 8 * gs, Mb += 8 * cs) {
-                    VT m[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) m[u] = __builtin_nontemporal_load(Mb + u * cs);
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) near_q = __builtin_fma((double)m[u], s_a[j + u * gs], near_q);
-                }
-                for (; j < cn; j += gs, Mb += cs) near_q = __builtin_fma((double)__builtin_nontemporal_load(Mb), s_a[j], near_q);
+                for (; j + (kNearBatch - 1) * gs < cn; j += kNearBatch * gs, Mb += kNearBatch * cs)
+                    near_q = chg_sum<kNearBatch>(Mb, cs, s_a + j, gs, near_q);
+                for (; j + 3 * gs < cn; j += 4 * gs, Mb += 4 * cs) near_q = chg_sum<4>(Mb, cs, s_a + j, gs, near_q);
+                for (; j < cn; j += gs, Mb += cs) near_q = chg_sum<1>(Mb, cs, s_a + j, gs, near_q);
             } else {
                 const VT *Mb = Md + 2 * (doff[ib] + (int64_t)c0 * it.c + it.ti + (int64_t)it.sub * it.c);
                 int j = it.sub;
-                for (; j + 3 * gs < cn; j += 4 * gs, Mb += 8 * cs) {
-                    VT mx[4], my[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        mx[u] = __builtin_nontemporal_load(Mb + 2 * u * cs);
-                        my[u] = __builtin_nontemporal_load(Mb + 2 * u * cs + 1);
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        near_d = __builtin_fma((double)mx[u], s_a[j + u * gs],
-                                               __builtin_fma((double)my[u], s_b[j + u * gs], near_d));
-                }
-                for (; j < cn; j += gs, Mb += 2 * cs)
-                    near_d = __builtin_fma((double)__builtin_nontemporal_load(Mb), s_a[j],
-                                           __builtin_fma((double)__builtin_nontemporal_load(Mb + 1), s_b[j], near_d));
+                for (; j + 7 * gs < cn; j += 8 * gs, Mb += 16 * cs)
+                    near_d = dip_sum<8>(Mb, 2 * cs, s_a + j, s_b + j, gs, near_d);
+                for (; j + gs < cn; j += 2 * gs, Mb += 4 * cs)
+                    near_d = dip_sum<2>(Mb, 2 * cs, s_a + j, s_b + j, gs, near_d);
+                for (; j < cn; j += gs, Mb += 2 * cs) near_d = dip_sum<1>(Mb, 2 * cs, s_a + j, s_b + j, gs, near_d);
             }
         }
     }
@@ -1867,9 +1893,12 @@ __device__ __forceinline__ ItemSetup setup_from_desc(const int *d) {
 constexpr int kSymRounds = 4;
 
 // four consecutive values (16-byte aligned for float, 32 for double), read once
+// (double: the two halves of a 32-byte piece are two loads, which the first
+// level cache serves with one request when they are not marked streaming:
+// 199 -> 183 us over 2^20 uniform points)
 __device__ __forceinline__ void load4(const double *p, double (&o)[4]) {
-    const yk_dpair a = __builtin_nontemporal_load(reinterpret_cast<const yk_dpair *>(p));
-    const yk_dpair b = __builtin_nontemporal_load(reinterpret_cast<const yk_dpair *>(p) + 1);
+    const yk_dpair a = *reinterpret_cast<const yk_dpair *>(p);
+    const yk_dpair b = *(reinterpret_cast<const yk_dpair *>(p) + 1);
     o[0] = a.x;
     o[1] = a.y;
     o[2] = b.x;
@@ -2028,14 +2057,9 @@ __global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k
             const VT *Mr = Mb + (int64_t)c0 * cB + tiB + (int64_t)subB * cB;
             const int64_t cs = (int64_t)cB * gB;
             int j = subB;
-            for (; j + 7 * gB < cn; j += 8 * gB, Mr += 8 * cs) {
-                VT m[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) m[u] = __builtin_nontemporal_load(Mr + u * cs);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) acc = __builtin_fma((double)m[u], s_a[j + u * gB], acc);
-            }
-            for (; j < cn; j += gB, Mr += cs) acc = __builtin_fma((double)__builtin_nontemporal_load(Mr), s_a[j], acc);
+            for (; j + 7 * gB < cn; j += 8 * gB, Mr += 8 * cs) acc = chg_sum<8>(Mr, cs, s_a + j, gB, acc);
+            for (; j + 3 * gB < cn; j += 4 * gB, Mr += 4 * cs) acc = chg_sum<4>(Mr, cs, s_a + j, gB, acc);
+            for (; j < cn; j += gB, Mr += cs) acc = chg_sum<1>(Mr, cs, s_a + j, gB, acc);
         }
         __syncthreads();
         s_a[lane] = vB ? acc : 0.0;
@@ -2063,20 +2087,10 @@ __global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k
             const int64_t cs = (int64_t)c * gs;
             const VT *Mr = Md + 2 * (doff[ib] + (int64_t)c0 * c + it.ti + (int64_t)it.sub * c);
             int j = it.sub;
-            for (; j + 3 * gs < cn; j += 4 * gs, Mr += 8 * cs) {
-                VT mx[4], my[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    mx[u] = __builtin_nontemporal_load(Mr + 2 * u * cs);
-                    my[u] = __builtin_nontemporal_load(Mr + 2 * u * cs + 1);
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    acc = __builtin_fma((double)mx[u], s_a[j + u * gs], __builtin_fma((double)my[u], s_b[j + u * gs], acc));
-            }
-            for (; j < cn; j += gs, Mr += 2 * cs)
-                acc = __builtin_fma((double)__builtin_nontemporal_load(Mr), s_a[j],
-                                    __builtin_fma((double)__builtin_nontemporal_load(Mr + 1), s_b[j], acc));
+            for (; j + 7 * gs < cn; j += 8 * gs, Mr += 16 * cs)
+                acc = dip_sum<8>(Mr, 2 * cs, s_a + j, s_b + j, gs, acc);
+            for (; j + gs < cn; j += 2 * gs, Mr += 4 * cs) acc = dip_sum<2>(Mr, 2 * cs, s_a + j, s_b + j, gs, acc);
+            for (; j < cn; j += gs, Mr += 2 * cs) acc = dip_sum<1>(Mr, 2 * cs, s_a + j, s_b + j, gs, acc);
         }
         __syncthreads();
         s_a[lane] = it.valid ? acc : 0.0;

@@ -1036,6 +1036,34 @@ ActiveSet &get_active(Context &ctx, FmmPlan &pl, int mask) {
         as->h_uoff = std::move(uoff);
         as->h_ul = std::move(ul);
     }
+    // many items: those with far more pairs than the mean (leaves on densely
+    // sampled curves) are one wavefront's long chain each, so they go first,
+    // dealt to the starts of the eight ranges that the launches' block map
+    // gives the XCDs, the heaviest first; the others keep their order.  (In
+    // Morton order they ended alone: 256 us of near field on 2^20 points and
+    // six curves of 4,096 nodes against 183 us without the curves.)
+    if (!pl.adaptive && items.size() >= 2048) {
+        const size_t n = items.size();
+        std::vector<int64_t> cost(n);
+        int64_t total = 0;
+        for (size_t i = 0; i < n; ++i) {
+            const int32_t li = items[i].x;
+            cost[i] = std::min<int64_t>(64, cnt[leaf_gbox(li)] - items[i].y) * (as->h_sq[li] + 2 * as->h_sd[li]);
+            total += cost[i];
+        }
+        std::vector<size_t> heavy, light;
+        for (size_t i = 0; i < n; ++i) ((double)cost[i] * (double)n > 3.0 * (double)total ? heavy : light).push_back(i);
+        std::stable_sort(heavy.begin(), heavy.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+        std::vector<int2> ordered;
+        ordered.reserve(n);
+        size_t l0 = 0;
+        for (size_t x = 0; x < 8; ++x) {
+            const size_t end = ordered.size() + n / 8 + (x < n % 8 ? 1 : 0);
+            for (size_t h = x; h < heavy.size() && ordered.size() < end; h += 8) ordered.push_back(items[heavy[h]]);
+            while (ordered.size() < end && l0 < light.size()) ordered.push_back(items[light[l0++]]);
+        }
+        if (ordered.size() == n) items.swap(ordered);   // (a range too short for its heavy items: as they were)
+    }
     // adaptive tree: the items grouped (stably) by their leaf's level and by
     // whether a coarser leaf touches it, class 2 l + coarser, so that each
     // class's near field runs with the series its pair distances need
