@@ -681,7 +681,7 @@ void box_potential(Context &ctx, const yk_grid &g, const double *B, double alpha
         fmm_m2m(ctx, pl);
         launch_fill(ctx, m2l_clear_len(pl, as, false), 0.0, pl.Lc.p);
         fmm_m2l(ctx, pl, as, false);
-        fmm_l2l(ctx, pl, as, false);
+        fmm_l2l(ctx, pl, as);
     }
     StageTimer tl(ctx, YK_STAGE_LEAF);
     const int64_t tiles_row = (bp.nlx + 15) / 16;
@@ -929,7 +929,7 @@ void box_potential_adaptive(Context &ctx, const double root[3], int64_t n, const
                                pl.xoff.p, pl.xl.p, bp.x_tab.p, bp.tin.p, coef, bp.p2l_tab.p, pl.Pp, pl.Lc.p);
             check_launch(ctx, "k_boxa_p2l");
         }
-        fmm_l2l(ctx, pl, as, false);
+        fmm_l2l(ctx, pl, as);
     }
     double *outs = pl.outs.ensure(pl.N);
     {

@@ -36,6 +36,35 @@ struct LevelInfo {
     double R = 0;                      // half-diagonal / alpha
 };
 
+// One launch of parent-child shifts (shifts.hip): n workgroups, each the
+// subtree below one box over nlev (at most three) levels, their descriptors
+// from `first` on.  M2M computes the boxes at level, level - 1, .. (each at most
+// 16, 4 and 1 boxes of a subtree of three levels); L2L the children at level,
+// level + 1, .. (of 1, 4 and 16 parents).
+struct ShiftGroup {
+    int level = 0, nlev = 0;
+    bool wide = false;   // one level, 16 boxes of the level per workgroup
+    int64_t first = 0, n = 0;
+};
+// M2M descriptor: boxes computed per level (0-2); the boxes, 16 + 4 + 1; four
+// children per box, 64 + 16 + 4: a row of M, -1 absent or computed at the level
+// before; for the boxes of the first two levels, 16 + 4, where they go:
+// 4 (their parent's index) + their position
+constexpr int kUpBox = 3, kUpChild = 24, kUpLink = kUpChild + 84, kUpDesc = kUpLink + 20;
+// L2L descriptor: parents per level (0-2); the root (3); their children,
+// 4 + 16 + 64 (-1: none, or no target below); the children's indices as
+// parents at the next level (-1: none), 4 + 16
+constexpr int kDownChild = 4, kDownLink = kDownChild + 84, kDownDesc = kDownLink + 20;
+constexpr int kDownWide = 3;   // wide: 16 parents, then four children each
+constexpr int kShiftLevels = 3;
+// Levels of more boxes with children than this are launched by themselves, 16
+// boxes per workgroup: 1,024 / 4,096 / 16,384 boxes take 7 / 7 / 20 us of M2M and
+// 8.5 / 9.5 / 28 of L2L, while the three together as subtrees took 40 and 43 us
+// (two workgroups to a compute unit).  Below, the launches themselves count:
+// three levels of up to 484 boxes take 6 to 15 us as subtrees, 4.5 to 7 us each
+// launched one by one.
+constexpr int64_t kShiftWide = 512;
+
 // Boxes of one target mask that take part in the downward pass.
 struct ActiveSet {
     DevBuf<int32_t> m2l_boxes;         // active boxes of levels lmin..L, sorted by (level, class)
@@ -68,7 +97,8 @@ struct ActiveSet {
     DevBuf<int2> sym_coarse;
     int n_sym_coarse = 0;
     std::vector<int64_t> l2l_begin, l2l_count;   // per level: active boxes (children) list slices
-    DevBuf<int32_t> l2l_boxes;         // active boxes of levels lmin+1..L (level-major)
+    std::vector<ShiftGroup> l2l_groups;   // coarsest first
+    DevBuf<int32_t> down_desc;
     std::vector<int> tile_begin, tile_count;     // per level: slice of m2l_tiles
     DevBuf<int32_t> leaves;            // active leaves (leaf-local indices)
     int64_t n_leaves = 0;
@@ -147,12 +177,8 @@ struct FmmPlan {
     DevBuf<int32_t> fchild, nchild;    // first child (global index) and child count
     DevBuf<int32_t> slot_oid;          // [4 classes][27 slots] -> offset id in 0..39
     DevBuf<int32_t> child4;            // [nbox][4] child at each position, -1 if none
-    DevBuf<int32_t> iota4;             // {0,1,2,3}: slot -> operator for M2M and L2L
     DevBuf<int32_t> iota40;            // 0..39: offset id -> M2L operator (sparse M2L)
     std::vector<int32_t> h_soid;       // host copy of slot_oid
-    DevBuf<int4> up_tiles;             // M2M tiles: parents of levels lmin..L-1, 64 per tile
-    DevBuf<int32_t> up_boxes;
-    std::vector<int> up_tile_begin, up_tile_count;
     DevBuf<double> serc;               // [2][nser]: series coefficients of F_{p+1}, F_{p+2}
     DevBuf<int32_t> vlist;             // [nbox][27]
     DevBuf<int32_t> lrange;            // [nleaf][6] start/end per set (sorted positions)
@@ -174,7 +200,10 @@ struct FmmPlan {
 
     // operators (double, column-major Pp x Pp blocks)
     DevBuf<double> m2m, l2l, m2l;      // [level][4][Pp*Pp], [level][4][Pp*Pp], [level][40][Pp*Pp]
-    DevBuf<float> m2lf, l2lf;
+    DevBuf<float> m2lf;
+    std::vector<ShiftGroup> m2m_groups;   // finest first
+    DevBuf<int32_t> up_desc;
+    DevBuf<double> up_op, down_op;     // M2M and L2L: operator fragments (shifts.hip)
     DevBuf<double> symop;              // M2L by sibling groups: operator fragments of its levels
     DevBuf<double> invFY, dipa, dipb;  // [level][p+2]
     DevBuf<double> cnn;                // 1/((n+1)(n+2)), n = 0 .. p+3
@@ -205,7 +234,6 @@ struct FmmPlan {
     DevBuf<int32_t> alr;                           // [nbox][6] leaf ranges by box (split boxes: empty)
     DevBuf<int32_t> p2m_list;                      // per level >= lmin: level-local indices of its leaves
     std::vector<int64_t> p2m_off;                  // [L + 2] slices of p2m_list by level
-    std::vector<int64_t> up_off, up_n;             // per level: the split boxes' slice of up_boxes (M2M)
     DevBuf<int32_t> woff, wl, wleaves;             // W lists (CSR over leaves), leaves with a W list
     int64_t n_wl = 0, n_wleaves = 0;
     DevBuf<int32_t> xbox, xoff, xl;                // X lists: boxes with one, CSR of source leaves
@@ -254,6 +282,10 @@ void gpu_sym_lists(Context &ctx, FmmPlan &pl, int l, int64_t n, const int32_t *d
 int sym_first_level(const FmmPlan &pl);
 void build_sym_ops(Context &ctx, FmmPlan &pl);
 void launch_m2l_sym(Context &ctx, FmmPlan &pl, ActiveSet &as);
+// shifts.hip
+void build_shift_ops(Context &ctx, FmmPlan &pl);
+void launch_m2m_group(Context &ctx, FmmPlan &pl, const ShiftGroup &gr);
+void launch_l2l_group(Context &ctx, FmmPlan &pl, ActiveSet &as, const ShiftGroup &gr);
 // leading entries of Lc that M2L adds to (to be cleared before it); it writes
 // the others
 int64_t m2l_clear_len(const FmmPlan &pl, const ActiveSet &as, bool f32);
@@ -264,7 +296,7 @@ std::vector<long double> bessel_i_seq(long double x, int nmax);
 // the stages between the leaf multipoles and the leaf local expansions
 void fmm_m2m(Context &ctx, FmmPlan &pl);
 void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32);
-void fmm_l2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32);
+void fmm_l2l(Context &ctx, FmmPlan &pl, ActiveSet &as);
 // adaptive tree, after L2L: the W-list multipoles added into the sorted sums
 // outs, then each leaf's local expansion at its points, written with outs to
 // the caller's arrays out[set] (sets in mask)

@@ -1225,85 +1225,6 @@ void launch_tile_gemm(Context &ctx, int P, int Pp, int ntiles, const int4 *tiles
     }
 }
 
-// Small levels of M2M (4 child slots) and L2L (1 parent slot): one block of
-// four wavefronts per box.  The (slot, column) pairs of the product are split
-// into four equal runs, one per wavefront (M2M: a child slot each; L2L: a
-// quarter of the columns each), so each lane's chain of operator loads is a
-// quarter as long; the four partial rows are summed through LDS.  (The tile
-// GEMM chains one memory round trip per slot, which dominates when a level
-// has few boxes.)  Padding rows and columns of the operators and of the
-// coefficient vectors are zero.
-template <int PP, int NS>
-__global__ __launch_bounds__(256) void k_small_gemv(
-    const int32_t *__restrict__ boxes, int64_t box0, const int32_t *__restrict__ src,
-    const uint32_t *__restrict__ bcode, const double *__restrict__ Op, const double *__restrict__ X,
-    int P, int assign, double *__restrict__ out) {
-    constexpr int KW = NS * PP / 4;          // (slot, column) pairs per wavefront
-    constexpr int BT = KW < 16 ? KW : 16;    // operator loads issued together
-    __shared__ double xs[NS * PP];
-    __shared__ double red[4][PP];
-    const int64_t box = boxes ? (int64_t)boxes[blockIdx.x] : box0 + blockIdx.x;
-    const int w = threadIdx.x >> 6, i = threadIdx.x & 63;
-    for (int f = threadIdx.x; f < NS * PP; f += 256) {
-        const int sj = src[box * NS + f / PP];
-        xs[f] = sj >= 0 ? X[(int64_t)sj * PP + f % PP] : 0.0;
-    }
-    const int s = NS == 1 ? 0 : w;           // this wavefront's slot
-    const int k0 = NS == 1 ? w * KW : 0;     // and its first column
-    const bool live = src[box * NS + s] >= 0;
-    __syncthreads();
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (i < PP && live) {
-        const double *A = Op + (size_t)(NS == 1 ? (int)(bcode[box] & 3u) : s) * PP * PP +
-                          (size_t)k0 * PP + i;
-        const double *x = xs + s * PP + k0;
-#pragma unroll
-        for (int kb = 0; kb < KW; kb += BT) {
-            double a[BT];
-#pragma unroll
-            for (int u = 0; u < BT; ++u) a[u] = A[(size_t)(kb + u) * PP];
-#pragma unroll
-            for (int u = 0; u < BT; ++u) acc[u & 3] = __builtin_fma(a[u], x[kb + u], acc[u & 3]);
-        }
-    }
-    if (i < PP) red[w][i] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-    __syncthreads();
-    if (w == 0 && i < PP) {
-        const double v = i < P ? (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]) : 0.0;
-        double *o = out + box * PP + i;
-        *o = assign ? v : *o + v;
-    }
-}
-
-void launch_small_gemv(Context &ctx, int Pp, int ns, int64_t nbox, const int32_t *boxes, int64_t box0,
-                       const int32_t *src, const uint32_t *bcode, const double *Op, const double *X,
-                       int P, int assign, double *out) {
-    if (nbox <= 0) return;
-#define YK_SMALL_CASE(PPV)                                                                         \
-    case PPV:                                                                                      \
-        if (ns == 1)                                                                               \
-            hipLaunchKernelGGL((k_small_gemv<PPV, 1>), dim3((unsigned)nbox), dim3(256), 0, ctx.stream, \
-                               boxes, box0, src, bcode, Op, X, P, assign, out);                    \
-        else                                                                                       \
-            hipLaunchKernelGGL((k_small_gemv<PPV, 4>), dim3((unsigned)nbox), dim3(256), 0, ctx.stream, \
-                               boxes, box0, src, bcode, Op, X, P, assign, out);                    \
-        break;
-    switch (Pp) {
-        YK_SMALL_CASE(16)
-        YK_SMALL_CASE(32)
-        YK_SMALL_CASE(48)
-        YK_SMALL_CASE(64)
-        default:
-            throw Error{YK_ERR_INTERNAL, "no small-level kernel for this padded order"};
-    }
-#undef YK_SMALL_CASE
-    check_launch(ctx, "k_small_gemv");
-}
-
-// levels with at most this many boxes take k_small_gemv for M2M (4 operators
-// per box: beyond ~1000 boxes the tile GEMM's shared operators win) and L2L
-constexpr int64_t kSmallLevelM2M = 1024, kSmallLevelL2L = 4096;
-
 __global__ void k_to_float(int64_t n, const double *__restrict__ a, float *__restrict__ b) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) b[i] = (float)a[i];
@@ -2486,33 +2407,8 @@ int m2l_persist_grid(Context &ctx) {
 // M2M over levels L-1 .. lmin: each parent box from its children (the
 // adaptive tree's split boxes only: a leaf keeps its own multipole)
 void fmm_m2m(Context &ctx, FmmPlan &pl) {
-    const int L = pl.L, P = pl.P, Pp = pl.Pp;
-    {
-        StageTimer tmm(ctx, YK_STAGE_M2M);
-        for (int l = L - 1; l >= pl.lmin; --l) {
-            const int64_t nbl = pl.lev[l].end - pl.lev[l].begin;
-            if (pl.adaptive) {
-                // the split boxes only (a leaf keeps its P2M multipole)
-                if (pl.up_n[l] <= kSmallLevelM2M)
-                    launch_small_gemv(ctx, Pp, 4, pl.up_n[l], pl.up_boxes.p + pl.up_off[l], 0, pl.child4.p,
-                                      pl.bcode.p, pl.m2m.p + (size_t)l * 4 * Pp * Pp, pl.M.p, P, 1, pl.M.p);
-                else
-                    launch_tile_gemm<double, double>(ctx, P, Pp, pl.up_tile_count[l], pl.up_tiles.p,
-                                                     pl.up_tile_begin[l], pl.up_boxes.p, 4, pl.child4.p,
-                                                     pl.iota4.p, pl.m2m.p, (int64_t)4 * Pp * Pp, 0, pl.M.p,
-                                                     1, pl.M.p);
-            } else if (nbl <= kSmallLevelM2M) {
-                launch_small_gemv(ctx, Pp, 4, nbl, nullptr, pl.lev[l].begin, pl.child4.p, pl.bcode.p,
-                                  pl.m2m.p + (size_t)l * 4 * Pp * Pp, pl.M.p, P, 1, pl.M.p);
-            } else {
-                // M2M on matrix cores: 4 child slots, operators S[l][position]
-                launch_tile_gemm<double, double>(ctx, P, Pp, pl.up_tile_count[l], pl.up_tiles.p,
-                                                 pl.up_tile_begin[l], pl.up_boxes.p, 4, pl.child4.p,
-                                                 pl.iota4.p, pl.m2m.p, (int64_t)4 * Pp * Pp, 0, pl.M.p,
-                                                 1, pl.M.p);
-            }
-        }
-    }
+    StageTimer tmm(ctx, YK_STAGE_M2M);
+    for (const ShiftGroup &gr : pl.m2m_groups) launch_m2m_group(ctx, pl, gr);
 }
 
 // FP64 M2L of dense V lists with 64 padded coefficients goes by sibling groups
@@ -2582,26 +2478,9 @@ void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
 }
 
 // L2L top-down over levels lmin+1 .. L (each box pulls its parent's expansion)
-void fmm_l2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
-    const int L = pl.L, P = pl.P, Pp = pl.Pp;
+void fmm_l2l(Context &ctx, FmmPlan &pl, ActiveSet &as) {
     StageTimer tl2(ctx, YK_STAGE_L2L);
-    for (int l = pl.lmin + 1; l <= L; ++l) {
-        // L2L top-down: one parent slot, operator E[l-1][position]
-        if (as.l2l_count[l] <= kSmallLevelL2L) {
-            launch_small_gemv(ctx, Pp, 1, as.l2l_count[l], as.l2l_boxes.p + as.l2l_begin[l], 0,
-                              pl.bparent.p, pl.bcode.p, pl.l2l.p + (size_t)(l - 1) * 4 * Pp * Pp,
-                              pl.Lc.p, P, 0, pl.Lc.p);
-        } else if (f32)
-            launch_tile_gemm<float, double>(ctx, P, Pp, as.tile_count[l], as.m2l_tiles.p,
-                                            as.tile_begin[l], as.m2l_boxes.p, 1, pl.bparent.p,
-                                            pl.iota4.p, pl.l2lf.p, (int64_t)4 * Pp * Pp, -1, pl.Lc.p,
-                                            0, pl.Lc.p);
-        else
-            launch_tile_gemm<double, double>(ctx, P, Pp, as.tile_count[l], as.m2l_tiles.p,
-                                             as.tile_begin[l], as.m2l_boxes.p, 1, pl.bparent.p,
-                                             pl.iota4.p, pl.l2l.p, (int64_t)4 * Pp * Pp, -1, pl.Lc.p,
-                                             0, pl.Lc.p);
-    }
+    for (const ShiftGroup &gr : as.l2l_groups) launch_l2l_group(ctx, pl, as, gr);
 }
 
 void fmm_adaptive_finish(Context &ctx, FmmPlan &pl, int mask, double *outs, double *const out[3]) {
@@ -2955,7 +2834,7 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                                    pl.py.p, qs, dns, pl.toff[1], pl.rI.p, p, Pp, inv_alpha, pl.Lc.p);
                 check_launch(ctx, "k_ad_p2l");
             }
-            fmm_l2l(ctx, pl, as, f32);
+            fmm_l2l(ctx, pl, as);
         }
     }
     if (!near_done) launch_near();

@@ -570,28 +570,68 @@ void finish_tree(Context &ctx, FmmPlan &pl, const std::vector<double> &cx, const
     std::vector<int32_t> ch4((size_t)nb * 4, -1);
     for (int64_t b = 0; b < nb; ++b)
         if (pl.hparent[b] >= 0) ch4[(size_t)pl.hparent[b] * 4 + (pl.hcode[b] & 3u)] = (int32_t)b;
-    std::vector<int4> utiles;
-    std::vector<int32_t> uboxes;
-    pl.up_tile_begin.assign(L + 1, 0);
-    pl.up_tile_count.assign(L + 1, 0);
-    pl.up_off.assign(L + 1, 0);
-    pl.up_n.assign(L + 1, 0);
-    for (int l = lmin; l < L; ++l) {
-        // the boxes with children (all of them in the uniform tree)
-        std::vector<int32_t> par;
+    // M2M launches of up to three levels, finest first: a subtree per box with
+    // children at the coarsest
+    std::vector<int32_t> udesc;
+    pl.m2m_groups.clear();
+    for (int l = L - 1; l >= lmin;) {
+        ShiftGroup gr;
+        gr.level = l;
+        gr.nlev = std::min(kShiftLevels, l - lmin + 1);
+        gr.first = (int64_t)(udesc.size() / kUpDesc);
+        std::vector<int32_t> split;
         for (int64_t b = pl.lev[l].begin; b < pl.lev[l].end; ++b)
-            if (nch[b] > 0) par.push_back((int32_t)b);
-        pl.up_tile_begin[l] = (int)utiles.size();
-        pl.up_off[l] = (int64_t)uboxes.size();
-        pl.up_n[l] = (int64_t)par.size();
-        for (size_t k0 = 0; k0 < par.size(); k0 += 64) {
-            const int cnt = (int)std::min<size_t>(64, par.size() - k0);
-            utiles.push_back(make_int4(l, 0, (int)uboxes.size(), cnt));
-            for (int k = 0; k < cnt; ++k) uboxes.push_back(par[k0 + k]);
+            if (nch[b] > 0) split.push_back((int32_t)b);
+        if ((int64_t)split.size() > kShiftWide) {
+            gr.nlev = 1;
+            gr.wide = true;
+            for (size_t s = 0; s < split.size(); s += 16) {
+                std::array<int32_t, kUpDesc> d;
+                d.fill(-1);
+                d[0] = (int32_t)std::min<size_t>(16, split.size() - s);
+                for (int j = 0; j < d[0]; ++j) {
+                    d[kUpBox + j] = split[s + j];
+                    for (int c = 0; c < 4; ++c) d[kUpChild + 4 * j + c] = ch4[(size_t)split[s + j] * 4 + c];
+                }
+                udesc.insert(udesc.end(), d.begin(), d.end());
+                ++gr.n;
+            }
+            pl.m2m_groups.push_back(gr);
+            --l;
+            continue;
         }
-        pl.up_tile_count[l] = (int)utiles.size() - pl.up_tile_begin[l];
+        const int lc = l - gr.nlev + 1;
+        for (int64_t r = pl.lev[lc].begin; r < pl.lev[lc].end; ++r) {
+            if (nch[r] == 0) continue;
+            std::array<int32_t, kUpDesc> d;
+            d.fill(-1);
+            d[0] = d[1] = d[2] = 0;
+            // from the root down: slot k of the descriptor is level l - k
+            std::vector<int32_t> at = {(int32_t)r};
+            for (int k = gr.nlev - 1; k >= 0; --k) {
+                int32_t *box = &d[kUpBox + (k == 0 ? 0 : k == 1 ? 16 : 20)], *ch = &d[kUpChild + (k == 0 ? 0 : k == 1 ? 64 : 80)];
+                std::vector<int32_t> next;
+                d[k] = (int32_t)at.size();
+                for (size_t j = 0; j < at.size(); ++j) {
+                    box[j] = at[j];
+                    for (int c = 0; c < 4; ++c) {
+                        const int32_t b = ch4[(size_t)at[j] * 4 + c];
+                        if (b >= 0 && k > 0 && nch[b] > 0) {   // computed at the level before
+                            d[kUpLink + (k == 1 ? 0 : 16) + next.size()] = (int32_t)(4 * j + c);
+                            next.push_back(b);
+                        } else {
+                            ch[4 * j + c] = b;
+                        }
+                    }
+                }
+                at.swap(next);
+            }
+            udesc.insert(udesc.end(), d.begin(), d.end());
+            ++gr.n;
+        }
+        pl.m2m_groups.push_back(gr);
+        l -= gr.nlev;
     }
-    const std::vector<int32_t> iota4 = {0, 1, 2, 3};
     // ---- slot -> offset id for the 4 parity classes ----
     std::vector<int32_t> soid(4 * kNumV);
     for (int cls = 0; cls < 4; ++cls) {
@@ -619,17 +659,13 @@ void finish_tree(Context &ctx, FmmPlan &pl, const std::vector<double> &cx, const
     up(pl.nchild, nch);
     up(pl.slot_oid, soid);
     up(pl.child4, ch4);
-    up(pl.iota4, iota4);
     {
         std::vector<int32_t> iota40(kNumOff);
         for (int k = 0; k < kNumOff; ++k) iota40[k] = k;
         up(pl.iota40, iota40);
     }
     pl.h_soid = soid;
-    if (!utiles.empty()) {
-        up(pl.up_tiles, utiles);
-        up(pl.up_boxes, uboxes);
-    }
+    if (!udesc.empty()) up(pl.up_desc, udesc);
     if (!pl.adaptive) {
         std::vector<int32_t> dl;
         for (int64_t li = 0; li < pl.nleaf; ++li)
@@ -808,14 +844,13 @@ void build_tables(Context &ctx, FmmPlan &pl, int p) {
     {
         std::vector<float> f(m2l.begin(), m2l.end());
         up(pl.m2lf, f);
-        std::vector<float> g(l2l.begin(), l2l.end());
-        up(pl.l2lf, g);
     }
     pl.M.ensure((size_t)nb * Pp);
     pl.Lc.ensure((size_t)nb * Pp);
     // (the padding entries of rows that M2L writes stay zero)
     launch_fill(ctx, nb * (int64_t)Pp, 0.0, pl.Lc.p);
     build_sym_ops(ctx, pl);
+    build_shift_ops(ctx, pl);
     YK_HIP(hipStreamSynchronize(ctx.stream));
     pl.tables_ms += std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
 }
@@ -1224,6 +1259,73 @@ ActiveSet &get_active(Context &ctx, FmmPlan &pl, int mask) {
             if (cnt[b] > 0) l2lb.push_back((int32_t)b);
         as->l2l_count[l] = (int64_t)l2lb.size() - as->l2l_begin[l];
     }
+    // L2L launches of up to three levels, coarsest first: a subtree per box with
+    // active children
+    std::vector<int32_t> first_child(pl.nbox, -1);   // index in l2lb of a box's first active child
+    for (size_t k = l2lb.size(); k-- > 0;) first_child[pl.hparent[l2lb[k]]] = (int32_t)k;
+    std::vector<int32_t> ddesc;
+    auto parents_at = [&](int l) {   // active boxes of level l with active children
+        std::vector<int32_t> v;
+        for (int64_t b = pl.lev[l].begin; b < pl.lev[l].end; ++b)
+            if (first_child[b] >= 0) v.push_back((int32_t)b);
+        return v;
+    };
+    for (int l = pl.lmin + 1; l <= L;) {
+        ShiftGroup gr;
+        gr.level = l;
+        gr.first = (int64_t)(ddesc.size() / kDownDesc);
+        const std::vector<int32_t> roots = parents_at(l - 1);
+        if ((int64_t)roots.size() > kShiftWide) {
+            gr.nlev = 1;
+            gr.wide = true;
+            for (size_t s = 0; s < roots.size(); s += 16) {
+                std::array<int32_t, kDownDesc> d;
+                d.fill(-1);
+                d[0] = (int32_t)std::min<size_t>(16, roots.size() - s);
+                for (int j = 0; j < d[0]; ++j) {
+                    const int32_t r = roots[s + j];
+                    d[kDownWide + j] = r;
+                    for (int32_t i = first_child[r]; i < (int32_t)l2lb.size() && pl.hparent[l2lb[i]] == r; ++i)
+                        d[kDownWide + 16 + 4 * j + (pl.hcode[l2lb[i]] & 3u)] = l2lb[i];
+                }
+                ddesc.insert(ddesc.end(), d.begin(), d.end());
+                ++gr.n;
+            }
+            as->l2l_groups.push_back(gr);
+            ++l;
+            continue;
+        }
+        gr.nlev = 1;
+        while (gr.nlev < kShiftLevels && l + gr.nlev <= L &&
+               (int64_t)parents_at(l + gr.nlev - 1).size() <= kShiftWide)
+            ++gr.nlev;
+        for (const int32_t r : roots) {
+            std::array<int32_t, kDownDesc> d;
+            d.fill(-1);
+            d[0] = d[1] = d[2] = 0;
+            d[3] = r;
+            std::vector<int32_t> at = {r};
+            for (int k = 0; k < gr.nlev; ++k) {
+                const int base = k == 0 ? 0 : k == 1 ? 4 : 20;
+                std::vector<int32_t> next;
+                d[k] = (int32_t)at.size();
+                for (size_t j = 0; j < at.size(); ++j)
+                    for (int32_t i = first_child[at[j]]; i < (int32_t)l2lb.size() && pl.hparent[l2lb[i]] == at[j]; ++i) {
+                        const int32_t b = l2lb[i], s = (int32_t)(4 * j + (pl.hcode[b] & 3u));
+                        d[kDownChild + base + s] = b;
+                        if (k + 1 < gr.nlev && first_child[b] >= 0) {
+                            d[kDownLink + base + s] = (int32_t)next.size();
+                            next.push_back(b);
+                        }
+                    }
+                at.swap(next);
+            }
+            ddesc.insert(ddesc.end(), d.begin(), d.end());
+            ++gr.n;
+        }
+        as->l2l_groups.push_back(gr);
+        l += gr.nlev;
+    }
     auto up = [&](auto &buf, const auto &vec) {
         using T = typename std::decay_t<decltype(vec)>::value_type;
         T *d = buf.ensure(vec.size());
@@ -1274,7 +1376,7 @@ ActiveSet &get_active(Context &ctx, FmmPlan &pl, int mask) {
         as->n_csr_tgt = (int64_t)ctgt.size();
         as->n_ptrans = (int64_t)ptgt.size();
     }
-    up(as->l2l_boxes, l2lb);
+    up(as->down_desc, ddesc);
     up(as->leaves, leaves);
     up(as->leaf_items, items);
     as->n_items = (int64_t)items.size();

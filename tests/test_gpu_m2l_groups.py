@@ -1,4 +1,4 @@
-"""M2L by sibling groups on the GPU, against the oracle's direct sums at sampled
+"""M2L by sibling groups and the parent-child shifts on the GPU, against the oracle's direct sums at sampled
 points: partly filled last tiles, absent boxes and children, levels too coarse
 for the groups (taken along box by box, or left to the dense tiles), both tree
 forms and the padded orders it serves."""
@@ -30,6 +30,13 @@ CASES = [
     dict(n=30011, leaf=32, alpha=0.03, tree=1, clustered=True),
     dict(n=5003, leaf=16, alpha=0.1, p=24),
     dict(n=5003, leaf=16, alpha=0.1, p=28),
+    # the shifts of the other padded orders: one, two and three levels of
+    # subtrees, levels of more than 512 boxes by themselves, leaves among the
+    # children of split boxes
+    dict(n=300, leaf=16, alpha=0.3, p=8),
+    dict(n=40009, leaf=16, alpha=0.2, p=12),
+    dict(n=3001, leaf=8, alpha=0.2, p=16),
+    dict(n=30011, leaf=16, alpha=0.1, tree=1, clustered=True, p=20),
 ]
 
 
@@ -59,5 +66,6 @@ def test_sibling_groups_match_direct_sums(yk, c):
     idx = rng.choice(n, size=200, replace=False)
     ref = oracle.volume_sum(xy, q, alpha, tgt_xy=xy[idx])
     # truncation: a box's points lie within sqrt(2)/2 sides of its centre, the
-    # centres of a pair at least two sides apart: the ratio is below 0.547
-    assert np.max(np.abs(got[idx] - ref)) <= 0.547 ** (p + 1) * np.max(np.abs(ref))
+    # centres of a pair at least two sides apart: the ratio is below 0.547, and
+    # the terms left out sum to 0.547^(p+1) / (1 - 0.547)
+    assert np.max(np.abs(got[idx] - ref)) <= 0.547 ** (p + 1) / 0.453 * np.max(np.abs(ref))
