@@ -69,9 +69,12 @@ typedef struct {
     int gmres_m;            /* Krylov dimension before a restart */
     int debug_flags;        /* bit0: synchronise and check after every kernel;
                                bit1: run the near field on the context's stream
-                               (by default a tree of fewer than 8192 leaves
-                               runs it on a second stream, overlapped with the
-                               far field; larger trees always run it in turn);
+                               in a launch of its own (by default a tree of
+                               fewer than 8192 leaves runs it in one launch
+                               with P2M or, with 2048 or more groups of up to
+                               64 targets, on a second stream overlapped with
+                               the far field; larger trees always run it in
+                               turn);
                                bit2: capture the density operator in a HIP
                                graph and replay it (off by default: slower
                                than eager launches here);

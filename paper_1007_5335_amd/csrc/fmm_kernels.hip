@@ -645,48 +645,93 @@ __global__ __launch_bounds__(256) void k_p2m_rows(
     }
 }
 
+// The strengths of the sorted points: gathered arrays (qs, dns), or read
+// through the permutation (perm) from the caller's q and either dipole vectors
+// dn or the factors w sigma n of the double-layer operator.
+struct Strengths {
+    const double *qs = nullptr, *dns = nullptr;
+    const int32_t *perm = nullptr;
+    const double *q = nullptr, *dn = nullptr, *w = nullptr, *sigma = nullptr, *normal = nullptr;
+    __device__ __forceinline__ double charge(int64_t j) const { return perm ? q[perm[j]] : qs[j]; }
+    // dipole of sorted position j, off1 the first dipole's
+    __device__ __forceinline__ double2 dipole(int64_t j, int64_t off1) const {
+        if (!perm) return make_double2(dns[2 * (j - off1)], dns[2 * (j - off1) + 1]);
+        const int32_t i = perm[j];
+        if (dn) return make_double2(dn[2 * i], dn[2 * i + 1]);
+        const double s = (w ? w[i] : 1.0) * sigma[i];
+        return make_double2(s * normal[2 * i], s * normal[2 * i + 1]);
+    }
+};
+
 // one block of four wavefronts per leaf, lanes over coefficients: wavefront w
 // sums the leaf's points w, w + 4, ... (two chains per lane) and the four
 // partial rows are added through LDS; the blocks also clear zero[0..nzero)
-__global__ __launch_bounds__(256) void k_p2m_apply(
-    int64_t leaf_base, int64_t nleaf, const int32_t *__restrict__ lrange, int64_t off1, int has_q,
-    int has_d, const double *__restrict__ qs, const double *__restrict__ dns,
-    const double *__restrict__ rq, const double *__restrict__ rd, int P, int Pp, double *__restrict__ M,
-    double *__restrict__ zero, int64_t nzero) {
-    __shared__ double part[4][64];
+constexpr int kRowStage = 256;   // strengths staged at a time (a multiple of 8)
+struct P2MApply {
+    int64_t leaf_base, nleaf;
+    const int32_t *lrange;
+    const double *rq, *rd;
+    int P, Pp;
+    double *M, *zero;
+    int64_t nzero;
+};
+__device__ __forceinline__ void p2m_apply(int64_t li, const P2MApply &a, const Strengths &st, int64_t off1, int has_q,
+                                          int has_d, double *lds) {
+    double(*part)[64] = reinterpret_cast<double(*)[64]>(lds);
+    double *sx = lds + 256, *sy = sx + kRowStage;
+    const int Pp = a.Pp;
     // zero[0..nzero) = 0 on the side (the local expansions, cleared here
     // rather than by a launch of their own)
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < nzero; e += (int64_t)gridDim.x * 256)
-        zero[e] = 0.0;
-    const int64_t li = blockIdx.x;
+    for (int64_t e = li * 256 + threadIdx.x; e < a.nzero; e += a.nleaf * 256) a.zero[e] = 0.0;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t b = leaf_base + li;
-    const int s0 = lrange[li * 6], e0 = has_q ? lrange[li * 6 + 1] : s0;
-    const int s1 = lrange[li * 6 + 2], e1 = has_d ? lrange[li * 6 + 3] : s1;
-    for (int ob = 0; ob < Pp; ob += 64) {
-        const int o = ob + lane;
-        double a0 = 0.0, a1 = 0.0;
+    const int64_t b = a.leaf_base + li;
+    const int s0 = a.lrange[li * 6], e0 = has_q ? a.lrange[li * 6 + 1] : s0;
+    const int s1 = a.lrange[li * 6 + 2], e1 = has_d ? a.lrange[li * 6 + 3] : s1;
+    const int o = lane;   // (Pp <= 64)
+    double a0 = 0.0, a1 = 0.0;
+    for (int c0 = s0; c0 < e0; c0 += kRowStage) {
+        const int cn = min(kRowStage, e0 - c0);
+        __syncthreads();
+        if ((int)threadIdx.x < cn) sx[threadIdx.x] = st.charge(c0 + threadIdx.x);
+        __syncthreads();
         if (o < Pp) {
-            for (int j = s0 + w; j < e0; j += 8) {
-                a0 = __builtin_fma(rq[(int64_t)j * Pp + o], qs[j], a0);
-                if (j + 4 < e0) a1 = __builtin_fma(rq[(int64_t)(j + 4) * Pp + o], qs[j + 4], a1);
+            const double *r = a.rq + (int64_t)c0 * Pp + o;
+            for (int j = w; j < cn; j += 8) {
+                a0 = __builtin_fma(r[(int64_t)j * Pp], sx[j], a0);
+                if (j + 4 < cn) a1 = __builtin_fma(r[(int64_t)(j + 4) * Pp], sx[j + 4], a1);
             }
-            for (int j = s1 + w; j < e1; j += 8) {
-                const int64_t jd = j - off1;
-                const double *r = rd + jd * 2 * (int64_t)Pp + o;
-                a0 = __builtin_fma(r[0], dns[2 * jd], __builtin_fma(r[Pp], dns[2 * jd + 1], a0));
-                if (j + 4 < e1) {
-                    const double *r4 = r + 8 * (int64_t)Pp;
-                    a1 = __builtin_fma(r4[0], dns[2 * jd + 8], __builtin_fma(r4[Pp], dns[2 * jd + 9], a1));
+        }
+    }
+    for (int c0 = s1; c0 < e1; c0 += kRowStage) {
+        const int cn = min(kRowStage, e1 - c0);
+        __syncthreads();
+        if ((int)threadIdx.x < cn) {
+            const double2 d = st.dipole(c0 + threadIdx.x, off1);
+            sx[threadIdx.x] = d.x;
+            sy[threadIdx.x] = d.y;
+        }
+        __syncthreads();
+        if (o < Pp) {
+            const double *r = a.rd + (int64_t)(c0 - off1) * 2 * Pp + o;
+            for (int j = w; j < cn; j += 8) {
+                const double *rj = r + (int64_t)j * 2 * Pp;
+                a0 = __builtin_fma(rj[0], sx[j], __builtin_fma(rj[Pp], sy[j], a0));
+                if (j + 4 < cn) {
+                    const double *r4 = rj + 8 * (int64_t)Pp;
+                    a1 = __builtin_fma(r4[0], sx[j + 4], __builtin_fma(r4[Pp], sy[j + 4], a1));
                 }
             }
         }
-        part[w][lane] = a0 + a1;
-        __syncthreads();
-        if (w == 0 && o < Pp)
-            M[b * Pp + o] = o < P ? (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]) : 0.0;
-        __syncthreads();
     }
+    part[w][lane] = a0 + a1;
+    __syncthreads();
+    if (w == 0 && o < Pp)
+        a.M[b * Pp + o] = o < a.P ? (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]) : 0.0;
+}
+constexpr int kP2MApplyLds = 256 + 2 * kRowStage;   // doubles
+__global__ __launch_bounds__(256) void k_p2m_apply(P2MApply a, Strengths st, int64_t off1, int has_q, int has_d) {
+    __shared__ double lds[kP2MApplyLds];
+    p2m_apply(blockIdx.x, a, st, off1, has_q, has_d, lds);
 }
 
 // ------------------------------------------------------------- M2L (MFMA) --
@@ -1620,16 +1665,35 @@ __device__ __forceinline__ double chg_sum(const VT *__restrict__ Mr, int64_t cs,
 // wavefronts per SIMD share, takes 8 of either: 223 us with 16, 211 with 8)
 constexpr int kNearBatch = 16;
 
+// the pass's side of a cached near field (both layouts)
+template <typename VT>
+struct NearPass {
+    Strengths st;
+    int64_t off1;
+    int has_q, has_d;
+    const int64_t *qoff, *doff;
+    const VT *Mq, *Md;
+    double dip_scale;
+    double *outs;
+};
+// both orders of every charge pair stored
+struct NearFull {
+    const int2 *items;
+    const int32_t *lrange, *uoff, *ulist;
+    int q_on, d_on, mask;
+};
 template <typename VT, int NTB>
-__global__ __launch_bounds__(NTB) void k_near_apply(
-    const int2 *__restrict__ items, const int32_t *__restrict__ lrange,
-    const int32_t *__restrict__ uoff, const int32_t *__restrict__ ulist,
-    const double *__restrict__ qs, const double *__restrict__ dns, int64_t off1, int q_on, int d_on,
-    int has_q, int has_d, int mask, const int64_t *__restrict__ qoff, const int64_t *__restrict__ doff,
-    const VT *__restrict__ Mq, const VT *__restrict__ Md, double dip_scale, double *__restrict__ outs) {
-    __shared__ double s_a[NTB > kLeafStage ? NTB : kLeafStage], s_b[kLeafStage];
+__device__ __forceinline__ void near_apply(int ib, const NearFull &nf, const NearPass<VT> &np, double *lds) {
+    double *s_a = lds, *s_b = s_a + (NTB > kLeafStage ? NTB : kLeafStage);
     __shared__ int qa[9], qn[9], da[9], dn_[9];
-    const int ib = xcd_remap(blockIdx.x, gridDim.x);
+    const int2 *__restrict__ items = nf.items;
+    const int32_t *__restrict__ lrange = nf.lrange, *__restrict__ uoff = nf.uoff, *__restrict__ ulist = nf.ulist;
+    const int q_on = nf.q_on, d_on = nf.d_on, mask = nf.mask, has_q = np.has_q, has_d = np.has_d;
+    const int64_t off1 = np.off1;
+    const int64_t *__restrict__ qoff = np.qoff, *__restrict__ doff = np.doff;
+    const VT *__restrict__ Mq = np.Mq, *__restrict__ Md = np.Md;
+    const double dip_scale = np.dip_scale;
+    double *__restrict__ outs = np.outs;
     const int lane = threadIdx.x;
     const ItemSetup it = item_setup<NTB>(items[ib], lrange, uoff, ulist, q_on, d_on, mask, qa, qn, da, dn_);
     double near_q = 0.0, near_d = 0.0;
@@ -1642,11 +1706,11 @@ __global__ __launch_bounds__(NTB) void k_near_apply(
             for (int f = lane; f < cn; f += NTB) {
                 const int j = flat_source(c0 + f, set == 0 ? qn : dn_, set == 0 ? qa : da);
                 if (set == 0) {
-                    s_a[f] = qs[j];
+                    s_a[f] = np.st.charge(j);
                 } else {
-                    const int64_t jd = j - off1;
-                    s_a[f] = dns[2 * jd];
-                    s_b[f] = dns[2 * jd + 1];
+                    const double2 d = np.st.dipole(j, off1);
+                    s_a[f] = d.x;
+                    s_b[f] = d.y;
                 }
             }
             __syncthreads();
@@ -1681,6 +1745,13 @@ __global__ __launch_bounds__(NTB) void k_near_apply(
         for (int gi = 0; gi < it.g; ++gi) tot += s_a[it.ti + gi * it.c];
         outs[it.t] = tot * kInv2Pi;
     }
+}
+
+template <int NTB> constexpr int kNearFullLds = (NTB > kLeafStage ? NTB : kLeafStage) + kLeafStage;
+template <typename VT, int NTB>
+__global__ __launch_bounds__(NTB) void k_near_apply(NearFull nf, NearPass<VT> np) {
+    __shared__ double lds[kNearFullLds<NTB>];
+    near_apply<VT, NTB>(xcd_remap(blockIdx.x, gridDim.x), nf, np, lds);
 }
 
 // ---------------------------------------------------- symmetric near field --
@@ -1833,17 +1904,26 @@ __device__ __forceinline__ void load4(const float *p, double (&o)[4]) {
     o[3] = a.w;
 }
 
+// each charge pair stored once
+struct NearSym {
+    const int32_t *desc;
+    const int64_t *desc_dst;
+    double *inc;
+};
+template <int NTB> constexpr int kNearSymLds = (NTB > kLeafStage ? NTB : kLeafStage) + kLeafStage + 64 + 4 * NTB;
 template <typename VT, int NTB>
-__global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k_near_apply_sym(
-    const int32_t *__restrict__ desc, const int64_t *__restrict__ desc_dst, const double *__restrict__ qs,
-    const double *__restrict__ dns, int64_t off1, int has_q, int has_d, const int64_t *__restrict__ qoff, const int64_t *__restrict__ doff, const VT *__restrict__ Mq,
-    const VT *__restrict__ Md, double dip_scale, double *__restrict__ outs, double *__restrict__ inc) {
-    __shared__ double s_a[NTB > kLeafStage ? NTB : kLeafStage], s_b[kLeafStage];
-    __shared__ double s_res[64];
-    __shared__ double s_p[4 * NTB];   // direct sums of part (1), four targets per lane
+__device__ __forceinline__ void near_apply_sym(int ib, const NearSym &ns, const NearPass<VT> &np, double *lds) {
+    double *s_a = lds, *s_b = s_a + (NTB > kLeafStage ? NTB : kLeafStage);
+    double *s_res = s_b + kLeafStage, *s_p = s_res + 64;   // s_p: direct sums of part (1), four targets per lane
     __shared__ int s_d[kItemDesc], s_pre[9];
     __shared__ int64_t s_dst[9];
-    const int ib = xcd_remap(blockIdx.x, gridDim.x);
+    const int32_t *__restrict__ desc = ns.desc;
+    const int64_t *__restrict__ desc_dst = ns.desc_dst, *__restrict__ qoff = np.qoff, *__restrict__ doff = np.doff;
+    const VT *__restrict__ Mq = np.Mq, *__restrict__ Md = np.Md;
+    const int has_q = np.has_q, has_d = np.has_d;
+    const int64_t off1 = np.off1;
+    const double dip_scale = np.dip_scale;
+    double *__restrict__ outs = np.outs, *__restrict__ inc = ns.inc;
     const int lane = threadIdx.x;
     // the item's descriptor: one round trip instead of the chain leaf -> U list -> ranges
     if (lane < kItemDesc) s_d[lane] = desc[(int64_t)ib * kItemDesc + lane];
@@ -1879,7 +1959,7 @@ __global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int t = 4 * lt + i;
-            qa4[i] = (vA && t < cA) ? qs[rs0 + t] : 0.0;
+            qa4[i] = (vA && t < cA) ? np.st.charge(rs0 + t) : 0.0;
             y4[i] = 0.0;
         }
         const VT *Mb = Mq + qoff[ib] + 4 * lt;
@@ -1904,7 +1984,7 @@ __global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k
             // the first batch is in flight while the sources' charges are staged
             load_batch(0);
             __syncthreads();
-            for (int f = lane; f < cn; f += NTB) s_a[f] = qs[flat_source(c0 + f, qo, qa)];
+            for (int f = lane; f < cn; f += NTB) s_a[f] = np.st.charge(flat_source(c0 + f, qo, qa));
             __syncthreads();
             for (int r0 = 0; r0 < cn; r0 += kSymRounds * nfb) {
                 if (r0 > 0) load_batch(r0);
@@ -1972,7 +2052,7 @@ __global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k
         for (int c0 = 0; c0 < it.nq; c0 += kLeafStage) {
             const int cn = min(kLeafStage, it.nq - c0);
             __syncthreads();
-            for (int f = lane; f < cn; f += NTB) s_a[f] = qs[flat_source(c0 + f, qn, qa)];
+            for (int f = lane; f < cn; f += NTB) s_a[f] = np.st.charge(flat_source(c0 + f, qn, qa));
             __syncthreads();
             if (!vB) continue;
             const VT *Mr = Mb + (int64_t)c0 * cB + tiB + (int64_t)subB * cB;
@@ -1998,9 +2078,9 @@ __global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k
             const int cn = min(kLeafStage, it.nd - c0);
             __syncthreads();
             for (int f = lane; f < cn; f += NTB) {
-                const int64_t jd = flat_source(c0 + f, dn_, da) - off1;
-                s_a[f] = dns[2 * jd];
-                s_b[f] = dns[2 * jd + 1];
+                const double2 d = np.st.dipole(flat_source(c0 + f, dn_, da), off1);
+                s_a[f] = d.x;
+                s_b[f] = d.y;
             }
             __syncthreads();
             if (!it.valid) continue;
@@ -2024,6 +2104,29 @@ __global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k
     }
     __syncthreads();
     if (lane < c) outs[it.t] = s_res[lane] * kInv2Pi;
+}
+
+template <typename VT, int NTB>
+__global__ __launch_bounds__(NTB) __attribute__((amdgpu_waves_per_eu(5))) void k_near_apply_sym(NearSym ns,
+                                                                                                NearPass<VT> np) {
+    __shared__ double lds[kNearSymLds<NTB>];
+    near_apply_sym<VT, NTB>(xcd_remap(blockIdx.x, gridDim.x), ns, np, lds);
+}
+
+// P2M (cached rows) and the cached near field of a small tree in one launch,
+// the strengths read through the permutation: both need only them, the near
+// field's items are the longer chains and go first, and the far field's
+// launches that follow are too short to hide a second stream's events behind.
+template <typename VT, bool SYM>
+__global__ __launch_bounds__(256) void k_p2m_near(P2MApply pa, NearFull nf, NearSym ns, NearPass<VT> np, int nitems) {
+    constexpr int kLds = kNearSymLds<256> > kP2MApplyLds ? kNearSymLds<256> : kP2MApplyLds;
+    __shared__ double lds[kLds];
+    if ((int)blockIdx.x < nitems) {   // (whole workgroups)
+        if constexpr (SYM) near_apply_sym<VT, 256>(blockIdx.x, ns, np, lds);
+        else near_apply<VT, 256>(blockIdx.x, nf, np, lds);
+    } else {
+        p2m_apply(blockIdx.x - nitems, pa, np.st, np.off1, np.has_q, np.has_d, lds);
+    }
 }
 
 using NearBuild64 = void (*)(const int2 *, const int32_t *, const int32_t *, const int32_t *,
@@ -2516,43 +2619,140 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
     const int has_q = (q && n0 > 0) ? 1 : 0, has_d = ((dn || bie) && n1 > 0) ? 1 : 0;
     const int L = pl.L, p = pl.p, P = pl.P, Pp = pl.Pp;
     const double inv_alpha = 1.0 / pl.alpha;
-    double *qs = pl.qs.ensure(n0 > 0 ? n0 : 1);
-    double *dns = pl.dns.ensure(n1 > 0 ? 2 * n1 : 1);
     double *outs = pl.outs.ensure(pl.N);
     pl.last_mask = mask;
     pl.last_has_q = has_q;
     pl.last_has_d = has_d;
-    {
-    StageTimer tg(ctx, YK_STAGE_GATHER);
-    if (has_q) {
-        hipLaunchKernelGGL(k_gather_q, dim3(nblk(n0, 256)), dim3(256), 0, ctx.stream, n0, pl.perm.p, q, qs);
-        check_launch(ctx, "k_gather_q");
-    }
-    if (has_d && bie) {
-        hipLaunchKernelGGL(k_gather_dn_form, dim3(nblk(n1, 256)), dim3(256), 0, ctx.stream, pl.toff[1], n1,
-                           pl.perm.p, bie->w, bie->sigma, bie->normal, dns);
-        check_launch(ctx, "k_gather_dn_form");
-    } else if (has_d) {
-        hipLaunchKernelGGL(k_gather_dn, dim3(nblk(n1, 256)), dim3(256), 0, ctx.stream, pl.toff[1], n1,
-                           pl.perm.p, dn, dns);
-        check_launch(ctx, "k_gather_dn");
-    }
-    }
     ActiveSet &as = get_active(ctx, pl, mask);
     // parts: bit 0 the near field, bit 1 the far field (the order check
     // evaluates them apart; the near field alone is then evaluated on the fly)
     const bool far = pl.lmin <= L && (has_q || has_d) && (parts & 2);
     const bool near_on = (parts & 1) != 0;
     const int64_t leaf_base = pl.lev[L].begin;
+    const bool f32 = prec == SUM_FP32;
 
-    // near field: independent of the far field until L2P, so it runs on the
-    // side stream while M2M, M2L and L2L run on the main one (forked after P2M,
-    // which would otherwise be starved of compute units)
-    // (only for small trees: with a large one both streams fill the GPU and
-    // sharing it was measured slower than running the stages in turn)
-    const bool overlap = !(ctx.opt.debug_flags & 2) && pl.nleaf < 8192 && near_on;
-    bool near_done = false;
-    const double *sym_inc = nullptr;   // incoming slots of the symmetric near field (for k_l2p)
+    // cached near field: (the near field alone, without the far field's L2P,
+    // cannot use the symmetric cache's incoming slots: it is evaluated on the
+    // fly, and so is the adaptive tree's)
+    const bool want_cache = near_on && as.n_leaves > 0 && ctx.opt.near_cache_mb > 0 && (parts & 2) && !pl.adaptive;
+    if (want_cache) ensure_near_layout(ctx, pl, as);
+    const bool near_cached = want_cache && (as.near_q_len + 2 * as.near_d_len) * (f32 ? 4 : 8) <=
+                                               ((int64_t)ctx.opt.near_cache_mb << 20);
+    // cached P2M rows for small trees (there the compute kernel's chains are
+    // latency-bound; for large ones it beats reading the rows) when they fit
+    // the cache budget
+    const bool p2m_cached = far && ctx.opt.near_cache_mb > 0 && pl.nleaf < 8192 && !pl.adaptive &&
+                            (n0 + 2 * n1) * (int64_t)Pp * (int64_t)sizeof(double) <=
+                                ((int64_t)ctx.opt.near_cache_mb << 20);
+    // few items: four wavefronts each, which would otherwise leave the GPU
+    // with under about eight wavefronts per CU
+    const bool wide = as.n_items < 2048;
+    // Small trees: P2M and the near field in one launch, which reads the
+    // strengths through the permutation (k_p2m_near).  With more items the
+    // near field outlasts P2M by so much that it goes to a second stream, under
+    // the whole far field; large trees fill the GPU with either, and sharing it
+    // was measured no faster than running the stages in turn.  (A density
+    // solve on 28,672 nodes, 15 operator applications: 1.75 ms with the second
+    // stream, 1.63 in one launch; a step on 64^2 cells 1.41 and 1.10 ms; a pass
+    // over 4,096 + 1,536 points 66 and 65 us.)
+    const bool merged = far && near_cached && p2m_cached && wide && !(ctx.opt.debug_flags & 2);
+    const bool overlap = !merged && !(ctx.opt.debug_flags & 2) && pl.nleaf < 8192 && near_on;
+
+    double *qs = nullptr, *dns = nullptr;
+    Strengths st;
+    if (merged) {
+        st.perm = pl.perm.p;
+        st.q = q;
+        if (bie) {
+            st.w = bie->w;
+            st.sigma = bie->sigma;
+            st.normal = bie->normal;
+        } else {
+            st.dn = dn;
+        }
+    } else {
+        qs = pl.qs.ensure(n0 > 0 ? n0 : 1);
+        dns = pl.dns.ensure(n1 > 0 ? 2 * n1 : 1);
+        st.qs = qs;
+        st.dns = dns;
+        StageTimer tg(ctx, YK_STAGE_GATHER);
+        if (has_q) {
+            hipLaunchKernelGGL(k_gather_q, dim3(nblk(n0, 256)), dim3(256), 0, ctx.stream, n0, pl.perm.p, q, qs);
+            check_launch(ctx, "k_gather_q");
+        }
+        if (has_d && bie) {
+            hipLaunchKernelGGL(k_gather_dn_form, dim3(nblk(n1, 256)), dim3(256), 0, ctx.stream, pl.toff[1], n1,
+                               pl.perm.p, bie->w, bie->sigma, bie->normal, dns);
+            check_launch(ctx, "k_gather_dn_form");
+        } else if (has_d) {
+            hipLaunchKernelGGL(k_gather_dn, dim3(nblk(n1, 256)), dim3(256), 0, ctx.stream, pl.toff[1], n1,
+                               pl.perm.p, dn, dns);
+            check_launch(ctx, "k_gather_dn");
+        }
+    }
+    // an evaluation of the near field's values on their first use
+    const bool small_only = pl.near_tmax <= 1.0;
+    const int q_on = n0 > 0 ? 1 : 0, d_on = n1 > 0 ? 1 : 0;
+    auto build_near = [&](hipStream_t stream) {
+        bool &built = f32 ? as.near32 : as.near64;
+        if (built) return;
+        StageTimer tb(ctx, YK_STAGE_NEAR_BUILD, stream);
+        // (symmetric: charge values by the first kernel, dipole values by the second)
+        const int q_full = as.near_sym ? 0 : q_on;
+        const bool second = !as.near_sym || d_on;
+        if (f32) {
+            float *mq = as.nq32.ensure(std::max<int64_t>(as.near_q_len, 1));
+            float *md = as.nd32.ensure(std::max<int64_t>(2 * as.near_d_len, 1));
+            if (as.near_sym)
+                hipLaunchKernelGGL(pick_near_build_sym32(small_only), dim3(as.n_items), dim3(64), 0, stream,
+                                   as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, mask,
+                                   0.5 * inv_alpha, as.item_qoff.p, mq);
+            if (second)
+                hipLaunchKernelGGL(pick_near_build32(small_only), dim3(as.n_items), dim3(64), 0, stream,
+                                   as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, q_full,
+                                   d_on, mask, 0.5 * inv_alpha, as.item_qoff.p, as.item_doff.p, mq, md);
+        } else {
+            double *mq = as.nq64.ensure(std::max<int64_t>(as.near_q_len, 1));
+            double *md = as.nd64.ensure(std::max<int64_t>(2 * as.near_d_len, 1));
+            if (as.near_sym)
+                hipLaunchKernelGGL(pick_near_build_sym64(pl.near_terms, small_only), dim3(as.n_items), dim3(64), 0,
+                                   stream, as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p,
+                                   mask, 0.5 * inv_alpha, as.item_qoff.p, mq);
+            if (second)
+                hipLaunchKernelGGL(pick_near_build64(pl.near_terms, small_only), dim3(as.n_items), dim3(64), 0, stream,
+                                   as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, q_full,
+                                   d_on, mask, 0.5 * inv_alpha, as.item_qoff.p, as.item_doff.p, mq, md);
+        }
+        check_launch(ctx, "k_near_build");
+        built = true;
+    };
+    const NearFull nfull{as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, q_on, d_on, mask};
+    NearSym nsym{as.sym_desc.p, as.sym_desc_dst.p, nullptr};
+    if (near_cached && as.near_sym && has_q) nsym.inc = as.inc.ensure(std::max<int64_t>(as.inc_len, 1));
+    const double *sym_inc = near_cached && as.near_sym ? nsym.inc : nullptr;   // incoming slots (for k_l2p)
+    auto near_pass = [&](auto vt) {
+        using VT = decltype(vt);
+        NearPass<VT> np;
+        np.st = st;
+        np.off1 = pl.toff[1];
+        np.has_q = has_q;
+        np.has_d = has_d;
+        np.qoff = as.item_qoff.p;
+        np.doff = as.item_doff.p;
+        if constexpr (std::is_same<VT, float>::value) {
+            np.Mq = as.nq32.p;
+            np.Md = as.nd32.p;
+        } else {
+            np.Mq = as.nq64.p;
+            np.Md = as.nd64.p;
+        }
+        np.dip_scale = 0.5 * inv_alpha;
+        np.outs = outs;
+        return np;
+    };
+
+    // near field: independent of the far field until L2P
+    bool near_done = merged;
     auto launch_near = [&]() {
         near_done = true;
         if (!near_on) {   // far field alone: L2P adds it to zeros
@@ -2566,103 +2766,22 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
         }
         hipStream_t near_stream = overlap ? ctx.side : ctx.stream;
         if (as.n_leaves > 0) {
-            const bool f32 = prec == SUM_FP32, small_only = pl.near_tmax <= 1.0;
-            const int q_on = n0 > 0 ? 1 : 0, d_on = n1 > 0 ? 1 : 0;
-            // (the near field alone, without the far field's L2P, cannot use the
-            // symmetric cache's incoming slots: it is evaluated on the fly)
-            // (the adaptive tree's near field is evaluated on the fly)
-            const bool want_cache = ctx.opt.near_cache_mb > 0 && (parts & 2) && !pl.adaptive;
-            if (want_cache) ensure_near_layout(ctx, pl, as);
-            const int64_t entries = as.near_q_len + 2 * as.near_d_len;
-            const int64_t bytes = entries * (f32 ? 4 : 8);
-            const bool cache = want_cache && bytes <= ((int64_t)ctx.opt.near_cache_mb << 20);
-            if (cache) {
-                bool &built = f32 ? as.near32 : as.near64;
-                if (!built && as.near_sym) {
-                    // charge values in the symmetric layout, dipole values as below
-                    StageTimer tb(ctx, YK_STAGE_NEAR_BUILD, near_stream);
-                    if (f32) {
-                        float *mq = as.nq32.ensure(std::max<int64_t>(as.near_q_len, 1));
-                        float *md = as.nd32.ensure(std::max<int64_t>(2 * as.near_d_len, 1));
-                        hipLaunchKernelGGL(pick_near_build_sym32(small_only), dim3(as.n_items), dim3(64), 0,
-                                           near_stream, as.leaf_items.p, pl.lrange.p, pl.ulist_off.p,
-                                           pl.ulist.p, pl.px.p, pl.py.p, mask, 0.5 * inv_alpha, as.item_qoff.p,
-                                           mq);
-                        if (d_on)
-                            hipLaunchKernelGGL(pick_near_build32(small_only), dim3(as.n_items), dim3(64), 0,
-                                               near_stream, as.leaf_items.p, pl.lrange.p, pl.ulist_off.p,
-                                               pl.ulist.p, pl.px.p, pl.py.p, 0, d_on, mask, 0.5 * inv_alpha,
-                                               as.item_qoff.p, as.item_doff.p, mq, md);
-                    } else {
-                        double *mq = as.nq64.ensure(std::max<int64_t>(as.near_q_len, 1));
-                        double *md = as.nd64.ensure(std::max<int64_t>(2 * as.near_d_len, 1));
-                        hipLaunchKernelGGL(pick_near_build_sym64(pl.near_terms, small_only), dim3(as.n_items),
-                                           dim3(64), 0, near_stream, as.leaf_items.p, pl.lrange.p,
-                                           pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, mask, 0.5 * inv_alpha,
-                                           as.item_qoff.p, mq);
-                        if (d_on)
-                            hipLaunchKernelGGL(pick_near_build64(pl.near_terms, small_only), dim3(as.n_items),
-                                               dim3(64), 0, near_stream, as.leaf_items.p, pl.lrange.p,
-                                               pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, 0, d_on, mask,
-                                               0.5 * inv_alpha, as.item_qoff.p, as.item_doff.p, mq, md);
-                    }
-                    check_launch(ctx, "k_near_build_sym");
-                    built = true;
-                }
-                if (!built) {
-                    StageTimer tb(ctx, YK_STAGE_NEAR_BUILD, near_stream);
-                    if (f32) {
-                        float *mq = as.nq32.ensure(std::max<int64_t>(as.near_q_len, 1));
-                        float *md = as.nd32.ensure(std::max<int64_t>(2 * as.near_d_len, 1));
-                        hipLaunchKernelGGL(pick_near_build32(small_only), dim3(as.n_items), dim3(64), 0,
-                                           near_stream, as.leaf_items.p, pl.lrange.p, pl.ulist_off.p,
-                                           pl.ulist.p, pl.px.p, pl.py.p, q_on, d_on, mask, 0.5 * inv_alpha,
-                                           as.item_qoff.p, as.item_doff.p, mq, md);
-                    } else {
-                        double *mq = as.nq64.ensure(std::max<int64_t>(as.near_q_len, 1));
-                        double *md = as.nd64.ensure(std::max<int64_t>(2 * as.near_d_len, 1));
-                        hipLaunchKernelGGL(pick_near_build64(pl.near_terms, small_only), dim3(as.n_items),
-                                           dim3(64), 0, near_stream, as.leaf_items.p, pl.lrange.p,
-                                           pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, q_on, d_on, mask,
-                                           0.5 * inv_alpha, as.item_qoff.p, as.item_doff.p, mq, md);
-                    }
-                    check_launch(ctx, "k_near_build");
-                    built = true;
-                }
+            if (near_cached) {
+                build_near(near_stream);
                 StageTimer tl(ctx, YK_STAGE_LEAF, near_stream);
-                // four wavefronts per item when the items alone would leave
-                // the GPU with under about eight wavefronts per CU
-                const bool wide = as.n_items < 2048;
                 const dim3 blk(wide ? 256 : 64);
-                if (as.near_sym) {
-                    double *inc = has_q ? as.inc.ensure(std::max<int64_t>(as.inc_len, 1)) : nullptr;
-                    if (f32) {
-                        auto kern = wide ? k_near_apply_sym<float, 256> : k_near_apply_sym<float, 64>;
-                        hipLaunchKernelGGL(kern, dim3(as.n_items), blk, 0, near_stream, as.sym_desc.p,
-                                           as.sym_desc_dst.p, qs, dns, pl.toff[1], has_q, has_d,
-                                           as.item_qoff.p, as.item_doff.p, as.nq32.p, as.nd32.p, 0.5 * inv_alpha, outs,
-                                           inc);
+                auto apply = [&](auto vt) {
+                    using VT = decltype(vt);
+                    if (as.near_sym) {
+                        auto kern = wide ? k_near_apply_sym<VT, 256> : k_near_apply_sym<VT, 64>;
+                        hipLaunchKernelGGL(kern, dim3(as.n_items), blk, 0, near_stream, nsym, near_pass(vt));
                     } else {
-                        auto kern = wide ? k_near_apply_sym<double, 256> : k_near_apply_sym<double, 64>;
-                        hipLaunchKernelGGL(kern, dim3(as.n_items), blk, 0, near_stream, as.sym_desc.p,
-                                           as.sym_desc_dst.p, qs, dns, pl.toff[1], has_q, has_d,
-                                           as.item_qoff.p, as.item_doff.p, as.nq64.p, as.nd64.p, 0.5 * inv_alpha, outs,
-                                           inc);
+                        auto kern = wide ? k_near_apply<VT, 256> : k_near_apply<VT, 64>;
+                        hipLaunchKernelGGL(kern, dim3(as.n_items), blk, 0, near_stream, nfull, near_pass(vt));
                     }
-                    sym_inc = inc;
-                } else if (f32) {
-                    auto kern = wide ? k_near_apply<float, 256> : k_near_apply<float, 64>;
-                    hipLaunchKernelGGL(kern, dim3(as.n_items), blk, 0, near_stream,
-                                       as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, qs, dns,
-                                       pl.toff[1], q_on, d_on, has_q, has_d, mask, as.item_qoff.p,
-                                       as.item_doff.p, as.nq32.p, as.nd32.p, 0.5 * inv_alpha, outs);
-                } else {
-                    auto kern = wide ? k_near_apply<double, 256> : k_near_apply<double, 64>;
-                    hipLaunchKernelGGL(kern, dim3(as.n_items), blk, 0, near_stream,
-                                       as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, qs, dns,
-                                       pl.toff[1], q_on, d_on, has_q, has_d, mask, as.item_qoff.p,
-                                       as.item_doff.p, as.nq64.p, as.nd64.p, 0.5 * inv_alpha, outs);
-                }
+                };
+                if (f32) apply(0.f);
+                else apply(0.0);
                 check_launch(ctx, "k_near_apply");
             } else if (pl.adaptive) {
                 // one launch per item class: a leaf of side s meets pairs with
@@ -2695,7 +2814,7 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
     };
     const size_t lvl = (size_t)(p + 2);
     bool lc_clear = false;   // Lc already cleared (by the cached P2M kernel)
-    const int64_t lc_len = m2l_clear_len(pl, as, prec == SUM_FP32);
+    const int64_t lc_len = m2l_clear_len(pl, as, f32);
     if (far && pl.adaptive) {
         // P2M at the leaves of every level from lmin on (one launch per level,
         // the level's tables; leaves coarser than lmin need no multipole)
@@ -2722,13 +2841,8 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
     if (far) {
         // upward pass
         if (!pl.adaptive) {
-        // cached rows for small trees (there the compute kernel's chains are
-        // latency-bound; for large ones it beats reading the rows) when they
-        // fit the cache budget (built on first use)
-        const int64_t rows_bytes = (n0 + 2 * n1) * (int64_t)Pp * (int64_t)sizeof(double);
-        const bool p2m_cache = ctx.opt.near_cache_mb > 0 && pl.nleaf < 8192 && !pl.adaptive &&
-                               rows_bytes <= ((int64_t)ctx.opt.near_cache_mb << 20);
-        if (p2m_cache && !pl.p2m_rows_built) {
+        if (p2m_cached && !pl.p2m_rows_built) {
+            // cached rows (built on first use)
             StageTimer tb(ctx, YK_STAGE_NEAR_BUILD);
             double *rq = pl.p2m_rq.ensure(std::max<int64_t>(n0 * Pp, 1));
             double *rd = pl.p2m_rd.ensure(std::max<int64_t>(2 * n1 * Pp, 1));
@@ -2742,11 +2856,26 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
             pl.p2m_gs.release();
             pl.p2m_rows_built = true;
         }
+        const P2MApply pa{leaf_base,    pl.nleaf, pl.lrange.p, pl.p2m_rq.p, pl.p2m_rd.p, P, Pp, pl.M.p,
+                          pl.Lc.p, lc_len};
+        if (merged) {
+            build_near(ctx.stream);
+            StageTimer tm(ctx, YK_STAGE_LEAF);
+            const dim3 grid((unsigned)(as.n_items + pl.nleaf));
+            auto both = [&](auto vt) {
+                using VT = decltype(vt);
+                auto kern = as.near_sym ? k_p2m_near<VT, true> : k_p2m_near<VT, false>;
+                hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx.stream, pa, nfull, nsym, near_pass(vt), (int)as.n_items);
+            };
+            if (f32) both(0.f);
+            else both(0.0);
+            check_launch(ctx, "k_p2m_near");
+            lc_clear = true;
+        } else {
         StageTimer tm(ctx, YK_STAGE_P2M);
-        if (p2m_cache) {
-            hipLaunchKernelGGL(k_p2m_apply, dim3((unsigned)pl.nleaf), dim3(256), 0, ctx.stream,
-                               leaf_base, pl.nleaf, pl.lrange.p, pl.toff[1], has_q, has_d, qs, dns,
-                               pl.p2m_rq.p, pl.p2m_rd.p, P, Pp, pl.M.p, pl.Lc.p, (int64_t)pl.nbox * Pp);
+        if (p2m_cached) {
+            hipLaunchKernelGGL(k_p2m_apply, dim3((unsigned)pl.nleaf), dim3(256), 0, ctx.stream, pa, st, pl.toff[1],
+                               has_q, has_d);
             check_launch(ctx, "k_p2m_apply");
             lc_clear = true;
         } else {
@@ -2810,9 +2939,9 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
         check_launch(ctx, "k_p2m");
         }
         }
-        launch_near();
+        }
+        if (!near_done) launch_near();
         fmm_m2m(ctx, pl);
-        const bool f32 = prec == SUM_FP32;
         if (f32) {
             const int64_t nm = pl.nbox * (int64_t)Pp;
             float *mf = pl.Mf.ensure(nm);
