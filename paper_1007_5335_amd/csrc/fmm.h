@@ -66,6 +66,8 @@ constexpr int kShiftLevels = 3;
 constexpr int64_t kShiftWide = 512;
 
 // Boxes of one target mask that take part in the downward pass.
+constexpr int kLeafKinds = 6;
+
 struct ActiveSet {
     DevBuf<int32_t> m2l_boxes;         // active boxes of levels lmin..L, sorted by (level, class)
     DevBuf<int4> m2l_tiles;            // {level, class, start, count} into m2l_boxes
@@ -103,8 +105,7 @@ struct ActiveSet {
     DevBuf<int32_t> leaves;            // active leaves (leaf-local indices)
     int64_t n_leaves = 0;
     DevBuf<int2> leaf_items;           // {leaf, first target} work items of <= 64 targets
-    std::vector<int64_t> item_lev_begin;   // adaptive tree: items by class 2 level + (a coarser
-                                           // leaf touches it), 2 (L + 1) + 1 offsets
+    int item_kind[kLeafKinds + 1] = {};    // adaptive tree: first item of each kind of near-field series
     int64_t n_items = 0;
     int64_t n_m2l_boxes = 0;
     // work counts (for measurement)
@@ -232,8 +233,9 @@ struct FmmPlan {
     DevBuf<int32_t> leaf_box, box_leaf, blevel, leaf_lev;
     DevBuf<uint32_t> leaf_start;                   // first level-15 cell of each leaf (sorted)
     DevBuf<int32_t> alr;                           // [nbox][6] leaf ranges by box (split boxes: empty)
-    DevBuf<int32_t> p2m_list;                      // per level >= lmin: level-local indices of its leaves
-    std::vector<int64_t> p2m_off;                  // [L + 2] slices of p2m_list by level
+    DevBuf<int32_t> p2m_list;                      // the leaf boxes of levels >= lmin, by level
+    DevBuf<int4> p2m_tiles;                        // {level, first entry of p2m_list, entries <= 16, 0}
+    int64_t n_p2m = 0, n_p2m_tiles = 0;
     DevBuf<int32_t> woff, wl, wleaves;             // W lists (CSR over leaves), leaves with a W list
     int64_t n_wl = 0, n_wleaves = 0;
     DevBuf<int32_t> xbox, xoff, xl;                // X lists: boxes with one, CSR of source leaves
@@ -291,6 +293,9 @@ void launch_l2l_group(Context &ctx, FmmPlan &pl, ActiveSet &as, const ShiftGroup
 int64_t m2l_clear_len(const FmmPlan &pl, const ActiveSet &as, bool f32);
 // terms of the near-field K0/K1 series for pairs with t = r^2/(4 alpha^2) <= tmax
 int near_series_terms(double tmax);
+// the adaptive tree's near-field items by the series they need: kind 0 also
+// arguments beyond the series, the others up to 14, 10, 8, 6 and 5 terms
+int near_series_kind(double tmax);
 // I_0(x) .. I_nmax(x) in extended precision
 std::vector<long double> bessel_i_seq(long double x, int nmax);
 // the stages between the leaf multipoles and the leaf local expansions

@@ -279,18 +279,32 @@ __global__ __launch_bounds__(64) void k_p2m_quad(
     int64_t off1, int has_q, int has_d, double inv_alpha, double invR,
     const double *__restrict__ invFY, const double *__restrict__ da, const double *__restrict__ db,
     const double *__restrict__ cnn, const double *__restrict__ sc, int nser, int /*p*/, int Pp,
-    double *__restrict__ M, const int32_t *__restrict__ leaf_list, int accumulate) {
+    double *__restrict__ M, const int32_t *__restrict__ leaf_list, int accumulate,
+    const int4 *__restrict__ tiles, const int32_t *__restrict__ nser_lv, const double *__restrict__ invR_lv,
+    int sc_stride) {
     constexpr int p = PO, P = 2 * PO + 1;
     extern __shared__ double smem[];
+    int64_t first = (int64_t)blockIdx.x * (64 / LPL);
+    if (tiles) {   // adaptive tree: {level, first leaf, leaves} per workgroup, tables by level
+        const int4 t = tiles[blockIdx.x];
+        first = 0;
+        leaf_list += t.y;
+        nleaf = t.z;
+        nser = nser_lv[t.x];
+        invR = invR_lv[t.x];
+        sc += (int64_t)t.x * sc_stride;
+        invFY += (int64_t)t.x * (p + 2);
+        da += (int64_t)t.x * (p + 2);
+        db += (int64_t)t.x * (p + 2);
+    }
     double *t_sc = smem;                   // [2 nser] F_{p+1}, F_{p+2} series
     double *t_cnn = t_sc + 2 * nser;       // [p+2]
     double *t_ify = t_cnn + (p + 2);       // [p+2]
     double *t_da = t_ify + (p + 2);        // [p+1]
     double *t_db = t_da + (p + 1);         // [p+1]
-    constexpr int LPB = 64 / LPL;           // leaves per block
     const int lane = threadIdx.x, q4 = lane % LPL;
     // leaf_list (optional): the leaves to serve, nleaf of them
-    const int64_t lidx = (int64_t)blockIdx.x * LPB + lane / LPL;
+    const int64_t lidx = first + lane / LPL;
     const bool leaf_ok = lidx < nleaf;
     const int64_t li = leaf_ok ? (leaf_list ? (int64_t)leaf_list[lidx] : lidx) : 0;
     const int64_t b = leaf_base + li;
@@ -1311,11 +1325,18 @@ __device__ __forceinline__ double neg_half_log(double t, const double2 *__restri
     return __builtin_fma(de, h2_hi, c.y + __builtin_fma(de, h2_lo, s * r));
 }
 
+// (the forms for large arguments are called: inlined, the series of every loop
+// would share the registers with their constants)
+__device__ __attribute__((noinline)) double k0_large_c(double t) { return k0_large(2.0 * sqrt(t)); }
+__device__ __attribute__((noinline)) double k1oz4_large_c(double t) {
+    const double z = 2.0 * sqrt(t);
+    return 4.0 * k1_large(z) / z;
+}
 template <int NT, bool kSmallOnly>
 __device__ __forceinline__ double near_k0(double t, const double2 *__restrict__ tab) {
     if (kSmallOnly || t <= 1.0)
         return __builtin_fma(neg_half_log(t, tab), horner_n<NT>(yk_ser_A, t), horner_n<NT>(yk_ser_B, t));
-    return k0_large(2.0 * sqrt(t));
+    return k0_large_c(t);
 }
 // 4 K1(z)/z with t = z^2/4
 template <int NT, bool kSmallOnly>
@@ -1324,8 +1345,7 @@ __device__ __forceinline__ double near_k1oz4(double t, const double2 *__restrict
         const double h2 = 2.0 * neg_half_log(t, tab);
         return fast_rcp(t) - __builtin_fma(h2, horner_n<NT>(yk_ser_C, t), horner_n<NT>(yk_ser_D, t));
     }
-    const double z = 2.0 * sqrt(t);
-    return 4.0 * k1_large(z) / z;
+    return k1oz4_large_c(t);
 }
 
 template <int NT>
@@ -1371,6 +1391,9 @@ struct Near {
     }
 };
 
+// The pairs' arithmetic bounds it (one pair at a time per lane and more wavefronts
+// beat two in flight: the two pairs' registers cost a wavefront per SIMD; a
+// coincident pair is masked, not branched around).
 // One wavefront per item: up to 64 targets of one leaf.  With c targets, the
 // 64 lanes form g = floor(64/c) groups of c lanes; lane l serves target l mod c
 // and walks every g-th source of the leaf's U list, so at most c - 1 lanes
@@ -1379,50 +1402,58 @@ struct Near {
 // the end.  The result is the near field alone (k_l2p adds the far field).
 constexpr int kLeafStage = 192;
 
-// MU: the longest U list (9 in a uniform tree; 16 for the adaptive one, whose
-// 2:1 balance bounds it by 13)
-template <int NT, bool kSmallOnly, bool kF32 = false, int MU = 9>
-__global__ __launch_bounds__(64) void k_leaf(
-    const int2 *__restrict__ items, int64_t leaf_base, const int32_t *__restrict__ lrange,
-    const int32_t *__restrict__ uoff, const int32_t *__restrict__ ulist,
-    const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ qs,
-    const double *__restrict__ dns, int64_t off1, int has_q, int has_d, int mask, double inv2a,
-    double dip_scale, double *__restrict__ outs) {
-    __shared__ double s_x[kLeafStage], s_y[kLeafStage], s_a[kLeafStage], s_b[kLeafStage];
-    __shared__ double2 s_log[YK_LOG_TAB];
-    __shared__ int qa[MU], qn[MU], da[MU], dn_[MU];
-    const int2 item = items[xcd_remap(blockIdx.x, gridDim.x)];
+// the longest U list (9 in a uniform tree; the adaptive one's 2:1 balance
+// bounds it by 13)
+constexpr int kLeafU = 16;
+struct LeafLds {
+    double x[kLeafStage], y[kLeafStage], a[kLeafStage], b[kLeafStage];
+    // per source set: flat end of each U-list leaf's sources, their first index less the flat begin
+    int end[2][kLeafU], beg[2][kLeafU];
+};
+struct LeafArgs {
+    const int2 *items;
+    const int32_t *lrange, *uoff, *ulist;
+    const double *px, *py, *qs, *dns;
+    int64_t off1;
+    int has_q, has_d, mask;
+    double inv2a, dip_scale;
+    double *outs;
+};
+// one item by the calling wavefront (sync: over the wavefront; the log table is ready after the first)
+template <int NT, bool kSmallOnly, bool kF32, typename Sync>
+__device__ __forceinline__ void leaf_item(const int2 item, const LeafArgs &A, LeafLds &S,
+                                          const double2 *__restrict__ s_log, Sync sync) {
     const int li = item.x;
-    const int lane = threadIdx.x;
-    if constexpr (!kF32)
-        for (int i = lane; i < YK_LOG_TAB; i += 64) s_log[i] = make_double2(yk_log_tab[2 * i], yk_log_tab[2 * i + 1]);
+    const int lane = threadIdx.x & 63;
     int rs[3], re[3], ntot = 0;
     for (int s = 0; s < 3; ++s) {
-        rs[s] = lrange[li * 6 + 2 * s];
-        re[s] = (mask >> s) & 1 ? lrange[li * 6 + 2 * s + 1] : rs[s];
+        rs[s] = A.lrange[li * 6 + 2 * s];
+        re[s] = (A.mask >> s) & 1 ? A.lrange[li * 6 + 2 * s + 1] : rs[s];
         ntot += re[s] - rs[s];
     }
-    const int u0 = uoff[li], nu = uoff[li + 1] - u0;
-    // U-list source ranges (at most MU leaves) of the two source sets, in
-    // LDS (indexed per lane below; a private array would live in scratch)
-    if (lane < MU) {
-        const int u = lane;
-        int a = 0, an = 0, b2 = 0, bn = 0;
-        if (u < nu) {
-            const int ul = ulist[u0 + u];
-            a = lrange[ul * 6];
-            an = has_q ? lrange[ul * 6 + 1] - a : 0;
-            b2 = lrange[ul * 6 + 2];
-            bn = has_d ? lrange[ul * 6 + 3] - b2 : 0;
+    const int u0 = A.uoff[li], nu = A.uoff[li + 1] - u0;
+    // U-list source ranges of the two source sets (lanes 0 to 15 charges, 16 to
+    // 31 dipoles), in LDS for the lanes' searches below
+    {
+        const int u = lane & 15, set = (lane >> 4) & 1;
+        int a = 0, n = 0;
+        if (u < nu && (set == 0 ? A.has_q : A.has_d)) {
+            const int ul = A.ulist[u0 + u];
+            a = A.lrange[ul * 6 + 2 * set];
+            n = A.lrange[ul * 6 + 2 * set + 1] - a;
         }
-        qa[u] = a; qn[u] = an; da[u] = b2; dn_[u] = bn;
+        int end = n;
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) {
+            const int o = __shfl_up(end, m, 16);
+            if (u >= m) end += o;
+        }
+        if (lane < 32) {
+            S.end[set][u] = end;
+            S.beg[set][u] = a - (end - n);
+        }
     }
-    __syncthreads();
-    int nq = 0, nd = 0;
-    for (int u = 0; u < MU; ++u) {
-        nq += qn[u];
-        nd += dn_[u];
-    }
+    sync();
     const int tb = item.y;
     const int c = min(64, ntot - tb);          // >= 1 by construction of the items
     const int g = 64 / c;
@@ -1438,63 +1469,119 @@ __global__ __launch_bounds__(64) void k_leaf(
     // the difference of two nearby coordinates is exact, whereas scaling
     // first would round each coordinate, which costs digits in (x - y).n for
     // the nearly tangential pairs of densely sampled, tightly curved curves
-    const double xs = px[t], ys = py[t];
+    const double xs = A.px[t], ys = A.py[t];
     using NearT = Near<NT, kSmallOnly, kF32>;
     typename NearT::acc_t near_q = 0, near_d = 0;
     for (int set = 0; set < 2; ++set) {
-        const int ntot_s = set == 0 ? nq : nd;
+        const int ntot_s = S.end[set][kLeafU - 1];
         for (int c0 = 0; c0 < ntot_s; c0 += kLeafStage) {
             const int cn = min(kLeafStage, ntot_s - c0);
-            __syncthreads();
+            sync();
             // cooperative gather of flat source indices [c0, c0 + cn) into LDS
             for (int f = lane; f < cn; f += 64) {
-                int r = c0 + f, u = 0;
-                const int *cnt = set == 0 ? qn : dn_;
-                while (u < MU - 1 && r >= cnt[u]) { r -= cnt[u]; ++u; }
-                const int j = (set == 0 ? qa[u] : da[u]) + r;
-                s_x[f] = px[j];
-                s_y[f] = py[j];
+                int u = 0;   // its leaf: the first whose end is beyond it
+#pragma unroll
+                for (int m = kLeafU / 2; m >= 1; m >>= 1)
+                    if (S.end[set][u + m - 1] <= c0 + f) u += m;
+                const int j = S.beg[set][u] + c0 + f;
+                S.x[f] = A.px[j];
+                S.y[f] = A.py[j];
                 if (set == 0) {
-                    s_a[f] = qs[j];
+                    S.a[f] = A.qs[j];
                 } else {
-                    const int64_t jd = j - off1;
-                    s_a[f] = dns[2 * jd];
-                    s_b[f] = dns[2 * jd + 1];
+                    const int64_t jd = j - A.off1;
+                    S.a[f] = A.dns[2 * jd];
+                    S.b[f] = A.dns[2 * jd + 1];
                 }
             }
-            __syncthreads();
+            sync();
             if (valid) {
                 // full passes (every lane's source index in range), then the tail
                 const int nfull = cn - cn % g;
                 if (set == 0) {
                     auto pair = [&](int j) {
-                        const double dx = (xs - s_x[j]) * inv2a, dy = (ys - s_y[j]) * inv2a;
+                        const double dx = (xs - S.x[j]) * A.inv2a, dy = (ys - S.y[j]) * A.inv2a;
                         const double tt = __builtin_fma(dx, dx, dy * dy);
-                        if (tt > 0.0) near_q += NearT::charge(s_a[j], tt, s_log);
+                        const bool on = tt > 0.0;
+                        const auto v = NearT::charge(S.a[j], on ? tt : 1.0, s_log);
+                        near_q += on ? v : 0;
                     };
-#pragma unroll 2
+#pragma unroll 1
                     for (int jj = 0; jj < nfull; jj += g) pair(jj + sub);
                     if (nfull + sub < cn) pair(nfull + sub);
                 } else {
                     auto pair = [&](int j) {
-                        const double dx = (xs - s_x[j]) * inv2a, dy = (ys - s_y[j]) * inv2a;
+                        const double dx = (xs - S.x[j]) * A.inv2a, dy = (ys - S.y[j]) * A.inv2a;
                         const double tt = __builtin_fma(dx, dx, dy * dy);
-                        if (tt > 0.0) near_d += NearT::dipole(__builtin_fma(dx, s_a[j], dy * s_b[j]), tt, s_log);
+                        const bool on = tt > 0.0;
+                        const auto v =
+                            NearT::dipole(__builtin_fma(dx, S.a[j], dy * S.b[j]), on ? tt : 1.0, s_log);
+                        near_d += on ? v : 0;
                     };
-#pragma unroll 2
+#pragma unroll 1
                     for (int jj = 0; jj < nfull; jj += g) pair(jj + sub);
                     if (nfull + sub < cn) pair(nfull + sub);
                 }
             }
         }
     }
-    __syncthreads();
-    s_x[lane] = valid ? (double)near_q + dip_scale * (double)near_d : 0.0;
-    __syncthreads();
+    sync();
+    S.x[lane] = valid ? (double)near_q + A.dip_scale * (double)near_d : 0.0;
+    sync();
     if (sub == 0) {
         double tot = 0.0;
-        for (int gi = 0; gi < g; ++gi) tot += s_x[ti + gi * c];
-        outs[t] = tot * kInv2Pi;
+        for (int gi = 0; gi < g; ++gi) tot += S.x[ti + gi * c];
+        A.outs[t] = tot * kInv2Pi;
+    }
+}
+
+template <int NT, bool kSmallOnly, bool kF32 = false>
+__global__ __launch_bounds__(64) void k_leaf(LeafArgs A) {
+    __shared__ LeafLds S;
+    __shared__ double2 s_log[YK_LOG_TAB];
+    if constexpr (!kF32)
+        for (int i = threadIdx.x; i < YK_LOG_TAB; i += 64)
+            s_log[i] = make_double2(yk_log_tab[2 * i], yk_log_tab[2 * i + 1]);
+    leaf_item<NT, kSmallOnly, kF32>(A.items[xcd_remap(blockIdx.x, gridDim.x)], A, S, s_log, [] { __syncthreads(); });
+}
+
+// The adaptive tree's items in one launch: the items are ordered by the series
+// their pair distances need (kLeafKinds, the slowest first), four to a
+// workgroup, which share the table of logarithms.  One launch per class of
+// leaves (level, coarser neighbour) left the GPU to the last wavefronts of each
+// of some 16 classes, several of them of a few dozen leaves: on 1.5 M clustered
+// points 1,288 us, this launch 619 (of that, 173 registers at two wavefronts
+// per SIMD instead of five would cost 450).
+struct LeafKinds {
+    int block[kLeafKinds + 1];   // first workgroup of each kind (a multiple of 8: every XCD takes part in each)
+    int item[kLeafKinds + 1];    // first item
+};
+struct WaveSync {
+    __device__ __forceinline__ void operator()() const {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+};
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5))) void k_leaf_kinds(LeafArgs A, LeafKinds K) {
+    __shared__ LeafLds S[4];
+    __shared__ double2 s_log[YK_LOG_TAB];
+    for (int i = threadIdx.x; i < YK_LOG_TAB; i += 256)
+        s_log[i] = make_double2(yk_log_tab[2 * i], yk_log_tab[2 * i + 1]);
+    __syncthreads();   // (the wavefronts are independent from here on)
+    int k = 0;
+    while (k < kLeafKinds - 1 && (int)blockIdx.x >= K.block[k + 1]) ++k;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int it = K.item[k] + 4 * xcd_remap(blockIdx.x - K.block[k], K.block[k + 1] - K.block[k]) + w;
+    if (it >= K.item[k + 1]) return;
+    const int2 item = A.items[it];
+    switch (k) {
+    case 0: leaf_item<14, false, false>(item, A, S[w], s_log, WaveSync()); break;
+    case 1: leaf_item<14, true, false>(item, A, S[w], s_log, WaveSync()); break;
+    case 2: leaf_item<10, true, false>(item, A, S[w], s_log, WaveSync()); break;
+    case 3: leaf_item<8, true, false>(item, A, S[w], s_log, WaveSync()); break;
+    case 4: leaf_item<6, true, false>(item, A, S[w], s_log, WaveSync()); break;
+    default: leaf_item<5, true, false>(item, A, S[w], s_log, WaveSync()); break;
     }
 }
 
@@ -2167,9 +2254,7 @@ NearBuildSym32 pick_near_build_sym32(bool small_only) {
     return small_only ? k_near_build_sym<8, true, true> : k_near_build_sym<8, false, true>;
 }
 
-using LeafKernel = void (*)(const int2 *, int64_t, const int32_t *, const int32_t *,
-                            const int32_t *, const double *, const double *, const double *,
-                            const double *, int64_t, int, int, int, double, double, double *);
+using LeafKernel = void (*)(LeafArgs);
 
 // L2P: one thread per target point, adding the local expansion of the
 // point's leaf (Horner in z with G_m = F_m(y)/F_m(Y), F_m downwards) to the
@@ -2246,18 +2331,30 @@ __global__ __launch_bounds__(256) void k_l2p(
 // beyond this scaled distance K_0 < 1e-250: the pair is dropped (also keeps
 // K_0 and the ratio K_1/K_0 away from underflow)
 constexpr double kFarRho = 600.0;
-// The products I_n(R_l) K_n(rho) of the W and X translations, from I_0(R_l)
-// K_0(rho) by the ratios of I (a per-level table, rI[l] = {I_0(R_l),
-// I_n(R_l)/I_{n-1}(R_l)}) and of K (the upward recurrence K_{n+1} = K_{n-1} +
-// (2n/rho) K_n, stable for K, run on the ratios), so that no factor leaves
-// the range of doubles however small the box.
+// The products T_n = I_n(R_l) K_n(rho) of the W and X translations, from the
+// level's table rI[l] = {I_0(R_l), r_n = I_n(R_l)/I_{n-1}(R_l)} and the upward
+// recurrence of K (stable for K): with A_n = I_n K_{n-1} and B_n = I_n K_{n+1} =
+// A_n + (2n/rho) T_n, T_{n+1} = r_{n+1} B_n and A_{n+1} = r_{n+1} T_n.  Every
+// factor stays in range however small the box, all terms are positive, and no
+// order divides (a division per order was two thirds of the arithmetic).
+
+// {K_0, K_1}(z), called and not inlined: inlined into a loop over sources, the
+// some hundred constants of its two branches are kept in registers across the
+// loop (256 VGPRs, one wavefront per SIMD, scalar spills).  On 1.5 M clustered
+// points k_ad_p2l took 341 us inlined, 113 with the call at four wavefronts per
+// SIMD, k_ad_m2p 113 and 83.
+__device__ __attribute__((noinline)) double2 k01_called(double z) {
+    double2 r;
+    k01(z, r.x, r.y);
+    return r;
+}
 
 // W list (M2P): the multipole of every box of the leaf's W list evaluated at
 // the leaf's targets, phi(x) = sum_n M_n F^K_n((x - c)/alpha) =
 // M_0 K_0 + 2 sum_{n>=1} Re(M_n e^{in theta}) K_n, added to the near-field
 // sums in outs.  One wavefront per leaf, a lane per target; each target sums
 // its boxes in list order (deterministic, no atomics).
-__global__ __launch_bounds__(64) void k_ad_m2p(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_ad_m2p(
     const int32_t *__restrict__ wleaves, const int32_t *__restrict__ woff, const int32_t *__restrict__ wl,
     const int32_t *__restrict__ lrange, int mask, const int32_t *__restrict__ blevel,
     const double *__restrict__ bcx, const double *__restrict__ bcy, const double *__restrict__ px,
@@ -2294,19 +2391,23 @@ __global__ __launch_bounds__(64) void k_ad_m2p(
                 const double rho = sqrt(wx * wx + wy * wy), ir = 1.0 / rho;
                 if (rho > kFarRho) continue;          // below 1e-250 of the box's sources
                 const double c = wx * ir, sn = wy * ir;
-                const double k0v = k0(rho);
-                double rk = k1(rho) / k0v;            // K_1 / K_0
-                double T0 = ri[0] * k0v;              // I_0(R) K_0(rho)
-                double sum = Md[0] * T0;
-                double er = c, ei = sn;               // e^{i n theta}
+                const double2 k01v = k01_called(rho);
+                double T = ri[0] * k01v.x, A = ri[0] * k01v.y;   // T_0; A_0 = I_0 K_1
+                const double T0 = T;
+                double sum = 0.0, m2 = 0.0;
+                double er = 1.0, ei = 0.0;            // e^{i n theta}
+#pragma unroll 4
                 for (int n = 1; n <= p; ++n) {
-                    T0 *= ri[n] * rk;                 // I_n(R) K_n(rho)
-                    sum += 2.0 * T0 * (Md[2 * n - 1] * er - Md[2 * n] * ei);
-                    rk = 1.0 / rk + 2.0 * n * ir;     // K_{n+1} / K_n
+                    const double B = A + m2 * ir * T;             // I_{n-1} K_n
+                    A = ri[n] * T;
+                    T = ri[n] * B;                                // T_n
+                    m2 += 2.0;
                     const double nr = er * c - ei * sn;
                     ei = er * sn + ei * c;
                     er = nr;
+                    sum += T * (Md[2 * n - 1] * er - Md[2 * n] * ei);
                 }
+                sum = Md[0] * T0 + 2.0 * sum;
                 acc += sum;
             }
         }
@@ -2316,108 +2417,292 @@ __global__ __launch_bounds__(64) void k_ad_m2p(
     }
 }
 
+// Sums over a wavefront's sources, eight orders at a time: every lane writes
+// its source's terms to LDS (row 2i the real, 2i + 1 the imaginary part of the
+// chunk's order i), then lane (row l / 4, part l % 4) adds up every fourth entry
+// of its row.  The row stride puts the 32 entries that half a wavefront reads
+// in different banks.  Nine KB per wavefront leave the occupancy to the
+// registers.
+constexpr int kSumStride = 68;
+constexpr int kSumLds = 16 * kSumStride;
+struct OrderSums {
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};   // chunk c: orders 8c .. 8c + 7 (p <= 31)
+    __device__ __forceinline__ void add(const double *sh, int c) {
+        const double *r = sh + (threadIdx.x >> 2) * kSumStride + (threadIdx.x & 3);
+        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; k += 2) {
+            s0 += r[4 * k];
+            s1 += r[4 * k + 4];
+        }
+        s0 += s1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] += k == c ? s0 : 0.0;
+    }
+    // put(output, sum) for the outputs 0 .. 2p, each from one lane
+    template <typename Put> __device__ __forceinline__ void store(int p, Put put) {
+        const int row = threadIdx.x >> 2, im = row & 1;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            double v = acc[c];
+            v += dpp_d<0xB1>(v);    // quad_perm [1,0,3,2]
+            v += dpp_d<0x4E>(v);    // quad_perm [2,3,0,1]
+            const int n = 8 * c + (row >> 1);
+            if ((threadIdx.x & 3) == 0 && n <= p && (n > 0 || !im)) put(n == 0 ? 0 : 2 * n - 1 + im, v);
+        }
+    }
+};
+
 // X list (P2L): the sources of every leaf of the box's X list into the box's
 // local expansion (scaled, Lh_m = L_m I_m(R_l)).  By Graf's addition theorem a
 // charge q at w = (y - c)/alpha contributes L_m = q K_m(|w|) e^{-i m theta};
 // a dipole D = d (n_x + i n_y), the normal derivative at y of that,
 // L_m = -(1/(2 alpha)) [conj(D) K_{|m-1|} e^{-i(m-1) theta} + D K_{m+1}
-// e^{-i(m+1) theta}].  One wavefront per box: per batch of 64 sources each
-// lane writes its source's P terms to LDS, then lane o adds up output o over
-// the batch (a fixed order); the box's row is added once at the end.
-constexpr int kP2LStride = 65;   // LDS row stride (doubles): conflict-free transposed reads
-
-__global__ __launch_bounds__(64) void k_ad_p2l(
+// e^{-i(m+1) theta}]; with a + i b = D e^{-i theta}/(2 alpha) and A, B as above
+// that is -(A + B) a cos(m theta) - (B - A) b sin(m theta) and
+// (A + B) a sin(m theta) - (B - A) b cos(m theta).
+// One wavefront per box, a lane per source.  FP64 issue bounds it (the orders
+// and K0, K1), so lanes are kept busy: the sources of up to 64 leaves form one
+// run, which the lanes take 64 at a time (leaf by leaf, leaves of some 15
+// points left three lanes of four idle).
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_ad_p2l(
     const int32_t *__restrict__ xbox, const int32_t *__restrict__ xoff, const int32_t *__restrict__ xl,
     const int32_t *__restrict__ lrange, int has_q, int has_d, const int32_t *__restrict__ blevel,
     const double *__restrict__ bcx, const double *__restrict__ bcy, const double *__restrict__ px,
     const double *__restrict__ py, const double *__restrict__ qs, const double *__restrict__ dns, int64_t off1,
     const double *__restrict__ rI, int p, int Pp, double inv_alpha, double *__restrict__ Lc) {
-    extern __shared__ double sh[];   // [Pp][kP2LStride]
+    __shared__ double sh[kSumLds];
+    __shared__ int s_end[64], s_beg[64];   // flat end of each leaf's sources; their first index less the flat begin
     const int lane = threadIdx.x;
     const int32_t d = xbox[blockIdx.x];
     const double *ri = rI + (int64_t)blevel[d] * (p + 3);
     const double cx = bcx[d], cy = bcy[d], h = 0.5 * inv_alpha;
-    const int P = 2 * p + 1;
-    double acc = 0.0;
-    for (int xi = xoff[blockIdx.x]; xi < xoff[blockIdx.x + 1]; ++xi) {
-        const int32_t c = xl[xi];
+    const int xe = xoff[blockIdx.x + 1];
+    OrderSums sums;
+    for (int x0 = xoff[blockIdx.x]; x0 < xe; x0 += 64) {
         for (int set = 0; set < 2; ++set) {
             if ((set == 0 && !has_q) || (set == 1 && !has_d)) continue;
-            const int a = lrange[c * 6 + 2 * set], e = lrange[c * 6 + 2 * set + 1];
-            for (int base = a; base < e; base += 64) {
-                const int j = base + lane;
-                double *col = sh + lane;
-                const double wx = j < e ? (px[j] - cx) * inv_alpha : 0.0;
-                const double wy = j < e ? (py[j] - cy) * inv_alpha : 0.0;
-                const double rho = sqrt(wx * wx + wy * wy);
-                if (j < e && rho <= kFarRho) {
-                    const double ir = 1.0 / rho;
-                    const double co = wx * ir, sn = wy * ir;
-                    const double k0v = k0(rho);
-                    double rk = k1(rho) / k0v;
-                    double T = ri[0] * k0v;                    // T_0 = I_0 K_0
-                    if (set == 0) {
-                        const double q = qs[j];
-                        col[0] = q * T;
-                        double er = co, ei = sn;
-                        for (int m = 1; m <= p; ++m) {
-                            T *= ri[m] * rk;                   // T_m
-                            rk = 1.0 / rk + 2.0 * m * ir;
-                            col[(2 * m - 1) * kP2LStride] = q * T * er;
-                            col[(2 * m) * kP2LStride] = -q * T * ei;
+            int a = 0, n = 0;
+            if (x0 + lane < xe) {
+                const int32_t c = xl[x0 + lane];
+                a = lrange[c * 6 + 2 * set];
+                n = lrange[c * 6 + 2 * set + 1] - a;
+            }
+            int end = n;
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) {
+                const int o = __shfl_up(end, m, 64);
+                if (lane >= m) end += o;
+            }
+            const int tot = __shfl(end, 63, 64);
+            __syncthreads();
+            s_end[lane] = end;
+            s_beg[lane] = a - (end - n);
+            __syncthreads();
+            for (int base = 0; base < tot; base += 64) {
+                const int f = base + lane;
+                int k = 0;   // the leaf of source f: the first whose end is beyond it
+#pragma unroll
+                for (int m = 32; m >= 1; m >>= 1)
+                    if (s_end[k + m - 1] <= f) k += m;
+                bool on = f < tot;
+                const int j = on ? s_beg[k] + f : 0;
+                double wx = 1.0, wy = 0.0;
+                if (on) {
+                    wx = (px[j] - cx) * inv_alpha;
+                    wy = (py[j] - cy) * inv_alpha;
+                }
+                double rho = sqrt(wx * wx + wy * wy);
+                if (rho > kFarRho) {
+                    on = false;
+                    rho = wx = 1.0;
+                    wy = 0.0;
+                }
+                const double ir = 1.0 / rho;
+                const double co = wx * ir, sn = wy * ir;
+                const double2 k01v = k01_called(rho);
+                double T = ri[0] * k01v.x, A = ri[0] * k01v.y;   // T_0; at order 0, A = B = I_0 K_1
+                double m2 = 0.0, er = 1.0, ei = 0.0;               // 2m, e^{i m theta}
+                auto orders = [&](auto emit) {
+                    for (int c = 0; 8 * c <= p; ++c) {
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            const int m = 8 * c + i;
+                            if (m > p) break;
+                            const double ct = m2 * ir * T, B = A + ct;
+                            emit(sh + 2 * i * kSumStride + lane, T, A + B, ct);
+                            A = ri[m + 1] * T;
+                            T = ri[m + 1] * B;
+                            m2 += 2.0;
                             const double nr = er * co - ei * sn;
                             ei = er * sn + ei * co;
                             er = nr;
                         }
-                    } else {
-                        const double Dx = dns[2 * (j - off1)], Dy = dns[2 * (j - off1) + 1];
-                        // T_m and T_{m+1} side by side: A_m = K_{|m-1|} I_m, B_m = K_{m+1} I_m
-                        double Tn = T * ri[1] * rk;            // T_1
-                        rk = 1.0 / rk + 2.0 * ir;              // K_2 / K_1
-                        double Tp = T;                         // T_{m-1} (unused at m = 0)
-                        // m = 0: A_0 = B_0 = K_1 I_0 = T_1 / (I_1/I_0)
-                        const double B0 = Tn / ri[1];
-                        col[0] = -2.0 * h * B0 * (Dx * co + Dy * sn);
-                        double ur = 1.0, ui = 0.0;             // e^{i(m-1) theta} at m = 1
-                        double vr = co * co - sn * sn, vi = 2.0 * co * sn;   // e^{i(m+1) theta} at m = 1
-                        double Tm = Tn;                        // T_m at m = 1
-                        for (int m = 1; m <= p; ++m) {
-                            Tn = Tm * ri[m + 1] * rk;          // T_{m+1}
-                            rk = 1.0 / rk + 2.0 * (m + 1) * ir;
-                            const double A = Tp * ri[m];       // K_{m-1} I_m
-                            const double B = Tn / ri[m + 1];   // K_{m+1} I_m
-                            const double re = -h * (A * (Dx * ur - Dy * ui) + B * (Dx * vr + Dy * vi));
-                            const double im = -h * (-A * (Dx * ui + Dy * ur) + B * (Dy * vr - Dx * vi));
-                            col[(2 * m - 1) * kP2LStride] = re;
-                            col[(2 * m) * kP2LStride] = im;
-                            Tp = Tm;
-                            Tm = Tn;
-                            double t2 = ur * co - ui * sn;
-                            ui = ur * sn + ui * co;
-                            ur = t2;
-                            t2 = vr * co - vi * sn;
-                            vi = vr * sn + vi * co;
-                            vr = t2;
-                        }
+                        __syncthreads();
+                        sums.add(sh, c);
+                        __syncthreads();
                     }
+                };
+                if (set == 0) {
+                    const double q = on ? qs[j] : 0.0;
+                    orders([&](double *row, double t, double, double) {
+                        const double qt = q * t;
+                        row[0] = qt * er;
+                        row[kSumStride] = -qt * ei;
+                    });
                 } else {
-                    for (int o = 0; o < P; ++o) col[o * kP2LStride] = 0.0;
+                    const double Dx = on ? h * dns[2 * (j - off1)] : 0.0, Dy = on ? h * dns[2 * (j - off1) + 1] : 0.0;
+                    const double ra = Dx * co + Dy * sn, rb = Dy * co - Dx * sn;
+                    orders([&](double *row, double, double ab, double ct) {
+                        const double sa = ab * ra, tb = ct * rb;
+                        row[0] = -(sa * er + tb * ei);
+                        row[kSumStride] = sa * ei - tb * er;
+                    });
                 }
-                __syncthreads();
-                if (lane < P) {
-                    const double *row = sh + lane * kP2LStride;
-                    double s0 = 0.0, s1 = 0.0;
-                    for (int k = 0; k < 64; k += 2) {
-                        s0 += row[k];
-                        s1 += row[k + 1];
-                    }
-                    acc += s0 + s1;
-                }
-                __syncthreads();
             }
         }
     }
-    if (lane < P) Lc[(int64_t)d * Pp + lane] += acc;
+    sums.store(p, [&](int o, double v) { Lc[(int64_t)d * Pp + o] += v; });
+}
+
+// P2M, one wavefront per leaf (entry of leaf_list: leaf_base plus it is the
+// box), a lane per point: for few leaves, where k_p2m_quad's chains of points
+// per lane leave the GPU idle and its unrolled code is fetched for a few
+// wavefronts only.  Per chunk of eight orders, the highest first: F_n further
+// down, then the terms with the powers of conj(z) from the chunk's first order
+// up, summed over the lanes as OrderSums says.  blevel: the box's level (its
+// tables); null: all at level lev.
+// Up to kP2MWaveLeaves leaves (of some 15 points): 4.4 k leaves 15 us against
+// 19 by quads, 9 k 23 against 20, 18 k 38 against 24 (order 24).
+constexpr int64_t kP2MWaveLeaves = 6144;
+struct P2MTables {
+    const int32_t *blevel;
+    int lev;
+    const double *sc;           // F_{p+1}, F_{p+2} series, sc_stride per level
+    const int32_t *nser_lv;     // null: nser
+    const double *invR_lv;      // null: invR
+    const double *invFY, *da, *db, *cnn;
+    int sc_stride, nser;
+    double invR;
+};
+__global__ __launch_bounds__(64) void k_p2m_wave(
+    int64_t leaf_base, const int32_t *__restrict__ leaf_list, const int32_t *__restrict__ lrange,
+    const double *__restrict__ bcx, const double *__restrict__ bcy, const double *__restrict__ px,
+    const double *__restrict__ py, const double *__restrict__ qs, const double *__restrict__ dns, int64_t off1,
+    int has_q, int has_d, double inv_alpha, P2MTables tb, int p, int Pp, double *__restrict__ M, int accumulate) {
+    __shared__ double sh[kSumLds];
+    const int lane = threadIdx.x;
+    const int64_t li = leaf_list[blockIdx.x], b = leaf_base + li;
+    const int l = tb.blevel ? tb.blevel[b] : tb.lev;
+    const double *ify = tb.invFY + (int64_t)l * (p + 2), *cnn = tb.cnn;
+    const double *da = tb.da + (int64_t)l * (p + 2), *db = tb.db + (int64_t)l * (p + 2);
+    const double *sc = tb.sc + (int64_t)l * tb.sc_stride;
+    const int nser = tb.nser_lv ? tb.nser_lv[l] : tb.nser;
+    const double invR = tb.invR_lv ? tb.invR_lv[l] : tb.invR;
+    const double cx = bcx[b], cy = bcy[b];
+    const int ctop = p >> 3;
+    OrderSums sums;
+    for (int set = 0; set < 2; ++set) {
+        if ((set == 0 && !has_q) || (set == 1 && !has_d)) continue;
+        const int s0 = lrange[li * 6 + 2 * set], e0 = lrange[li * 6 + 2 * set + 1];
+        for (int base = s0; base < e0; base += 64) {
+            const int j = min(base + lane, e0 - 1);
+            const bool on = base + lane < e0;
+            const double wx = (px[j] - cx) * inv_alpha, wy = (py[j] - cy) * inv_alpha;
+            const double y = 0.25 * (wx * wx + wy * wy);
+            const double zx = wx * invR, zy = -wy * invR;   // conj(w)/R
+            double F1, F2;
+            f_start(y, sc, nser, F1, F2);
+            auto fnext = [&](int n) {   // F_n / F_n(Y), downwards from n = p
+                const double F0 = F1 + y * F2 * cnn[n];
+                F2 = F1;
+                F1 = F0;
+                return F0 * ify[n];
+            };
+            // conj(z)^2 and ^8, and the chunks' first powers 8c - set
+            const double z2r = zx * zx - zy * zy, z2i = 2.0 * zx * zy;
+            const double z4r = z2r * z2r - z2i * z2i, z4i = 2.0 * z2r * z2i;
+            const double z8r = z4r * z4r - z4i * z4i, z8i = 2.0 * z4r * z4i;
+            double u1r = z8r, u1i = z8i;
+            if (set == 1) {   // conj(z)^7
+                const double z3r = z2r * zx - z2i * zy, z3i = z2r * zy + z2i * zx;
+                u1r = z4r * z3r - z4i * z3i;
+                u1i = z4r * z3i + z4i * z3r;
+            }
+            const double u2r = u1r * z8r - u1i * z8i, u2i = u1r * z8i + u1i * z8r;
+            const double u3r = u2r * z8r - u2i * z8i, u3i = u2r * z8i + u2i * z8r;
+            auto first_power = [&](int c, double &wr, double &wi) {
+                wr = c == 3 ? u3r : c == 2 ? u2r : c == 1 ? u1r : 1.0;
+                wi = c == 3 ? u3i : c == 2 ? u2i : c == 1 ? u1i : 0.0;
+            };
+            auto up = [&](double &wr, double &wi) {
+                const double nr = wr * zx - wi * zy;
+                wi = wr * zy + wi * zx;
+                wr = nr;
+            };
+            if (set == 0) {
+                const double q = on ? qs[j] : 0.0;
+                for (int c = ctop; c >= 0; --c) {
+                    double g[8], wr, wi;
+#pragma unroll
+                    for (int i = 7; i >= 0; --i) g[i] = 8 * c + i <= p ? fnext(8 * c + i) : 0.0;
+                    first_power(c, wr, wi);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const double t = q * g[i];
+                        double *row = sh + 2 * i * kSumStride + lane;
+                        row[0] = t * wr;
+                        row[kSumStride] = t * wi;
+                        up(wr, wi);
+                    }
+                    __syncthreads();
+                    sums.add(sh, c);
+                    __syncthreads();
+                }
+            } else {
+                // term_n = h [a_n D Psi_{n+1} + b_n conj(D) Psi_{n-1}], Psi_k = G_k
+                // conj(z)^k, Psi_{-1} = conj(Psi_1); h folded into D, E = D conj(z)^2
+                const double h = on ? 0.5 * inv_alpha : 0.0;
+                const double Dx = h * dns[2 * (j - off1)], Dy = h * dns[2 * (j - off1) + 1];
+                const double Ex = Dx * z2r - Dy * z2i, Ey = Dx * z2i + Dy * z2r;
+                auto gn = [&](int n) { return n <= p ? fnext(n) : n == p + 1 ? F1 * ify[n] : 0.0; };
+                double g[10];   // G_{8c-1} .. G_{8c+8}
+                g[1] = gn(8 * ctop + 8);
+                g[0] = gn(8 * ctop + 7);
+                for (int c = ctop; c >= 0; --c) {
+                    g[9] = g[1];
+                    g[8] = g[0];
+#pragma unroll
+                    for (int k = 7; k >= 1; --k) g[k] = gn(8 * c - 1 + k);
+                    g[0] = c > 0 ? gn(8 * c - 1) : 0.0;
+                    double wr, wi;   // conj(z)^(n-1)
+                    first_power(c, wr, wi);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int n = 8 * c + i;
+                        double *row = sh + 2 * i * kSumStride + lane;
+                        if (n == 0) {   // the real part alone: (a + b) Re(D Psi_1)
+                            row[0] = (da[0] + db[0]) * (g[2] * (Dx * zx - Dy * zy));
+                            row[kSumStride] = 0.0;
+                        } else if (n <= p) {
+                            const double X = da[n] * g[i + 2], Y = db[n] * g[i];
+                            const double tr = X * Ex + Y * Dx, ti = X * Ey - Y * Dy;
+                            row[0] = tr * wr - ti * wi;
+                            row[kSumStride] = tr * wi + ti * wr;
+                            up(wr, wi);
+                        }
+                    }
+                    __syncthreads();
+                    sums.add(sh, c);
+                    __syncthreads();
+                }
+            }
+        }
+    }
+    double *Mb = M + b * Pp;
+    sums.store(p, [&](int o, double v) { Mb[o] = accumulate ? Mb[o] + v : v; });
+    if (!accumulate)
+        for (int o = 2 * p + 1 + lane; o < Pp; o += 64) Mb[o] = 0.0;
 }
 
 // L2P of the adaptive tree: as k_l2p, with the leaf's level (and its tables)
@@ -2471,18 +2756,7 @@ __global__ __launch_bounds__(256) void k_ad_l2p(
         o[i] = v;
 }
 
-LeafKernel pick_leaf_kernel(int nt, bool small_only, bool f32, bool adaptive) {
-    if (adaptive) {
-        if (f32) return small_only ? k_leaf<8, true, true, 16> : k_leaf<8, false, true, 16>;
-        if (small_only) {
-            if (nt <= 5) return k_leaf<5, true, false, 16>;
-            if (nt <= 6) return k_leaf<6, true, false, 16>;
-            if (nt <= 8) return k_leaf<8, true, false, 16>;
-            if (nt <= 10) return k_leaf<10, true, false, 16>;
-            return k_leaf<14, true, false, 16>;
-        }
-        return k_leaf<14, false, false, 16>;
-    }
+LeafKernel pick_leaf_kernel(int nt, bool small_only, bool f32) {
     if (f32) return small_only ? k_leaf<8, true, true> : k_leaf<8, false, true>;
     if (small_only) {
         if (nt <= 5) return k_leaf<5, true>;
@@ -2783,30 +3057,32 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                 if (f32) apply(0.f);
                 else apply(0.0);
                 check_launch(ctx, "k_near_apply");
-            } else if (pl.adaptive) {
-                // one launch per item class: a leaf of side s meets pairs with
-                // t = r^2/(4 alpha^2) <= 2 s^2/alpha^2 among leaves of its size
-                // or finer, 4.5 s^2/alpha^2 with a coarser one (at a corner);
-                // the fine levels take short series
-                StageTimer tl(ctx, YK_STAGE_LEAF, near_stream);
-                for (int k = 0; k < 2 * (L + 1); ++k) {
-                    const int64_t i0 = as.item_lev_begin[k], ni = as.item_lev_begin[k + 1] - i0;
-                    if (ni == 0) continue;
-                    const int l = k >> 1;
-                    const double tl_max = ((k & 1) ? 4.5 : 2.0) * pl.lev[l].side * pl.lev[l].side * inv_alpha *
-                                          inv_alpha;
-                    LeafKernel kern = pick_leaf_kernel(near_series_terms(tl_max), tl_max <= 1.0, f32, true);
-                    hipLaunchKernelGGL(kern, dim3((unsigned)ni), dim3(64), 0, near_stream, as.leaf_items.p + i0,
-                                       leaf_base, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, qs,
-                                       dns, pl.toff[1], has_q, has_d, mask, 0.5 * inv_alpha, 0.5 * inv_alpha, outs);
-                    check_launch(ctx, "k_leaf");
-                }
             } else {
-                LeafKernel kern = pick_leaf_kernel(pl.near_terms, small_only, f32, pl.adaptive);
                 StageTimer tl(ctx, YK_STAGE_LEAF, near_stream);
-                hipLaunchKernelGGL(kern, dim3(as.n_items), dim3(64), 0, near_stream, as.leaf_items.p,
-                                   leaf_base, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, qs,
-                                   dns, pl.toff[1], has_q, has_d, mask, 0.5 * inv_alpha, 0.5 * inv_alpha, outs);
+                LeafArgs la{as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, qs, dns,
+                            pl.toff[1], has_q, has_d, mask, 0.5 * inv_alpha, 0.5 * inv_alpha, outs};
+                if (!pl.adaptive) {
+                    hipLaunchKernelGGL(pick_leaf_kernel(pl.near_terms, small_only, f32), dim3(as.n_items), dim3(64), 0,
+                                       near_stream, la);
+                } else if (f32) {
+                    // the kind with large arguments, then the others (one series serves them)
+                    const int n_large = as.item_kind[1];
+                    if (n_large > 0)
+                        hipLaunchKernelGGL((k_leaf<8, false, true>), dim3(n_large), dim3(64), 0, near_stream, la);
+                    la.items += n_large;
+                    if (as.n_items > n_large)
+                        hipLaunchKernelGGL((k_leaf<8, true, true>), dim3(as.n_items - n_large), dim3(64), 0,
+                                           near_stream, la);
+                } else {
+                    LeafKinds lk;
+                    int blocks = 0;
+                    for (int k = 0; k <= kLeafKinds; ++k) {
+                        lk.block[k] = blocks;
+                        lk.item[k] = as.item_kind[k];
+                        if (k < kLeafKinds) blocks += ((as.item_kind[k + 1] - as.item_kind[k] + 3) / 4 + 7) / 8 * 8;
+                    }
+                    hipLaunchKernelGGL(k_leaf_kinds, dim3(blocks), dim3(256), 0, near_stream, la, lk);
+                }
                 check_launch(ctx, "k_leaf");
             }
         }
@@ -2816,25 +3092,28 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
     bool lc_clear = false;   // Lc already cleared (by the cached P2M kernel)
     const int64_t lc_len = m2l_clear_len(pl, as, f32);
     if (far && pl.adaptive) {
-        // P2M at the leaves of every level from lmin on (one launch per level,
-        // the level's tables; leaves coarser than lmin need no multipole)
+        // P2M at the leaves of every level from lmin on, with the level's tables
+        // (leaves coarser than lmin need no multipole)
         StageTimer tm(ctx, YK_STAGE_P2M);
         pl.mq_kept = false;
+        const int64_t nl = pl.n_p2m;
         auto quad4 = p == 8 ? k_p2m_quad<8, 4> : p == 12 ? k_p2m_quad<12, 4> : p == 16 ? k_p2m_quad<16, 4>
                    : p == 20 ? k_p2m_quad<20, 4> : p == 24 ? k_p2m_quad<24, 4> : p == 28 ? k_p2m_quad<28, 4>
                    : p == 31 ? k_p2m_quad<31, 4> : nullptr;
         YK_REQUIRE(quad4 != nullptr, "no P2M kernel for this order");
-        for (int l = pl.lmin; l <= L; ++l) {
-            const int64_t nl = pl.p2m_off[l + 1] - pl.p2m_off[l];
-            if (nl == 0) continue;
-            const int ns = pl.nser_lv[l];
-            const size_t tabs = (2 * (size_t)ns + 4 * (size_t)(p + 2)) * sizeof(double);
-            hipLaunchKernelGGL(quad4, dim3((unsigned)((nl + 15) / 16)), dim3(64), tabs, ctx.stream,
-                               pl.lev[l].begin, nl, pl.alr.p + pl.lev[l].begin * 6, pl.bcx.p, pl.bcy.p, pl.px.p,
-                               pl.py.p, qs, dns, pl.toff[1], has_q, has_d, inv_alpha, 1.0 / pl.lev[l].R,
-                               pl.invFY.p + l * lvl, pl.dipa.p + l * lvl, pl.dipb.p + l * lvl, pl.cnn.p,
-                               pl.serc_lv.p + (size_t)l * 2 * pl.nser_stride, ns, p, Pp, pl.M.p,
-                               pl.p2m_list.p + pl.p2m_off[l], 0);
+        if (nl > 0 && nl < kP2MWaveLeaves) {
+            const P2MTables tb{pl.blevel.p, 0, pl.serc_lv.p, pl.nser_dev.p, pl.invR_lv.p, pl.invFY.p, pl.dipa.p,
+                               pl.dipb.p, pl.cnn.p, 2 * pl.nser_stride, 0, 0.0};
+            hipLaunchKernelGGL(k_p2m_wave, dim3((unsigned)nl), dim3(64), 0, ctx.stream, 0, pl.p2m_list.p, pl.alr.p,
+                               pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs, dns, pl.toff[1], has_q, has_d, inv_alpha, tb,
+                               p, Pp, pl.M.p, 0);
+            check_launch(ctx, "k_p2m_wave");
+        } else if (nl > 0) {
+            const size_t tabs = (2 * (size_t)pl.nser_stride + 4 * (size_t)(p + 2)) * sizeof(double);
+            hipLaunchKernelGGL(quad4, dim3((unsigned)pl.n_p2m_tiles), dim3(64), tabs, ctx.stream, 0, nl, pl.alr.p,
+                               pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs, dns, pl.toff[1], has_q, has_d, inv_alpha, 0.0,
+                               pl.invFY.p, pl.dipa.p, pl.dipb.p, pl.cnn.p, pl.serc_lv.p, 0, p, Pp, pl.M.p,
+                               pl.p2m_list.p, 0, pl.p2m_tiles.p, pl.nser_dev.p, pl.invR_lv.p, 2 * pl.nser_stride);
             check_launch(ctx, "k_p2m_quad");
         }
     }
@@ -2899,7 +3178,8 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                                leaf_base, pl.n_dleaves, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs,
                                dns, pl.toff[1], with_q, 1, inv_alpha, 1.0 / pl.lev[L].R, pl.invFY.p + L * lvl,
                                pl.dipa.p + L * lvl, pl.dipb.p + L * lvl, pl.cnn.p, pl.serc.p, pl.nser, p, Pp,
-                               pl.M.p, pl.dleaves.p, add_only);
+                               pl.M.p, pl.dleaves.p, add_only, (const int4 *)nullptr, (const int32_t *)nullptr,
+                               (const double *)nullptr, 0);
         };
         if (quad && half && keep_charge_m == 2 && pl.mq_kept && has_q) {
             // the charges' leaf multipoles of the keeping pass are still in M:
@@ -2927,7 +3207,8 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                                leaf_base, pl.nleaf, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs,
                                dns, pl.toff[1], has_q, has_d, inv_alpha, 1.0 / pl.lev[L].R,
                                pl.invFY.p + L * lvl, pl.dipa.p + L * lvl, pl.dipb.p + L * lvl, pl.cnn.p,
-                               pl.serc.p, pl.nser, p, Pp, pl.M.p, (const int32_t *)nullptr, 0);
+                               pl.serc.p, pl.nser, p, Pp, pl.M.p, (const int32_t *)nullptr, 0, (const int4 *)nullptr,
+                               (const int32_t *)nullptr, (const double *)nullptr, 0);
         } else {
             const size_t shp = ((size_t)(p + 2) * 64 + 4 * Pp) * sizeof(double) + tabs;
             hipLaunchKernelGGL(k_p2m<0>, dim3((unsigned)((pl.nleaf + 3) / 4)), dim3(64), shp, ctx.stream,
@@ -2958,8 +3239,7 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                 // expansions (before L2L passes them down)
                 StageTimer tx(ctx, YK_STAGE_M2L);
                 hipLaunchKernelGGL(k_ad_p2l, dim3((unsigned)pl.n_xbox), dim3(64),
-                                   (size_t)Pp * kP2LStride * sizeof(double), ctx.stream, pl.xbox.p, pl.xoff.p,
-                                   pl.xl.p, pl.lrange.p, has_q, has_d, pl.blevel.p, pl.bcx.p, pl.bcy.p, pl.px.p,
+                                   0, ctx.stream, pl.xbox.p, pl.xoff.p, pl.xl.p, pl.lrange.p, has_q, has_d, pl.blevel.p, pl.bcx.p, pl.bcy.p, pl.px.p,
                                    pl.py.p, qs, dns, pl.toff[1], pl.rI.p, p, Pp, inv_alpha, pl.Lc.p);
                 check_launch(ctx, "k_ad_p2l");
             }

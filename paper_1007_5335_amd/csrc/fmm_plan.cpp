@@ -213,6 +213,12 @@ int near_series_terms(double tmax) {
     return std::min(YK_NSER64, k);
 }
 
+int near_series_kind(double tmax) {
+    if (tmax > 1.0) return 0;
+    const int n = near_series_terms(tmax);
+    return n <= 5 ? 5 : n <= 6 ? 4 : n <= 8 ? 3 : n <= 10 ? 2 : 1;
+}
+
 bool build_lists(Context &ctx, FmmPlan &pl, const std::vector<uint32_t> &keys, const uint32_t *dkeys) {
     const int64_t N = pl.N;
     // ---- merged Morton codes (each set's block is sorted) ----
@@ -519,21 +525,24 @@ void build_lists_adaptive(Context &ctx, FmmPlan &pl, const std::vector<uint32_t>
         up(pl.xl, xl);
         up(pl.wleaves, wleaves);
     }
-    // ---- leaf ranges by box (P2M launches per level), leaves per level ----
+    // ---- leaf ranges by box, the leaves that have a multipole by level ----
     {
         std::vector<int32_t> alr((size_t)nb * 6, 0);
         for (int64_t li = 0; li < pl.nleaf; ++li)
             for (int j = 0; j < 6; ++j) alr[(size_t)pl.h_leaf_box[li] * 6 + j] = pl.h_lrange[(size_t)li * 6 + j];
         up(pl.alr, alr);
         std::vector<int32_t> pls;
-        pl.p2m_off.assign(L + 2, 0);
-        for (int l = 0; l <= L; ++l) {
-            pl.p2m_off[l] = (int64_t)pls.size();
-            if (l < lmin) continue;
+        std::vector<int4> tiles;
+        for (int l = lmin; l <= L; ++l) {
+            const size_t first = pls.size();
             for (int64_t b = pl.lev[l].begin; b < pl.lev[l].end; ++b)
-                if (pl.h_box_leaf[b] >= 0) pls.push_back((int32_t)(b - pl.lev[l].begin));
+                if (pl.h_box_leaf[b] >= 0) pls.push_back((int32_t)b);
+            for (size_t k = first; k < pls.size(); k += 16)
+                tiles.push_back(make_int4(l, (int)k, (int)std::min<size_t>(16, pls.size() - k), 0));
         }
-        pl.p2m_off[L + 1] = (int64_t)pls.size();
+        pl.n_p2m = (int64_t)pls.size();
+        pl.n_p2m_tiles = (int64_t)tiles.size();
+        up(pl.p2m_tiles, tiles);
         up(pl.p2m_list, pls);
     }
     // near field: t = r^2 / (4 alpha^2) of a U-list pair is at most 2 s^2 / alpha^2
@@ -1099,10 +1108,11 @@ ActiveSet &get_active(Context &ctx, FmmPlan &pl, int mask) {
         }
         if (ordered.size() == n) items.swap(ordered);   // (a range too short for its heavy items: as they were)
     }
-    // adaptive tree: the items grouped (stably) by their leaf's level and by
-    // whether a coarser leaf touches it, class 2 l + coarser, so that each
-    // class's near field runs with the series its pair distances need
-    as->item_lev_begin.assign(2 * (L + 1) + 1, 0);
+    // adaptive tree: the items grouped (stably) by the near-field series they
+    // need, the longest first, and within by their leaf's level and by whether
+    // a coarser leaf touches it: a leaf of side s meets pairs with
+    // t = r^2/(4 alpha^2) <= 2 s^2/alpha^2 among leaves of its size or finer,
+    // 4.5 s^2/alpha^2 with a coarser one (at a corner)
     if (pl.adaptive) {
         std::vector<std::vector<int2>> by(2 * (L + 1));
         for (const int2 &it : items) {
@@ -1113,11 +1123,15 @@ ActiveSet &get_active(Context &ctx, FmmPlan &pl, int mask) {
             by[2 * l + coarser].push_back(it);
         }
         items.clear();
-        for (int k = 0; k < 2 * (L + 1); ++k) {
-            as->item_lev_begin[k] = (int64_t)items.size();
-            items.insert(items.end(), by[k].begin(), by[k].end());
+        for (int k = 0; k < kLeafKinds; ++k) {
+            as->item_kind[k] = (int)items.size();
+            for (int c = 0; c < 2 * (L + 1); ++c) {
+                const double s = pl.lev[c >> 1].side / pl.alpha;
+                if (near_series_kind(((c & 1) ? 4.5 : 2.0) * s * s) == k)
+                    items.insert(items.end(), by[c].begin(), by[c].end());
+            }
         }
-        as->item_lev_begin[2 * (L + 1)] = (int64_t)items.size();
+        as->item_kind[kLeafKinds] = (int)items.size();
     }
     as->h_items = items;
     as->h_tcnt.assign(pl.nleaf, 0);

@@ -66,6 +66,20 @@ YK_HD double k1oz_of_t(double t) {
 YK_HD double k0(double z) { return k0_of_t(0.25 * z * z); }
 YK_HD double k1(double z) { return z * k1oz_of_t(0.25 * z * z); }
 
+// K0(z) and K1(z) together (one logarithm, or one exponential and square root).
+YK_HD void k01(double z, double &K0, double &K1) {
+    const double t = 0.25 * z * z;
+    if (t <= 1.0) {
+        const double lnt = log(t);
+        K0 = k0_small(t, lnt);
+        K1 = z * k1oz_small(t, lnt);
+    } else {
+        const double e = exp(-z) / sqrt(z), x = 4.0 / z - 1.0;
+        K0 = e * clenshaw(yk_cheb_K0, x);
+        K1 = e * clenshaw(yk_cheb_K1, x);
+    }
+}
+
 // ------------------------------------------------------- fast FP64 log ---
 // Natural logarithm for the near-field series (t > 0, finite).  With
 // t = m 2^e and m in [sqrt(1/2), sqrt(2)), ln t = e ln 2 + 2 atanh(s),
