@@ -3165,26 +3165,22 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                   : p == 8 ? k_p2m_quad<8, 4> : p == 12 ? k_p2m_quad<12, 4> : p == 16 ? k_p2m_quad<16, 4>
                   : p == 20 ? k_p2m_quad<20, 4> : p == 24 ? k_p2m_quad<24, 4> : p == 28 ? k_p2m_quad<28, 4>
                   : p == 31 ? k_p2m_quad<31, 4> : nullptr;
-        auto row = p == 8 ? k_p2m_quad<8, 32> : p == 12 ? k_p2m_quad<12, 32> : p == 16 ? k_p2m_quad<16, 32>
-                 : p == 20 ? k_p2m_quad<20, 32> : p == 24 ? k_p2m_quad<24, 32> : p == 28 ? k_p2m_quad<28, 32>
-                 : p == 31 ? k_p2m_quad<31, 32> : nullptr;
         auto half = p == 8 ? k_p2m_half<8> : p == 12 ? k_p2m_half<12> : p == 16 ? k_p2m_half<16>
                   : p == 20 ? k_p2m_half<20> : p == 24 ? k_p2m_half<24> : p == 28 ? k_p2m_half<28>
                   : p == 31 ? k_p2m_half<31> : nullptr;
         // the leaves that hold dipoles (few, but their points are dense along
         // the curves): 32 lanes per leaf; charges too unless add_only
-        auto dipole_leaves = [&](int with_q, int add_only, hipStream_t st) {
-            hipLaunchKernelGGL(row, dim3((unsigned)((pl.n_dleaves + 1) / 2)), dim3(64), tabs, st,
-                               leaf_base, pl.n_dleaves, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs,
-                               dns, pl.toff[1], with_q, 1, inv_alpha, 1.0 / pl.lev[L].R, pl.invFY.p + L * lvl,
-                               pl.dipa.p + L * lvl, pl.dipb.p + L * lvl, pl.cnn.p, pl.serc.p, pl.nser, p, Pp,
-                               pl.M.p, pl.dleaves.p, add_only, (const int4 *)nullptr, (const int32_t *)nullptr,
-                               (const double *)nullptr, 0);
+        auto dipole_leaves = [&](int with_q, int add_only) {
+            const P2MTables tb{nullptr, L, pl.serc.p, nullptr, nullptr, pl.invFY.p, pl.dipa.p, pl.dipb.p, pl.cnn.p,
+                               0, pl.nser, 1.0 / pl.lev[L].R};
+            hipLaunchKernelGGL(k_p2m_wave, dim3((unsigned)pl.n_dleaves), dim3(64), 0, ctx.stream, leaf_base,
+                               pl.dleaves.p, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs, dns, pl.toff[1],
+                               with_q, 1, inv_alpha, tb, p, Pp, pl.M.p, add_only);
         };
         if (quad && half && keep_charge_m == 2 && pl.mq_kept && has_q) {
             // the charges' leaf multipoles of the keeping pass are still in M:
             // the dipoles are added to them
-            if (has_d && pl.n_dleaves > 0) dipole_leaves(0, 1, ctx.stream);
+            if (has_d && pl.n_dleaves > 0) dipole_leaves(0, 1);
             pl.mq_kept = false;
         } else if (quad && half) {
             // charges in two halves of the orders on the leaves without
@@ -3201,7 +3197,7 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                                pl.nser, Pp, pl.M.p, split_d, pl.Lc.p, lc_len);
             lc_clear = true;
             if (keep_charge_m == 1 && has_q && !has_d) pl.mq_kept = true;
-            if (split_d) dipole_leaves(has_q, 0, ctx.stream);
+            if (split_d) dipole_leaves(has_q, 0);
         } else if (quad) {
             hipLaunchKernelGGL(quad, dim3((unsigned)((pl.nleaf + 15) / 16)), dim3(64), tabs, ctx.stream,
                                leaf_base, pl.nleaf, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs,

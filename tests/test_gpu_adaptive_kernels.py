@@ -32,6 +32,10 @@ CASES = [
     dict(n=12007, nodes=1000, leaf=32, alpha=0.03, p=31),
     dict(n=90017, nodes=2048, leaf=16, alpha=0.02, p=31),      # more than 8,192 leaves
     dict(n=90017, nodes=2048, leaf=16, alpha=0.003, p=8),
+    # uniform trees of more than 8,192 leaves: the leaves with dipoles by
+    # themselves, several points per lane or a few
+    dict(n=90017, nodes=9000, leaf=8, alpha=0.05, p=31, tree=0),
+    dict(n=90017, nodes=300, leaf=8, alpha=0.05, p=12, tree=0),
 ]
 
 
@@ -50,7 +54,7 @@ def test_adaptive_kernels_match_direct_sums(yk, c):
     bxy, ones = 0.5 + 0.2 * nrm, np.ones(nodes)
     d = rng.standard_normal(nodes)
     print(f"adaptive kernels: {c}", flush=True)
-    ctx = yk.yk_create(leaf_size=c["leaf"], p=p, tree=yk.YK_TREE_ADAPTIVE, direct=0)
+    ctx = yk.yk_create(leaf_size=c["leaf"], p=p, tree=c.get("tree", yk.YK_TREE_ADAPTIVE), direct=0)
     try:
         bd = yk.Boundary(bxy, nrm, ones, ones, [0, nodes])
         ov = torch.empty(n, dtype=torch.float64, device="cuda")
