@@ -31,7 +31,6 @@ struct WarmStart {
     DevBuf<float> params, adam_m, adam_v, grad;
     int64_t adam_t = 0;
     DevBuf<float> Xall, Tall, Xbat, Tbat, h1, h2, d1, d2, yb, dyb, part, cpart, lpart;
-    DevBuf<float> wt;                     // transposed hidden-layer weights for the fused inference
     DevBuf<int32_t> brows;
     DevBuf<double> scal, dtmp, fscale;
     std::vector<std::unique_ptr<Obs>> obs;
@@ -54,6 +53,8 @@ struct WarmStart {
     // (device memory; fs[6] is the density scale r_s)
     void features(const double *sm1, const double *s0, const double *gm1, const double *g0,
                   const double *gp1, float *X, double *fs);
+    double loss_grad_fused(int64_t rows, const float *X, const float *T, float *G);
+    double loss_of(int64_t rows, int nb);
     void colsum(int64_t rows, int cols, const float *D, float *out);
 };
 

@@ -384,37 +384,46 @@ __global__ void k_gather_rows(int64_t nb, int Fp, const int32_t *__restrict__ ro
     if (f == 0) Tb[r] = T[src];
 }
 
-// ------------------------------------------------------- fused inference --
-// Inference over many rows: a workgroup of four wavefronts takes kPredRows rows
-// through both hidden layers on the matrix cores and writes one output per
-// row; the first layer's activations stay in LDS.  Wavefront w owns columns
-// 64 w .. 64 w + 63 of both layers.  Weights are read transposed (WT[k][col],
-// so a fragment's sixteen columns are contiguous).
+// ----------------------------------------------------------- fused passes --
+// The network of 256 hidden units (kFp inputs) over many rows, on the matrix
+// cores in FP32: inference, or the loss and everything of its gradient that
+// goes row by row.  A workgroup of four wavefronts takes 16 RT rows through
+// all layers, its activations in LDS; wavefront w owns columns 64 w .. 64 w +
+// 63 of every product.  The matrix cores bound it (10 GFLOP for 32,768 rows),
+// next the hyperbolic tangents.
 //   v_mfma_f32_16x16x4f32: lane l holds A[l%16][l/16], B[l/16][l%16];
 //   C rows 4(l/16) + r, column l%16.
-// LDS row strides are 4 more than a multiple of 64 words, so the sixteen rows
-// and four k of a fragment read fall on distinct banks.
-constexpr int kPredRows = 32;
+// The terms of a product may come in any order: step s of a run of 16 takes k =
+// 4 (l/16) + s, so that a lane reads four consecutive k of A (LDS) and of the
+// weights (W[col][k], from cache) at once; the weights of the next run are
+// loaded while this one is multiplied.  LDS row strides are 4 mod 16 words:
+// the sixteen rows of a read fall on distinct banks.
+// RT: up to 512 workgroups, two per CU, are resident; the smallest RT with no
+// more than that has the shortest chains.  (32,768 rows: inference 80 us with
+// single words per load and 32 rows, 67 this way; the gradient's products and
+// passes by layer 260, 116.)
+typedef f4v f4u __attribute__((aligned(4)));   // (the caller's features: any float alignment)
+constexpr int kH = 256, kSh = kH + 4, kSx = kFp + 4;
 
-template <int FP, int H>
-__global__ __launch_bounds__(256) void k_mlp_predict(int64_t rows, const float *__restrict__ X,
-                                                     const float *__restrict__ W1T, const float *__restrict__ b1,
-                                                     const float *__restrict__ W2T, const float *__restrict__ b2,
-                                                     const float *__restrict__ w3, const float *__restrict__ b3,
-                                                     float *__restrict__ y) {
-    static_assert(H == 256 && FP % 4 == 0, "four wavefronts of 64 columns");
-    constexpr int SX = (FP + 59) / 64 * 64 + 4, SH = H + 4;
-    constexpr int RT = kPredRows / 16;
-    __shared__ float xs[kPredRows * SX];
-    __shared__ float hs[kPredRows * SH];
-    __shared__ float ys[4][kPredRows];
+struct MlpArgs {
+    int64_t rows;
+    const float *X, *W1, *b1, *W2, *b2, *w3, *b3;
+    float *y;                     // inference: the outputs
+    const float *T;               // gradient: the targets, and what it writes:
+    float *H1, *D2, *D1;          // first layer's activations, both layers' gradients at the sums
+    float *lp;                    // per workgroup: sum of squared errors
+    float *pw3, *pb1, *pb2, *pb3; // per workgroup: partial gradients (256 each; b3 one)
+};
+
+template <int RT, bool GRAD>
+__global__ __launch_bounds__(256, 2) void k_mlp(MlpArgs p) {
+    constexpr int R = 16 * RT;
+    static_assert(kFp % 16 == 0 && kSx <= kSh, "runs of 16; the inputs lie where the activations come to lie");
+    __shared__ float hs[R * kSh];
+    __shared__ float ys[4][R], dys[R];
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, lr = l & 15, lk = l >> 4;
-    const int64_t r0 = (int64_t)blockIdx.x * kPredRows;
-    for (int e = tid; e < kPredRows * FP; e += 256) {
-        const int r = e / FP, k = e % FP;
-        xs[r * SX + k] = r0 + r < rows ? X[(r0 + r) * FP + k] : 0.f;
-    }
-    __syncthreads();
+    const int64_t r0 = (int64_t)blockIdx.x * R;
+    const int nrow = (int)min<int64_t>(R, p.rows - r0);
     const int c0 = 64 * w;
     f4v acc[RT][4];
     auto clear = [&]() {
@@ -423,72 +432,286 @@ __global__ __launch_bounds__(256) void k_mlp_predict(int64_t rows, const float *
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
     };
-    // acc += A[rows][k] WT[k][cols] over k < K, A in LDS with row stride S
-    auto layer = [&](const float *As, int S, const float *WT, int K) {
-        for (int k0 = 0; k0 < K; k0 += 4) {
-            const int k = k0 + lk;
-            float a[RT], b[4];
+    // acc += A[rows][k] B[k][cols] over k < K, A in LDS with row stride S
+    auto layer = [&](int S, int K, auto load) {
+        f4v b[4], bn[4];
+        load(0, bn);
+        for (int k0 = 0; k0 < K; k0 += 16) {
 #pragma unroll
-            for (int i = 0; i < RT; ++i) a[i] = As[(16 * i + lr) * S + k];
+            for (int j = 0; j < 4; ++j) b[j] = bn[j];
+            if (k0 + 16 < K) load(k0 + 16, bn);
+            f4v a[RT];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = WT[(int64_t)k * H + c0 + 16 * j + lr];
+            for (int i = 0; i < RT; ++i) a[i] = *(const f4v *)&hs[(16 * i + lr) * S + k0 + 4 * lk];
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < RT; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
+        }
+    };
+    auto rows_of = [&](const float *W, int K) {   // B[k][col] = W[col][k]
+        return [=](int k0, f4v (&b)[4]) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) b[j] = *(const f4v *)&W[(c0 + 16 * j + lr) * K + k0 + 4 * lk];
+        };
+    };
+    // each of the lane's elements: its row in the workgroup, its column
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[j], acc[i][j], 0, 0, 0);
-        }
+                for (int r = 0; r < 4; ++r) f(i, j, r, 16 * i + 4 * lk + r, c0 + 16 * j + lr);
     };
-    clear();
-    layer(xs, SX, W1T, FP);
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int col = c0 + 16 * j + lr;
-            const float bb = b1[col];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) hs[(16 * i + 4 * lk + r) * SH + col] = tanhf(acc[i][j][r] + bb);
-        }
+    auto copy_out = [&](float *dst) {   // the LDS rows to dst
+        for (int e = tid; e < nrow * (kH / 4); e += 256)
+            *(f4v *)&dst[(r0 + e / (kH / 4)) * kH + 4 * (e % (kH / 4))] =
+                *(const f4v *)&hs[(e / (kH / 4)) * kSh + 4 * (e % (kH / 4))];
+    };
+    for (int e = tid; e < R * (kFp / 4); e += 256) {
+        const int r = e / (kFp / 4), k = 4 * (e % (kFp / 4));
+        *(f4v *)&hs[r * kSx + k] = r < nrow ? *(const f4u *)&p.X[(r0 + r) * kFp + k] : f4v{0.f, 0.f, 0.f, 0.f};
+    }
     __syncthreads();
     clear();
-    layer(hs, SH, W2T, H);
+    layer(kSx, kFp, rows_of(p.W1, kFp));
+    __syncthreads();
+    f4v h1[RT][4];   // (the gradient's last product has its elements in the same lanes)
+    each([&](int i, int j, int r, int row, int col) {
+        const float h = tanhf(acc[i][j][r] + p.b1[col]);
+        hs[row * kSh + col] = h;
+        if constexpr (GRAD) h1[i][j][r] = h;
+    });
+    __syncthreads();
+    if constexpr (GRAD) copy_out(p.H1);
+    clear();
+    layer(kSh, kH, rows_of(p.W2, kH));
     // this wavefront's share of sum_col tanh(z + b2[col]) w3[col], then the
     // sixteen lanes of each row group and the four wavefronts
-    float part[RT][4];
+    f4v yp[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) yp[i] = f4v{0.f, 0.f, 0.f, 0.f};
+    each([&](int i, int j, int r, int, int col) {
+        acc[i][j][r] = tanhf(acc[i][j][r] + p.b2[col]);
+        yp[i][r] += acc[i][j][r] * p.w3[col];
+    });
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            float sacc = 0.f;
+            float v = yp[i][r];
+#pragma unroll
+            for (int m = 8; m >= 1; m >>= 1) v += __shfl_xor(v, m, 16);
+            if (lr == 0) ys[w][16 * i + 4 * lk + r] = v;
+        }
+    __syncthreads();
+    const float yv = tid < nrow ? ((ys[0][tid] + ys[1][tid]) + (ys[2][tid] + ys[3][tid])) + p.b3[0] : 0.f;
+    if constexpr (!GRAD) {
+        if (tid < nrow) p.y[r0 + tid] = yv;
+    } else {
+        if (tid < 64) {
+            const float d = tid < nrow ? yv - p.T[r0 + tid] : 0.f;
+            float dy = 2.f * d / (float)p.rows, e = d * d;
+            if (tid < R) dys[tid] = dy;
+#pragma unroll
+            for (int m = 32; m >= 1; m >>= 1) {
+                e += __shfl_xor(e, m, 64);
+                dy += __shfl_xor(dy, m, 64);
+            }
+            if (tid == 0) {
+                p.lp[blockIdx.x] = e;
+                p.pb3[blockIdx.x] = dy;
+            }
+        }
+        __syncthreads();
+        // D2 = dy w3 (1 - h2^2); column sums of h2 dy and of D2
+        float sw[4] = {0.f, 0.f, 0.f, 0.f}, sb[4] = {0.f, 0.f, 0.f, 0.f};
+        each([&](int i, int j, int r, int row, int col) {
+            const float h = acc[i][j][r], dy = dys[row], d = dy * p.w3[col] * (1.f - h * h);
+            sw[j] += h * dy;
+            sb[j] += d;
+            hs[row * kSh + col] = d;
+        });
+        auto col_sums = [&](float (&v)[4], float *dst) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int col = c0 + 16 * j + lr;
-                sacc += tanhf(acc[i][j][r] + b2[col]) * w3[col];
+                v[j] += __shfl_xor(v[j], 16, 64);
+                v[j] += __shfl_xor(v[j], 32, 64);
+                if (lk == 0) dst[(int64_t)blockIdx.x * kH + c0 + 16 * j + lr] = v[j];
             }
+        };
+        col_sums(sw, p.pw3);
+        col_sums(sb, p.pb2);
+        __syncthreads();
+        copy_out(p.D2);
+        // D1 = (D2 W2) (1 - h1^2) and its column sums
+        clear();
+        layer(kSh, kH, [&](int k0, f4v (&b)[4]) {
 #pragma unroll
-            for (int m = 8; m >= 1; m >>= 1) sacc += __shfl_xor(sacc, m, 16);
-            part[i][r] = sacc;
-        }
-    if (lr == 0)
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int i = 0; i < RT; ++i)
+                for (int s = 0; s < 4; ++s) b[j][s] = p.W2[(k0 + 4 * lk + s) * kH + c0 + 16 * j + lr];
+        });
+        __syncthreads();
 #pragma unroll
-            for (int r = 0; r < 4; ++r) ys[w][16 * i + 4 * lk + r] = part[i][r];
-    __syncthreads();
-    if (tid < kPredRows && r0 + tid < rows) y[r0 + tid] = ((ys[0][tid] + ys[1][tid]) + (ys[2][tid] + ys[3][tid])) + b3[0];
+        for (int j = 0; j < 4; ++j) sb[j] = 0.f;
+        each([&](int i, int j, int r, int row, int col) {
+            const float h = h1[i][j][r], d = acc[i][j][r] * (1.f - h * h);
+            sb[j] += d;
+            hs[row * kSh + col] = d;
+        });
+        col_sums(sb, p.pb1);
+        __syncthreads();
+        copy_out(p.D1);
+    }
 }
 
-// WT[k][col] = W[col][k] for a [cols][K] block (column-major weights)
-__global__ void k_transpose_w(int cols, int K, const float *__restrict__ W, float *__restrict__ WT) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)cols * K) return;
-    const int k = (int)(e / cols), col = (int)(e % cols);
-    WT[e] = W[(int64_t)col * K + k];
+// The weights' gradients, sums over the rows: g_W2 = D2^T H1 (256 x 256, split
+// into z2 runs of rows2 rows and four quarters) and g_W1 = D1^T X (256 x kFp,
+// z1 runs of rows1), one launch, partial results per run.  A wavefront's 64
+// columns of an operand are 4 (l%16) + tile, so one load of four words per lane
+// gives all four fragments of a step, straight from memory to registers; the
+// next 16 rows are loaded while these are multiplied (rows beyond the end: the
+// last one, its first operand cleared when it is used, so that no load waits on
+// a branch).  32,768 rows: 72 us, half of it matrix-core time, the rest waiting
+// for loads; products staged through LDS, one launch per weight, took 115.
+__global__ __launch_bounds__(256, 2) void k_weight_grads(int64_t rows, const float *__restrict__ D2,
+                                                         const float *__restrict__ H1, const float *__restrict__ D1,
+                                                         const float *__restrict__ X, int z2, int rows2, int rows1,
+                                                         float *__restrict__ part2, float *__restrict__ part1) {
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    if ((int)blockIdx.x < 4 * z2) {
+        const int b = xcd_tile(blockIdx.x, 4 * z2), z = b >> 2;   // (a run's quarters on one XCD)
+        const int m0 = 128 * ((b >> 1) & 1) + 64 * (w >> 1), n0 = 128 * (b & 1) + 64 * (w & 1);
+        const int64_t kb = (int64_t)z * rows2, ke = min<int64_t>(rows, kb + rows2);
+        f4v acc[4][4], a[4], c[4], an[4], cn[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
+        auto load = [&](int64_t k0) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int64_t k = min<int64_t>(k0 + 4 * s + lk, ke - 1);
+                an[s] = *(const f4v *)&D2[k * kH + m0 + 4 * lr];
+                cn[s] = *(const f4v *)&H1[k * kH + n0 + 4 * lr];
+            }
+        };
+        load(kb);
+        for (int64_t k0 = kb; k0 < ke; k0 += 16) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                a[s] = an[s];
+                c[s] = cn[s];
+            }
+            if (k0 + 16 < ke) load(k0 + 16);
+            if (k0 + 16 > ke)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    if (k0 + 4 * s + lk >= ke) a[s] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i], c[s][j], acc[i][j], 0, 0, 0);
+        }
+        float *out = part2 + (int64_t)z * kH * kH;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                *(f4v *)&out[(m0 + 4 * (4 * lk + r) + i) * kH + n0 + 4 * lr] =
+                    f4v{acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
+    } else {
+        constexpr int NJ = kFp / 16;
+        const int z = blockIdx.x - 4 * z2, m0 = 64 * w;
+        const int64_t kb = (int64_t)z * rows1, ke = min<int64_t>(rows, kb + rows1);
+        f4v acc[4][NJ], a[4], an[4];
+        float c[4][NJ], cn[4][NJ];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) acc[i][j] = f4v{0.f, 0.f, 0.f, 0.f};
+        auto load = [&](int64_t k0) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int64_t k = min<int64_t>(k0 + 4 * s + lk, ke - 1);
+                an[s] = *(const f4v *)&D1[k * kH + m0 + 4 * lr];
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) cn[s][j] = X[k * kFp + 16 * j + lr];
+            }
+        };
+        load(kb);
+        for (int64_t k0 = kb; k0 < ke; k0 += 16) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                a[s] = an[s];
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) c[s][j] = cn[s][j];
+            }
+            if (k0 + 16 < ke) load(k0 + 16);
+            if (k0 + 16 > ke)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    if (k0 + 4 * s + lk >= ke) a[s] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s][i], c[s][j], acc[i][j], 0, 0, 0);
+        }
+        float *out = part1 + (int64_t)z * kH * kFp;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) out[(m0 + 4 * (4 * lk + r) + i) * kFp + 16 * j + lr] = acc[i][j][r];
+    }
+}
+
+// All partial gradients added up in one launch: segment s has n[s] elements in
+// nz[s] partial rows; a workgroup takes 64 elements, its sixteen wavefronts the
+// rows z = w (mod 16), whose sums are added in a fixed order.
+struct GradSums {
+    static constexpr int kSegs = 6;
+    const float *part[kSegs];
+    float *out[kSegs];
+    int n[kSegs], nz[kSegs], block[kSegs + 1];
+};
+__global__ __launch_bounds__(1024) void k_sum_grads(GradSums g) {
+    __shared__ float sh[16][64];
+    int s = 0;
+    while (s < GradSums::kSegs - 1 && (int)blockIdx.x >= g.block[s + 1]) ++s;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int n = g.n[s], nz = g.nz[s], e = 64 * ((int)blockIdx.x - g.block[s]) + lane;
+    float v = 0.f;
+    if (e < n)
+#pragma unroll 8
+        for (int z = w; z < nz; z += 16) v += g.part[s][(int64_t)z * n + e];
+    sh[w][lane] = v;
+    __syncthreads();
+    if (w == 0 && e < n) {
+        float t = 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) t += sh[k][lane];
+        g.out[s][e] = t;
+    }
 }
 
 }  // namespace
 
 // --------------------------------------------------------------- host side --
+static int mlp_row_tiles(int64_t rows) { return rows <= 16 * 512 ? 1 : rows <= 32 * 512 ? 2 : 4; }
+
 void sgemm(Context &ctx, int M, int N, int K, const float *A, int64_t sam, int64_t sak, const float *B,
            int64_t sbk, int64_t sbn, float *C, int64_t ldc, DevBuf<float> &part, const float *tanh_bias) {
     if (M <= 0 || N <= 0) return;
@@ -592,24 +815,82 @@ void WarmStart::forward(int64_t rows, const float *X, float *y) {
     check_launch(ctx, "k_rowdot");
 }
 
+// the fused passes over rows of features X (H = kH, Fp = kFp); returns the workgroups
+template <bool GRAD> static int launch_mlp(WarmStart &ws, int64_t rows, const float *X, MlpArgs &a) {
+    const float *P = ws.params.p;
+    a.rows = rows;
+    a.X = X;
+    a.W1 = P + ws.o_W1;
+    a.b1 = P + ws.o_b1;
+    a.W2 = P + ws.o_W2;
+    a.b2 = P + ws.o_b2;
+    a.w3 = P + ws.o_w3;
+    a.b3 = P + ws.o_b3;
+    const int rt = mlp_row_tiles(rows);
+    const int nb = (int)nblk(rows, 16 * rt);
+    auto kern = rt == 1 ? k_mlp<1, GRAD> : rt == 2 ? k_mlp<2, GRAD> : k_mlp<4, GRAD>;
+    hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, ws.ctx.stream, a);
+    check_launch(ws.ctx, "k_mlp");
+    return nb;
+}
+
 void WarmStart::forward_fused(int64_t rows, const float *X, float *y) {
-    if (H != 256 || Fp != kFp) {   // (other widths: the layer-by-layer products)
+    if (H != kH || Fp != kFp) {   // (other widths: the layer-by-layer products)
         forward(rows, X, y);
         return;
     }
-    const float *P = params.p;
-    float *W1T = wt.ensure((size_t)H * Fp + (size_t)H * H), *W2T = W1T + (size_t)H * Fp;
-    hipLaunchKernelGGL(k_transpose_w, dim3(nblk((int64_t)H * Fp, 256)), dim3(256), 0, ctx.stream, H, Fp, P + o_W1,
-                       W1T);
-    hipLaunchKernelGGL(k_transpose_w, dim3(nblk((int64_t)H * H, 256)), dim3(256), 0, ctx.stream, H, H, P + o_W2,
-                       W2T);
-    check_launch(ctx, "k_transpose_w");
-    hipLaunchKernelGGL((k_mlp_predict<kFp, 256>), dim3(nblk(rows, kPredRows)), dim3(256), 0, ctx.stream, rows, X,
-                       W1T, P + o_b1, W2T, P + o_b2, P + o_w3, P + o_b3, y);
-    check_launch(ctx, "k_mlp_predict");
+    MlpArgs a{};
+    a.y = y;
+    launch_mlp<false>(*this, rows, X, a);
+}
+
+double WarmStart::loss_grad_fused(int64_t rows, const float *X, const float *T, float *G) {
+    const int nb = (int)nblk(rows, 16 * mlp_row_tiles(rows));
+    MlpArgs a{};
+    a.T = T;
+    a.H1 = h1.ensure((size_t)rows * kH);
+    a.D2 = d2.ensure((size_t)rows * kH);
+    a.D1 = d1.ensure((size_t)rows * kH);
+    a.lp = lpart.ensure(nb);
+    a.pw3 = cpart.ensure((size_t)nb * (3 * kH + 1));
+    a.pb1 = a.pw3 + (size_t)nb * kH;
+    a.pb2 = a.pb1 + (size_t)nb * kH;
+    a.pb3 = a.pb2 + (size_t)nb * kH;
+    launch_mlp<true>(*this, rows, X, a);
+    // runs of rows: at most 64 and 256 of them (one wavefront of each kind per
+    // SIMD; 64 and 128, which leaves half the CUs one of the second kind, took
+    // 90 us and not 72), at least 64 rows each, in steps of 16
+    auto run = [&](int most) { return (int)std::max<int64_t>(64, ((rows + most - 1) / most + 15) / 16 * 16); };
+    const int rows2 = run(64), rows1 = run(256);
+    const int z2 = (int)nblk(rows, rows2), z1 = (int)nblk(rows, rows1);
+    float *p2 = part.ensure((size_t)z2 * kH * kH + (size_t)z1 * kH * kFp), *p1 = p2 + (size_t)z2 * kH * kH;
+    hipLaunchKernelGGL(k_weight_grads, dim3(4 * z2 + z1), dim3(256), 0, ctx.stream, rows, a.D2, a.H1, a.D1, X, z2,
+                       rows2, rows1, p2, p1);
+    check_launch(ctx, "k_weight_grads");
+    const GradSums g0{{p2, p1, a.pw3, a.pb1, a.pb2, a.pb3},
+                      {G + o_W2, G + o_W1, G + o_w3, G + o_b1, G + o_b2, G + o_b3},
+                      {kH * kH, kH * kFp, kH, kH, kH, 1},
+                      {z2, z1, nb, nb, nb, nb},
+                      {}};
+    GradSums g = g0;
+    for (int s = 0; s < GradSums::kSegs; ++s) g.block[s + 1] = g.block[s] + (int)nblk(g.n[s], 64);
+    hipLaunchKernelGGL(k_sum_grads, dim3(g.block[GradSums::kSegs]), dim3(1024), 0, ctx.stream, g);
+    check_launch(ctx, "k_sum_grads");
+    return loss_of(rows, nb);
+}
+
+// the mean of nb partial sums of squared errors
+double WarmStart::loss_of(int64_t rows, int nb) {
+    std::vector<float> hl(nb);
+    YK_HIP(hipMemcpyAsync(hl.data(), lpart.p, nb * sizeof(float), hipMemcpyDeviceToHost, ctx.stream));
+    YK_HIP(hipStreamSynchronize(ctx.stream));
+    double s = 0;
+    for (float v : hl) s += v;
+    return s / (double)rows;
 }
 
 double WarmStart::loss_grad(int64_t rows, const float *X, const float *T, float *G) {
+    if (H == kH && Fp == kFp) return loss_grad_fused(rows, X, T, G);
     float *P = params.p;
     float *y = yb.ensure(rows), *dy = dyb.ensure(rows);
     forward(rows, X, y);
@@ -634,12 +915,7 @@ double WarmStart::loss_grad(int64_t rows, const float *X, const float *T, float 
     colsum(rows, H, D1, G + o_b1);
     colsum(rows, H, D2, G + o_b2);
     colsum(rows, 1, dy, G + o_b3);
-    std::vector<float> hl(nb);
-    YK_HIP(hipMemcpyAsync(hl.data(), lp, nb * sizeof(float), hipMemcpyDeviceToHost, ctx.stream));
-    YK_HIP(hipStreamSynchronize(ctx.stream));
-    double s = 0;
-    for (float v : hl) s += v;
-    return s / (double)rows;
+    return loss_of(rows, nb);
 }
 
 void WarmStart::colsum(int64_t rows, int cols, const float *D, float *out) {
