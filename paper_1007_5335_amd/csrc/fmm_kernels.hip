@@ -702,47 +702,63 @@ __device__ __forceinline__ void p2m_apply(int64_t li, const P2MApply &a, const S
     const int s0 = a.lrange[li * 6], e0 = has_q ? a.lrange[li * 6 + 1] : s0;
     const int s1 = a.lrange[li * 6 + 2], e1 = has_d ? a.lrange[li * 6 + 3] : s1;
     const int o = lane;   // (Pp <= 64)
-    double a0 = 0.0, a1 = 0.0;
+    double acc = 0.0;
+    // this wavefront's points w, w + 4, ... of the cn staged: up to eight at a
+    // time, all their rows' loads in flight (beyond the end: the last row, times
+    // the zero that the stage is padded with)
+    auto sum_rows = [&](auto at, int cn) {
+        for (int j = w; j < cn; j += 32) {
+            if (j + 16 < cn) at(std::integral_constant<int, 8>(), j);
+            else if (j + 4 < cn) at(std::integral_constant<int, 4>(), j);
+            else at(std::integral_constant<int, 1>(), j);
+        }
+    };
     for (int c0 = s0; c0 < e0; c0 += kRowStage) {
         const int cn = min(kRowStage, e0 - c0);
         __syncthreads();
-        if ((int)threadIdx.x < cn) sx[threadIdx.x] = st.charge(c0 + threadIdx.x);
+        sx[threadIdx.x] = (int)threadIdx.x < cn ? st.charge(c0 + threadIdx.x) : 0.0;
         __syncthreads();
         if (o < Pp) {
             const double *r = a.rq + (int64_t)c0 * Pp + o;
-            for (int j = w; j < cn; j += 8) {
-                a0 = __builtin_fma(r[(int64_t)j * Pp], sx[j], a0);
-                if (j + 4 < cn) a1 = __builtin_fma(r[(int64_t)(j + 4) * Pp], sx[j + 4], a1);
-            }
+            sum_rows([&](auto N, int j) {
+                double m[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) m[u] = r[(int64_t)min(j + 4 * u, cn - 1) * Pp];
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc = __builtin_fma(m[u], sx[j + 4 * u], acc);
+            }, cn);
         }
     }
     for (int c0 = s1; c0 < e1; c0 += kRowStage) {
         const int cn = min(kRowStage, e1 - c0);
         __syncthreads();
-        if ((int)threadIdx.x < cn) {
-            const double2 d = st.dipole(c0 + threadIdx.x, off1);
-            sx[threadIdx.x] = d.x;
-            sy[threadIdx.x] = d.y;
-        }
+        double2 d = make_double2(0.0, 0.0);
+        if ((int)threadIdx.x < cn) d = st.dipole(c0 + threadIdx.x, off1);
+        sx[threadIdx.x] = d.x;
+        sy[threadIdx.x] = d.y;
         __syncthreads();
         if (o < Pp) {
             const double *r = a.rd + (int64_t)(c0 - off1) * 2 * Pp + o;
-            for (int j = w; j < cn; j += 8) {
-                const double *rj = r + (int64_t)j * 2 * Pp;
-                a0 = __builtin_fma(rj[0], sx[j], __builtin_fma(rj[Pp], sy[j], a0));
-                if (j + 4 < cn) {
-                    const double *r4 = rj + 8 * (int64_t)Pp;
-                    a1 = __builtin_fma(r4[0], sx[j + 4], __builtin_fma(r4[Pp], sy[j + 4], a1));
+            sum_rows([&](auto N, int j) {
+                double mx[N], my[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const double *rj = r + (int64_t)min(j + 4 * u, cn - 1) * 2 * Pp;
+                    mx[u] = rj[0];
+                    my[u] = rj[Pp];
                 }
-            }
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+                    acc = __builtin_fma(mx[u], sx[j + 4 * u], __builtin_fma(my[u], sy[j + 4 * u], acc));
+            }, cn);
         }
     }
-    part[w][lane] = a0 + a1;
+    part[w][lane] = acc;
     __syncthreads();
     if (w == 0 && o < Pp)
         a.M[b * Pp + o] = o < a.P ? (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]) : 0.0;
 }
-constexpr int kP2MApplyLds = 256 + 2 * kRowStage;   // doubles
+constexpr int kP2MApplyLds = 256 + 2 * kRowStage + 64;   // doubles (64: read past the last stage's end)
 __global__ __launch_bounds__(256) void k_p2m_apply(P2MApply a, Strengths st, int64_t off1, int has_q, int has_d) {
     __shared__ double lds[kP2MApplyLds];
     p2m_apply(blockIdx.x, a, st, off1, has_q, has_d, lds);
@@ -1712,45 +1728,84 @@ __global__ __launch_bounds__(64) void k_near_build(
 
 // NTB = 64, or 256 for trees with too few items to fill the GPU (the layout
 // of the values does not depend on how many lanes share a target)
-// Dipole values (pairs) of NU sources gs apart, one vector load each and all in
-// flight together, then the sums over them: acc += mx a + my b.
-template <int NU>
-__device__ __forceinline__ double dip_sum(const double *__restrict__ Mr, int64_t cs2, const double *a, const double *b,
-                                          int gs, double acc) {
-    yk_dpair m[NU];
-#pragma unroll
-    for (int u = 0; u < NU; ++u) m[u] = __builtin_nontemporal_load(reinterpret_cast<const yk_dpair *>(Mr + u * cs2));
-#pragma unroll
-    for (int u = 0; u < NU; ++u) acc = __builtin_fma(m[u].x, a[u * gs], __builtin_fma(m[u].y, b[u * gs], acc));
-    return acc;
-}
-template <int NU>
-__device__ __forceinline__ double dip_sum(const float *__restrict__ Mr, int64_t cs2, const double *a, const double *b,
-                                          int gs, double acc) {
-    yk_fpair m[NU];
-#pragma unroll
-    for (int u = 0; u < NU; ++u) m[u] = __builtin_nontemporal_load(reinterpret_cast<const yk_fpair *>(Mr + u * cs2));
-#pragma unroll
-    for (int u = 0; u < NU; ++u)
-        acc = __builtin_fma((double)m[u].x, a[u * gs], __builtin_fma((double)m[u].y, b[u * gs], acc));
-    return acc;
-}
-// Charge values of NU sources, likewise.
-template <int NU, typename VT>
-__device__ __forceinline__ double chg_sum(const VT *__restrict__ Mr, int64_t cs, const double *a, int gs, double acc) {
-    VT m[NU];
-#pragma unroll
-    for (int u = 0; u < NU; ++u) m[u] = __builtin_nontemporal_load(Mr + u * cs);
-#pragma unroll
-    for (int u = 0; u < NU; ++u) acc = __builtin_fma((double)m[u], a[u * gs], acc);
-    return acc;
-}
 // sources per lane whose values are in flight together: an item of a densely
 // sampled curve (58 targets, 130 dipoles) is one wavefront's chain of such
 // batches (200,003 points: 176 us with 8 charges or 4 dipoles and two loads per
 // dipole, 144 us with 16 and 8; the symmetric kernel, whose registers five
 // wavefronts per SIMD share, takes 8 of either: 223 us with 16, 211 with 8)
 constexpr int kNearBatch = 16;
+
+// batch(N, full, j0) over cn sources, gs at a time: sources j0, j0 + gs, ...,
+// j0 + (N-1) gs of each lane group, all in range or (the last batch) masked
+template <int NB, typename Batch>
+__device__ __forceinline__ void source_batches(int cn, int gs, Batch batch) {
+    int j0 = 0;
+    for (; j0 + NB * gs <= cn; j0 += NB * gs) batch(std::integral_constant<int, NB>(), std::true_type(), j0);
+    const int r = cn - j0;
+    if (r <= 0) return;
+    if (NB > 8 && r > 8 * gs) batch(std::integral_constant<int, NB>(), std::false_type(), j0);
+    else if (r > 4 * gs) batch(std::integral_constant<int, 8>(), std::false_type(), j0);
+    else if (r > 2 * gs) batch(std::integral_constant<int, 4>(), std::false_type(), j0);
+    else batch(std::integral_constant<int, 2>(), std::false_type(), j0);
+}
+
+// Values of an item's block.  A large tree's are read from memory once per pass
+// (streaming: 200,003 points 147 us, 160 otherwise); a small tree's stay in
+// cache between the passes of a solve (28,672 nodes, P2M and near field 26 us
+// streaming, 21 not; 1,536 nodes 18 and 13).
+template <bool kStream, typename T> __device__ __forceinline__ T near_value(const char *p) {
+    if constexpr (kStream) return __builtin_nontemporal_load(reinterpret_cast<const T *>(p));
+    else return *reinterpret_cast<const T *>(p);
+}
+// acc plus lane group sub's share (of g) of the sums of target t's values
+// against cn staged charges a (dipoles a, b): blk the values' block from the
+// first of them, c targets per source.  One 32-bit offset per load; the last
+// batch is masked, not cut into smaller ones whose round trips would add up.
+template <int NB, bool kStream, typename VT>
+__device__ __forceinline__ double chg_rows(const VT *blk, int c, int g, int t, int sub, int cn, const double *a,
+                                           double acc) {
+    c = __builtin_amdgcn_readfirstlane(c);
+    g = __builtin_amdgcn_readfirstlane(g);
+    const char *base = reinterpret_cast<const char *>(blk);
+    source_batches<NB>(cn, g, [&](auto N, auto full, int j0) {
+        VT m[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int j = j0 + u * g + sub;
+            m[u] = near_value<kStream, VT>(base + (full || j < cn ? (uint32_t)(t + j * c) : 0u) * (uint32_t)sizeof(VT));
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int j = j0 + u * g + sub;
+            acc = __builtin_fma((double)m[u], full || j < cn ? a[j] : 0.0, acc);
+        }
+    });
+    return acc;
+}
+template <int NB, bool kStream, typename VT>
+__device__ __forceinline__ double dip_rows(const VT *blk, int c, int g, int t, int sub, int cn, const double *a,
+                                           const double *b, double acc) {
+    using Pair = typename Pair2<VT>::type;
+    c = __builtin_amdgcn_readfirstlane(c);
+    g = __builtin_amdgcn_readfirstlane(g);
+    const char *base = reinterpret_cast<const char *>(blk);
+    source_batches<NB>(cn, g, [&](auto N, auto full, int j0) {
+        Pair m[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int j = j0 + u * g + sub;
+            m[u] =
+                near_value<kStream, Pair>(base + (full || j < cn ? (uint32_t)(t + j * c) : 0u) * (uint32_t)sizeof(Pair));
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int j = j0 + u * g + sub;
+            const bool on = full || j < cn;
+            acc = __builtin_fma((double)m[u].x, on ? a[j] : 0.0, __builtin_fma((double)m[u].y, on ? b[j] : 0.0, acc));
+        }
+    });
+    return acc;
+}
 
 // the pass's side of a cached near field (both layouts)
 template <typename VT>
@@ -1802,26 +1857,12 @@ __device__ __forceinline__ void near_apply(int ib, const NearFull &nf, const Nea
             }
             __syncthreads();
             if (!it.valid) continue;
-            // the values are read once per pass: eight loads in flight per lane
-            // (explicitly, the trip count is data dependent), non-temporal
-            const int gs = it.g;
-            const int64_t cs = (int64_t)it.c * gs;   // element stride of one pass
-            if (set == 0) {
-                const VT *Mb = Mq + qoff[ib] + (int64_t)c0 * it.c + it.ti + (int64_t)it.sub * it.c;
-                int j = it.sub;
-                for (; j + (kNearBatch - 1) * gs < cn; j += kNearBatch * gs, Mb += kNearBatch * cs)
-                    near_q = chg_sum<kNearBatch>(Mb, cs, s_a + j, gs, near_q);
-                for (; j + 3 * gs < cn; j += 4 * gs, Mb += 4 * cs) near_q = chg_sum<4>(Mb, cs, s_a + j, gs, near_q);
-                for (; j < cn; j += gs, Mb += cs) near_q = chg_sum<1>(Mb, cs, s_a + j, gs, near_q);
-            } else {
-                const VT *Mb = Md + 2 * (doff[ib] + (int64_t)c0 * it.c + it.ti + (int64_t)it.sub * it.c);
-                int j = it.sub;
-                for (; j + 7 * gs < cn; j += 8 * gs, Mb += 16 * cs)
-                    near_d = dip_sum<8>(Mb, 2 * cs, s_a + j, s_b + j, gs, near_d);
-                for (; j + gs < cn; j += 2 * gs, Mb += 4 * cs)
-                    near_d = dip_sum<2>(Mb, 2 * cs, s_a + j, s_b + j, gs, near_d);
-                for (; j < cn; j += gs, Mb += 2 * cs) near_d = dip_sum<1>(Mb, 2 * cs, s_a + j, s_b + j, gs, near_d);
-            }
+            if (set == 0)
+                near_q = chg_rows<kNearBatch, NTB == 64>(Mq + qoff[ib] + (int64_t)c0 * it.c, it.c, it.g, it.ti, it.sub,
+                                                         cn, s_a, near_q);
+            else
+                near_d = dip_rows<kNearBatch / 2, NTB == 64>(Md + 2 * (doff[ib] + (int64_t)c0 * it.c), it.c, it.g,
+                                                             it.ti, it.sub, cn, s_a, s_b, near_d);
         }
     }
     __syncthreads();
@@ -2142,12 +2183,7 @@ __device__ __forceinline__ void near_apply_sym(int ib, const NearSym &ns, const 
             for (int f = lane; f < cn; f += NTB) s_a[f] = np.st.charge(flat_source(c0 + f, qn, qa));
             __syncthreads();
             if (!vB) continue;
-            const VT *Mr = Mb + (int64_t)c0 * cB + tiB + (int64_t)subB * cB;
-            const int64_t cs = (int64_t)cB * gB;
-            int j = subB;
-            for (; j + 7 * gB < cn; j += 8 * gB, Mr += 8 * cs) acc = chg_sum<8>(Mr, cs, s_a + j, gB, acc);
-            for (; j + 3 * gB < cn; j += 4 * gB, Mr += 4 * cs) acc = chg_sum<4>(Mr, cs, s_a + j, gB, acc);
-            for (; j < cn; j += gB, Mr += cs) acc = chg_sum<1>(Mr, cs, s_a + j, gB, acc);
+            acc = chg_rows<8, NTB == 64>(Mb + (int64_t)c0 * cB, cB, gB, tiB, subB, cn, s_a, acc);
         }
         __syncthreads();
         s_a[lane] = vB ? acc : 0.0;
@@ -2171,14 +2207,8 @@ __device__ __forceinline__ void near_apply_sym(int ib, const NearSym &ns, const 
             }
             __syncthreads();
             if (!it.valid) continue;
-            const int gs = it.g;
-            const int64_t cs = (int64_t)c * gs;
-            const VT *Mr = Md + 2 * (doff[ib] + (int64_t)c0 * c + it.ti + (int64_t)it.sub * c);
-            int j = it.sub;
-            for (; j + 7 * gs < cn; j += 8 * gs, Mr += 16 * cs)
-                acc = dip_sum<8>(Mr, 2 * cs, s_a + j, s_b + j, gs, acc);
-            for (; j + gs < cn; j += 2 * gs, Mr += 4 * cs) acc = dip_sum<2>(Mr, 2 * cs, s_a + j, s_b + j, gs, acc);
-            for (; j < cn; j += gs, Mr += 2 * cs) acc = dip_sum<1>(Mr, 2 * cs, s_a + j, s_b + j, gs, acc);
+            acc = dip_rows<8, NTB == 64>(Md + 2 * (doff[ib] + (int64_t)c0 * c), c, it.g, it.ti, it.sub, cn, s_a, s_b,
+                                         acc);
         }
         __syncthreads();
         s_a[lane] = it.valid ? acc : 0.0;
