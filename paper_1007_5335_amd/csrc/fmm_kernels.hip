@@ -2286,9 +2286,88 @@ NearBuildSym32 pick_near_build_sym32(bool small_only) {
 
 using LeafKernel = void (*)(LeafArgs);
 
+// L2P reads its leaf's expansion once per point.  The points of a workgroup are
+// consecutive in leaf order, so the leaves they span (at most kL2PRows, points
+// of one set) are staged in LDS: all rows' loads are in flight together, and the
+// series' loop waits on no memory.  Coefficient k lies at k + 1, so that the pair
+// 2m - 1, 2m is one aligned read.
+constexpr int kL2PRows = 32, kL2PStride = 66;
+constexpr int kL2PLds = kL2PRows * kL2PStride;
+template <typename RowOf>
+__device__ __forceinline__ bool l2p_stage(double *s_rows, int64_t n, int64_t toff1, int64_t toff2,
+                                          const int32_t *__restrict__ pleaf, int Pp, int32_t &first, RowOf row_of) {
+    const int64_t t0 = (int64_t)blockIdx.x * 256, te = min(t0 + 256, n);
+    first = pleaf[t0];
+    const int rows = pleaf[te - 1] - first + 1;
+    // (the points of one set are in leaf order; two sets' are not)
+    const bool one_set = !(t0 < toff1 && toff1 < te) && !(t0 < toff2 && toff2 < te);
+    if (!one_set || rows < 1 || rows > kL2PRows || Pp > 64) return false;   // (the whole workgroup)
+    const int lane = threadIdx.x & 63;
+    if (lane < Pp)
+#pragma unroll 8
+        for (int r = threadIdx.x >> 6; r < rows; r += 4) s_rows[r * kL2PStride + 1 + lane] = row_of(first + r)[lane];
+    return true;
+}
+// What a point needs beside the series, all read before the rows are waited for
+// (one after the other, these loads were most of the time of a small tree's
+// pass).  Points beyond the end read the last one's.
+struct L2PPoint {
+    int64_t t;
+    int set;
+    int32_t leaf, dst;
+    double x, y, near, bx, diag;
+    bool on;
+    __device__ __forceinline__ L2PPoint(int64_t n, int64_t toff1, int64_t toff2, int mask, const int32_t *pleaf,
+                                        const double *px, const double *py, const double *outs, const int32_t *perm,
+                                        const double *bw, const double *bk, const double *bxv, double inv_alpha2) {
+        const int64_t t0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+        t = min(t0, n - 1);
+        set = (t >= toff1) + (t >= toff2);
+        on = t0 < n && ((mask >> set) & 1);
+        leaf = pleaf[t];
+        dst = perm[t];
+        x = px[t];
+        y = py[t];
+        near = outs[t];
+        bx = diag = 0.0;
+        if (set == 1 && bxv) {
+            bx = bxv[dst];
+            diag = dl_diag_weight(bw[dst], bk[dst], inv_alpha2);
+        }
+    }
+    // double-layer operator: x - 2 (DL + corrected diagonal)
+    __device__ __forceinline__ void store(double v, bool op, double *out0, double *out1, double *out2) const {
+        double *o = set == 0 ? out0 : set == 1 ? out1 : out2;
+        o[dst] = set == 1 && op ? bx - 2.0 * (v + diag * bx) : v;
+    }
+};
+// the series at scaled offset (wx, wy): Horner in z with G_m = F_m(y)/F_m(Y),
+// F_m downwards; at(k) is coefficient k, 2 pi times the value returned
+template <typename At>
+__device__ __forceinline__ double l2p_series(double wx, double wy, double invR, const double *sc, int nser,
+                                             const double *ify, const double *cnn, int p, At at) {
+    const double yv = 0.25 * (wx * wx + wy * wy);
+    const double zx = wx * invR, zy = wy * invR;
+    double F1, F2;
+    f_start(yv, sc, nser, F1, F2);
+    double sr = 0.0, si = 0.0;
+#pragma unroll 4
+    for (int m = p; m >= 1; --m) {
+        const double F0 = F1 + yv * F2 * cnn[m];
+        const double gm = F0 * ify[m];
+        const double cr = at(2 * m - 1) * gm, ci = at(2 * m) * gm;
+        const double nr = sr * zx - si * zy + cr;
+        si = sr * zy + si * zx + ci;
+        sr = nr;
+        F2 = F1;
+        F1 = F0;
+    }
+    const double F0 = F1 + yv * F2 * cnn[0];
+    return at(0) * F0 * ify[0] + 2.0 * (sr * zx - si * zy);
+}
+
 // L2P: one thread per target point, adding the local expansion of the
-// point's leaf (Horner in z with G_m = F_m(y)/F_m(Y), F_m downwards) to the
-// near-field sum already in outs.  The level's tables are staged in LDS.
+// point's leaf to the near-field sum already in outs.  The level's tables are staged in LDS.
 __global__ __launch_bounds__(256) void k_l2p(
     int64_t n, int64_t toff1, int64_t toff2, int mask, const int32_t *__restrict__ pleaf,
     int64_t leaf_base, const double *__restrict__ bcx, const double *__restrict__ bcy,
@@ -2300,6 +2379,7 @@ __global__ __launch_bounds__(256) void k_l2p(
     const double *__restrict__ bx, const double *__restrict__ inc, const int64_t *__restrict__ inc_base,
     const int32_t *__restrict__ inc_cnt, const int32_t *__restrict__ lrange) {
     extern __shared__ double dyn[];
+    __shared__ double s_rows[kL2PLds];
     double *t_cnn = dyn;               // [p+1]
     double *t_ify = t_cnn + p + 1;     // [p+1]
     double *t_sc = t_ify + p + 1;      // [2 nser]
@@ -2308,53 +2388,45 @@ __global__ __launch_bounds__(256) void k_l2p(
         t_ify[i] = invFY[i];
     }
     for (int i = threadIdx.x; i < 2 * nser; i += blockDim.x) t_sc[i] = sc[i];
-    __syncthreads();
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const int set = (t >= toff1) + (t >= toff2);
-    if (!((mask >> set) & 1)) return;
-    const int32_t lb = pleaf[t];
+    const L2PPoint pt(n, toff1, toff2, mask, pleaf, px, py, outs, perm, bw, bk, bx, inv_alpha * inv_alpha);
+    const int32_t lb = pt.leaf;
     const int64_t b = leaf_base + lb;
-    const double *Lb = Lc + b * Pp;
-    // the incoming slots of the symmetric near field (charge targets): their
-    // indices are read before the series, which hides the loads behind it
+    const double wx = (pt.x - bcx[b]) * inv_alpha, wy = (pt.y - bcy[b]) * inv_alpha;
+    int32_t first = 0;
+    const bool staged = l2p_stage(s_rows, n, toff1, toff2, pleaf, Pp, first,
+                                  [&](int32_t leaf) { return Lc + (leaf_base + leaf) * Pp; });
+    // the incoming slots of the symmetric near field (charge targets), of which
+    // a leaf has one per neighbour that owns their pair block: eight at once
+    constexpr int kIn = 8;
+    double in[kIn];
     int32_t n_in = 0, n0 = 0;
     int64_t in_base = 0;
-    if (set == 0 && inc) {
+    if (pt.set == 0 && inc) {
         const int32_t s0 = lrange[lb * 6];
         n0 = lrange[lb * 6 + 1] - s0;
-        in_base = inc_base[lb] + (t - s0);
+        in_base = inc_base[lb] + (pt.t - s0);
         n_in = inc_cnt[lb];
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) in[k] = n_in > k ? inc[in_base + (int64_t)k * n0] : 0.0;
     }
-    const double wx = (px[t] - bcx[b]) * inv_alpha, wy = (py[t] - bcy[b]) * inv_alpha;
-    const double yv = 0.25 * (wx * wx + wy * wy);
-    const double zx = wx * invR, zy = wy * invR;
-    double F1, F2;
-    f_start(yv, t_sc, nser, F1, F2);
-    double sr = 0.0, si = 0.0;
-#pragma unroll 4
-    for (int m = p; m >= 1; --m) {
-        const double F0 = F1 + yv * F2 * t_cnn[m];
-        const double gm = F0 * t_ify[m];
-        const double cr = Lb[2 * m - 1] * gm, ci = Lb[2 * m] * gm;
-        const double nr = sr * zx - si * zy + cr;
-        si = sr * zy + si * zx + ci;
-        sr = nr;
-        F2 = F1;
-        F1 = F0;
+    __syncthreads();
+    if (!pt.on) return;
+    double far;
+    if (staged) {
+        const double *Lb = s_rows + (lb - first) * kL2PStride + 1;
+        far = l2p_series(wx, wy, invR, t_sc, nser, t_ify, t_cnn, p, [&](int k) { return Lb[k]; });
+    } else {
+        const double *Lb = Lc + b * Pp;
+        far = l2p_series(wx, wy, invR, t_sc, nser, t_ify, t_cnn, p, [&](int k) { return Lb[k]; });
     }
-    const double F0 = F1 + yv * F2 * t_cnn[0];
     // near field + far field, written straight to the caller's array of the set
-    double v = outs[t] + (Lb[0] * F0 * t_ify[0] + 2.0 * (sr * zx - si * zy)) * kInv2Pi;
-    // symmetric near field: the charges of the neighbours that own the pair
-    // blocks with this leaf, one incoming slot per owner
-    for (int k = 0; k < n_in; ++k) v += inc[in_base + (int64_t)k * n0];
-    double *o = set == 0 ? out0 : set == 1 ? out1 : out2;
-    const int32_t i = perm[t];
-    if (set == 1 && bx)   // double-layer operator: x - 2 (DL + corrected diagonal)
-        o[i] = bx[i] - 2.0 * (v + dl_diag_weight(bw[i], bk[i], inv_alpha * inv_alpha) * bx[i]);
-    else
-        o[i] = v;
+    double v = pt.near + far * kInv2Pi;
+    if (n_in > 0) {
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) v += in[k];
+        for (int k = kIn; k < n_in; ++k) v += inc[in_base + (int64_t)k * n0];
+    }
+    pt.store(v, bx != nullptr, out0, out1, out2);
 }
 
 // ------------------------------------------------------- adaptive tree ---
@@ -2736,7 +2808,8 @@ __global__ __launch_bounds__(64) void k_p2m_wave(
 }
 
 // L2P of the adaptive tree: as k_l2p, with the leaf's level (and its tables)
-// per point; leaves coarser than lmin have no local expansion.
+// per point, all levels' tables in LDS; leaves coarser than lmin have no local
+// expansion.
 __global__ __launch_bounds__(256) void k_ad_l2p(
     int64_t n, int64_t toff1, int64_t toff2, int mask, const int32_t *__restrict__ pleaf,
     const int32_t *__restrict__ leaf_box, const int32_t *__restrict__ leaf_lev, int lmin,
@@ -2746,44 +2819,37 @@ __global__ __launch_bounds__(256) void k_ad_l2p(
     const double *__restrict__ serc_lv, const int32_t *__restrict__ nser_lv, int nser_stride, int p, int Pp,
     const double *__restrict__ outs, const int32_t *__restrict__ perm, double *__restrict__ out0,
     double *__restrict__ out1, double *__restrict__ out2, const double *__restrict__ bw,
-    const double *__restrict__ bk, const double *__restrict__ bx) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const int set = (t >= toff1) + (t >= toff2);
-    if (!((mask >> set) & 1)) return;
-    const int32_t li = pleaf[t];
+    const double *__restrict__ bk, const double *__restrict__ bx, int nlev) {
+    extern __shared__ double dyn[];
+    __shared__ double s_rows[kL2PLds];
+    double *t_ify = dyn, *t_sc = t_ify + nlev * (p + 2);   // levels lmin .. lmin + nlev - 1
+    for (int k = threadIdx.x; k < nlev * (p + 2); k += 256) t_ify[k] = invFY[(int64_t)lmin * (p + 2) + k];
+    for (int k = threadIdx.x; k < nlev * 2 * nser_stride; k += 256)
+        t_sc[k] = serc_lv[(int64_t)lmin * 2 * nser_stride + k];
+    const L2PPoint pt(n, toff1, toff2, mask, pleaf, px, py, outs, perm, bw, bk, bx, inv_alpha * inv_alpha);
+    const int32_t li = pt.leaf;
     const int l = leaf_lev[li];
-    double v = outs[t];
+    const int64_t b = leaf_box[li];
+    const double wx = (pt.x - bcx[b]) * inv_alpha, wy = (pt.y - bcy[b]) * inv_alpha;
+    int32_t first = 0;
+    const bool staged = nlev > 0 && l2p_stage(s_rows, n, toff1, toff2, pleaf, Pp, first,
+                                              [&](int32_t leaf) { return Lc + (int64_t)leaf_box[leaf] * Pp; });
+    __syncthreads();
+    if (!pt.on) return;
+    double v = pt.near;
     if (l >= lmin) {
-        const int64_t b = leaf_box[li];
-        const double *Lb = Lc + b * Pp;
-        const double *ify = invFY + (int64_t)l * (p + 2);
-        const double invR = invR_lv[l];
-        const double wx = (px[t] - bcx[b]) * inv_alpha, wy = (py[t] - bcy[b]) * inv_alpha;
-        const double yv = 0.25 * (wx * wx + wy * wy);
-        const double zx = wx * invR, zy = wy * invR;
-        double F1, F2;
-        f_start(yv, serc_lv + (int64_t)l * 2 * nser_stride, nser_lv[l], F1, F2);
-        double sr = 0.0, si = 0.0;
-        for (int m = p; m >= 1; --m) {
-            const double F0 = F1 + yv * F2 * cnn[m];
-            const double gm = F0 * ify[m];
-            const double cr = Lb[2 * m - 1] * gm, ci = Lb[2 * m] * gm;
-            const double nr = sr * zx - si * zy + cr;
-            si = sr * zy + si * zx + ci;
-            sr = nr;
-            F2 = F1;
-            F1 = F0;
+        const double *ify = t_ify + (l - lmin) * (p + 2), *sc = t_sc + (l - lmin) * 2 * nser_stride;
+        double far;
+        if (staged) {
+            const double *Lb = s_rows + (li - first) * kL2PStride + 1;
+            far = l2p_series(wx, wy, invR_lv[l], sc, nser_lv[l], ify, cnn, p, [&](int k) { return Lb[k]; });
+        } else {
+            const double *Lb = Lc + b * Pp;
+            far = l2p_series(wx, wy, invR_lv[l], sc, nser_lv[l], ify, cnn, p, [&](int k) { return Lb[k]; });
         }
-        const double F0 = F1 + yv * F2 * cnn[0];
-        v += (Lb[0] * F0 * ify[0] + 2.0 * (sr * zx - si * zy)) * kInv2Pi;
+        v += far * kInv2Pi;
     }
-    double *o = set == 0 ? out0 : set == 1 ? out1 : out2;
-    const int32_t i = perm[t];
-    if (set == 1 && bx)   // double-layer operator: x - 2 (DL + corrected diagonal)
-        o[i] = bx[i] - 2.0 * (v + dl_diag_weight(bw[i], bk[i], inv_alpha * inv_alpha) * bx[i]);
-    else
-        o[i] = v;
+    pt.store(v, bx != nullptr, out0, out1, out2);
 }
 
 LeafKernel pick_leaf_kernel(int nt, bool small_only, bool f32) {
@@ -2890,6 +2956,18 @@ void fmm_l2l(Context &ctx, FmmPlan &pl, ActiveSet &as) {
     for (const ShiftGroup &gr : as.l2l_groups) launch_l2l_group(ctx, pl, as, gr);
 }
 
+static void launch_ad_l2p(Context &ctx, FmmPlan &pl, int mask, const double *outs, double *const out[3],
+                          const BieFuse *bie) {
+    const int nlev = std::max(0, pl.L - pl.lmin + 1);
+    const size_t tabs = (size_t)nlev * (pl.p + 2 + 2 * pl.nser_stride) * sizeof(double);
+    hipLaunchKernelGGL(k_ad_l2p, dim3(nblk(pl.N, 256)), dim3(256), tabs, ctx.stream, pl.N, pl.toff[1], pl.toff[2], mask,
+                       pl.pleaf.p, pl.leaf_box.p, pl.leaf_lev.p, pl.lmin, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p,
+                       pl.Lc.p, 1.0 / pl.alpha, pl.invR_lv.p, pl.invFY.p, pl.cnn.p, pl.serc_lv.p, pl.nser_dev.p,
+                       pl.nser_stride, pl.p, pl.Pp, outs, pl.perm.p, out[0], out[1], out[2], bie ? bie->w : nullptr,
+                       bie ? bie->kappa : nullptr, (bie && bie->kappa) ? bie->sigma : nullptr, nlev);
+    check_launch(ctx, "k_ad_l2p");
+}
+
 void fmm_adaptive_finish(Context &ctx, FmmPlan &pl, int mask, double *outs, double *const out[3]) {
     const int p = pl.p, Pp = pl.Pp;
     const double inv_alpha = 1.0 / pl.alpha;
@@ -2900,12 +2978,7 @@ void fmm_adaptive_finish(Context &ctx, FmmPlan &pl, int mask, double *outs, doub
                            pl.rI.p, p, Pp, inv_alpha, outs);
         check_launch(ctx, "k_ad_m2p");
     }
-    hipLaunchKernelGGL(k_ad_l2p, dim3(nblk(pl.N, 256)), dim3(256), 0, ctx.stream, pl.N, pl.toff[1], pl.toff[2], mask,
-                       pl.pleaf.p, pl.leaf_box.p, pl.leaf_lev.p, pl.lmin, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p,
-                       pl.Lc.p, inv_alpha, pl.invR_lv.p, pl.invFY.p, pl.cnn.p, pl.serc_lv.p, pl.nser_dev.p,
-                       pl.nser_stride, p, Pp, outs, pl.perm.p, out[0], out[1], out[2], (const double *)nullptr,
-                       (const double *)nullptr, (const double *)nullptr);
-    check_launch(ctx, "k_ad_l2p");
+    launch_ad_l2p(ctx, pl, mask, outs, out, nullptr);
 }
 
 void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, double *const out[3],
@@ -3283,13 +3356,7 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                                pl.py.p, pl.M.p, pl.rI.p, p, Pp, inv_alpha, outs);
             check_launch(ctx, "k_ad_m2p");
         }
-        hipLaunchKernelGGL(k_ad_l2p, dim3(nblk(pl.N, 256)), dim3(256), 0, ctx.stream, pl.N, pl.toff[1], pl.toff[2],
-                           mask, pl.pleaf.p, pl.leaf_box.p, pl.leaf_lev.p, pl.lmin, pl.bcx.p, pl.bcy.p, pl.px.p,
-                           pl.py.p, pl.Lc.p, inv_alpha, pl.invR_lv.p, pl.invFY.p, pl.cnn.p, pl.serc_lv.p,
-                           pl.nser_dev.p, pl.nser_stride, p, Pp, outs, pl.perm.p, out[0], out[1], out[2],
-                           bie ? bie->w : nullptr, bie ? bie->kappa : nullptr,
-                           (bie && bie->kappa) ? bie->sigma : nullptr);
-        check_launch(ctx, "k_ad_l2p");
+        launch_ad_l2p(ctx, pl, mask, outs, out, bie);
         return;   // L2P wrote the outputs
     }
     if (far && as.n_leaves > 0) {
