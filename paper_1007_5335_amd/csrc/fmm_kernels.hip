@@ -79,235 +79,46 @@ __device__ __forceinline__ void f_start(double y, const double *__restrict__ sc,
 }
 
 // ------------------------------------------------------------------- P2M ---
-// One wavefront serves four leaves, 16 lanes (one DPP row) each; lanes over
-// source points.  Each lane builds G_n = F_n(y)/F_n(Y) for n = 0..p+1 in its
-// own LDS column (downwards), then the terms of every order are summed over
-// the row with DPP (no LDS round trip); the lane whose index matches the
-// output's position mod 16 stores the batch sum, and the batch sums are then
-// accumulated in registers, output o = lane + 16 k.  The level's tables
-// (F-series coefficients, recurrence factors, normalisations, dipole weights)
-// are staged in LDS so the order loops read no scalar memory.
 template <int CTRL>
 __device__ __forceinline__ double dpp_d(double v) {
     const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
     return __hiloint2double(hi, lo);
 }
-// sum over the 16 lanes of a row, in every lane of the row
-__device__ __forceinline__ double row16_sum(double v) {
-    v += dpp_d<0xB1>(v);    // quad_perm [1,0,3,2]
-    v += dpp_d<0x4E>(v);    // quad_perm [2,3,0,1]
-    v += dpp_d<0x124>(v);   // row_ror:4
-    v += dpp_d<0x128>(v);   // row_ror:8
-    return v;
-}
-
-constexpr int kP2MSlots = 8;   // outputs per lane: Pp <= 128
-
-// NMAX > 0: orders known to be at most NMAX - 1 (Pp <= 2 NMAX), so G_n lives
-// in registers and the order loops unroll; NMAX = 0: G_n in LDS, any order.
-template <int NMAX>
-__global__ __launch_bounds__(64) void k_p2m(
-    int64_t leaf_base, int64_t nleaf, const int32_t *__restrict__ lrange,
-    const double *__restrict__ bcx, const double *__restrict__ bcy, const double *__restrict__ px,
-    const double *__restrict__ py, const double *__restrict__ qs, const double *__restrict__ dns,
-    int64_t off1, int has_q, int has_d, double inv_alpha, double invR,
-    const double *__restrict__ invFY, const double *__restrict__ da, const double *__restrict__ db,
-    const double *__restrict__ cnn, const double *__restrict__ sc, int nser, int p, int Pp,
-    double *__restrict__ M) {
-    constexpr bool kReg = NMAX > 0;
-    extern __shared__ double smem[];
-    double *G = smem;                                  // [(p+2)][64] (LDS form only)
-    double *s_out = G + (kReg ? 0 : (p + 2) * 64);     // [4][Pp] row sums of one batch
-    double *t_sc = s_out + 4 * Pp;                     // [2 nser] F_{p+1}, F_{p+2} series
-    double *t_cnn = t_sc + 2 * nser;                   // [p+2]
-    double *t_ify = t_cnn + (p + 2);                   // [p+2]
-    double *t_da = t_ify + (p + 2);                    // [p+1]
-    double *t_db = t_da + (p + 1);                     // [p+1]
-    const int lane = threadIdx.x, grp = lane >> 4, gl = lane & 15;
-    const int64_t li = (int64_t)blockIdx.x * 4 + grp;
-    const bool leaf_ok = li < nleaf;
-    const int64_t b = leaf_base + (leaf_ok ? li : 0);
-    const int P = 2 * p + 1, nk = Pp >> 4;
-    for (int k = lane; k < 2 * nser; k += 64) t_sc[k] = sc[k];
-    for (int k = lane; k < p + 2; k += 64) {
-        t_cnn[k] = cnn[k];
-        t_ify[k] = invFY[k];
-    }
-    if (has_d)
-        for (int k = lane; k < p + 1; k += 64) {
-            t_da[k] = da[k];
-            t_db[k] = db[k];
-        }
-    double *So = s_out + grp * Pp;
-    double macc[kP2MSlots];
-#pragma unroll
-    for (int k = 0; k < kP2MSlots; ++k) macc[k] = 0.0;
-    double Gr[kReg ? NMAX + 2 : 1];
-    __syncthreads();
-    const double cx = bcx[b], cy = bcy[b];
-    // G_n of this lane's point, register or LDS form
-    auto gget = [&](int n) -> double {
-        if constexpr (kReg) return Gr[n];
-        else return G[n * 64 + lane];
-    };
-    for (int set = 0; set < 2; ++set) {
-        if ((set == 0 && !has_q) || (set == 1 && !has_d)) continue;
-        const int s0 = leaf_ok ? lrange[li * 6 + 2 * set] : 0;
-        const int e0 = leaf_ok ? lrange[li * 6 + 2 * set + 1] : 0;
-        // uniform trip count over the four groups
-        int nmax = e0 - s0;
-        nmax = max(nmax, __shfl_xor(nmax, 16, 64));
-        nmax = max(nmax, __shfl_xor(nmax, 32, 64));
-        for (int base = 0; base < nmax; base += 16) {
-            const int j = s0 + base + gl;
-            const bool valid = j < e0;
-            const int jc = valid ? j : (e0 > s0 ? s0 : (set == 0 ? 0 : (int)off1));   // weight 0 below
-            const double wx = valid ? (px[jc] - cx) * inv_alpha : 0.0;
-            const double wy = valid ? (py[jc] - cy) * inv_alpha : 0.0;
-            const double y = 0.25 * (wx * wx + wy * wy);
-            const double zx = wx * invR, zy = -wy * invR;   // conj(w)/R
-            double F1, F2;
-            f_start(y, t_sc, nser, F1, F2);
-            if constexpr (kReg) {
-#pragma unroll
-                for (int n = NMAX + 1; n >= 0; --n) {
-                    if (n > p + 1) continue;
-                    if (n == p + 1) {
-                        Gr[n] = F1 * t_ify[n];
-                    } else {
-                        const double F0 = F1 + y * F2 * t_cnn[n];
-                        Gr[n] = F0 * t_ify[n];
-                        F2 = F1;
-                        F1 = F0;
-                    }
-                }
-            } else {
-                G[(p + 1) * 64 + lane] = F1 * t_ify[p + 1];
-                for (int n = p; n >= 0; --n) {
-                    const double F0 = F1 + y * F2 * t_cnn[n];
-                    G[n * 64 + lane] = F0 * t_ify[n];
-                    F2 = F1;
-                    F1 = F0;
-                }
-            }
-            // the row sum of order n goes to output 2n-1 (real) and 2n (imaginary)
-            auto emit = [&](int n, double tr, double ti) {
-                tr = row16_sum(tr);
-                ti = row16_sum(ti);
-                const int orr = n == 0 ? 0 : 2 * n - 1;
-                if (gl == (orr & 15)) So[orr] = tr;
-                if (n > 0 && gl == ((2 * n) & 15)) So[2 * n] = ti;
-            };
-            if (set == 0) {
-                const double q = valid ? qs[jc] : 0.0;
-                double pr = 1.0, pi = 0.0;     // conj(z)^n
-                auto body = [&](int n) {
-                    const double g = q * gget(n);
-                    emit(n, g * pr, g * pi);
-                    const double nr = pr * zx - pi * zy;
-                    pi = pr * zy + pi * zx;
-                    pr = nr;
-                };
-                if constexpr (kReg) {
-#pragma unroll
-                    for (int n = 0; n < NMAX; ++n)
-                        if (n <= p) body(n);
-                } else {
-                    for (int n = 0; n <= p; ++n) body(n);
-                }
-            } else {
-                const double Dx = valid ? dns[2 * (jc - off1)] : 0.0;
-                const double Dy = valid ? dns[2 * (jc - off1) + 1] : 0.0;
-                const double h = 0.5 * inv_alpha;
-                // window Psi_{n-1}, Psi_n, Psi_{n+1};  Psi_k = G_k conj(z)^k
-                double pr = zx, pi = zy;                       // conj(z)^1
-                const double g1 = gget(1);
-                double c_r = gget(0), c_i = 0.0;               // Psi_0
-                double n_r = g1 * pr, n_i = g1 * pi;           // Psi_1
-                double m_r = n_r, m_i = -n_i;                  // Psi_{-1} = conj(Psi_1)
-                auto body = [&](int n) {
-                    // term_n = h [a_n D Psi_{n+1} + b_n conj(D) Psi_{n-1}]
-                    const double an = t_da[n], bn = t_db[n];
-                    const double t1r = Dx * n_r - Dy * n_i, t1i = Dx * n_i + Dy * n_r;
-                    const double t2r = Dx * m_r + Dy * m_i, t2i = Dx * m_i - Dy * m_r;
-                    emit(n, h * (an * t1r + bn * t2r), h * (an * t1i + bn * t2i));
-                    m_r = c_r; m_i = c_i;
-                    c_r = n_r; c_i = n_i;
-                    const double nr = pr * zx - pi * zy;
-                    pi = pr * zy + pi * zx;
-                    pr = nr;
-                    if (n + 2 <= p + 1) {
-                        const double g = gget(n + 2);
-                        n_r = g * pr; n_i = g * pi;
-                    } else {
-                        n_r = 0.0; n_i = 0.0;
-                    }
-                };
-                if constexpr (kReg) {
-#pragma unroll
-                    for (int n = 0; n < NMAX; ++n)
-                        if (n <= p) body(n);
-                } else {
-                    for (int n = 0; n <= p; ++n) body(n);
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < kP2MSlots; ++k)
-                if (k < nk && gl + 16 * k < P) macc[k] += So[gl + 16 * k];
-            __syncthreads();
-        }
-    }
-    if (leaf_ok)
-#pragma unroll
-        for (int k = 0; k < kP2MSlots; ++k)
-            if (k < nk) M[b * Pp + gl + 16 * k] = gl + 16 * k < P ? macc[k] : 0.0;
-}
-
-// P2M with LPL lanes per leaf (4: a DPP quad; 32: half a wavefront) for a compile-time
-// order PO: each lane takes every LPL-th point of its leaf and accumulates all
-// 2p+1 outputs in registers; the lanes' partial sums are combined at the end
-// (DPP steps for a quad, shuffles otherwise).  Per point: F_n downwards
+// P2M of the adaptive tree with four lanes (a DPP quad) per leaf for a
+// compile-time order PO: each lane takes every fourth point of its leaf and
+// accumulates all 2p+1 outputs in registers; the lanes' partial sums are combined
+// at the end.  tiles: {level, first entry of leaf_list, entries} per workgroup,
+// each with its level's tables.  Per point: F_n downwards
 // (G_n = F_n(y)/F_n(Y) in registers), then the terms with the powers of
 // conj(z) upwards.
-template <int PO, int LPL>
+template <int PO>
 __global__ __launch_bounds__(64) void k_p2m_quad(
-    int64_t leaf_base, int64_t nleaf, const int32_t *__restrict__ lrange,
+    const int32_t *__restrict__ lrange,
     const double *__restrict__ bcx, const double *__restrict__ bcy, const double *__restrict__ px,
     const double *__restrict__ py, const double *__restrict__ qs, const double *__restrict__ dns,
-    int64_t off1, int has_q, int has_d, double inv_alpha, double invR,
+    int64_t off1, int has_q, int has_d, double inv_alpha,
     const double *__restrict__ invFY, const double *__restrict__ da, const double *__restrict__ db,
-    const double *__restrict__ cnn, const double *__restrict__ sc, int nser, int /*p*/, int Pp,
-    double *__restrict__ M, const int32_t *__restrict__ leaf_list, int accumulate,
+    const double *__restrict__ cnn, const double *__restrict__ sc, int Pp, double *__restrict__ M, const int32_t *__restrict__ leaf_list,
     const int4 *__restrict__ tiles, const int32_t *__restrict__ nser_lv, const double *__restrict__ invR_lv,
     int sc_stride) {
     constexpr int p = PO, P = 2 * PO + 1;
     extern __shared__ double smem[];
-    int64_t first = (int64_t)blockIdx.x * (64 / LPL);
-    if (tiles) {   // adaptive tree: {level, first leaf, leaves} per workgroup, tables by level
-        const int4 t = tiles[blockIdx.x];
-        first = 0;
-        leaf_list += t.y;
-        nleaf = t.z;
-        nser = nser_lv[t.x];
-        invR = invR_lv[t.x];
-        sc += (int64_t)t.x * sc_stride;
-        invFY += (int64_t)t.x * (p + 2);
-        da += (int64_t)t.x * (p + 2);
-        db += (int64_t)t.x * (p + 2);
-    }
+    const int4 t = tiles[blockIdx.x];
+    const int nser = nser_lv[t.x];
+    const double invR = invR_lv[t.x];
+    sc += (int64_t)t.x * sc_stride;
+    invFY += (int64_t)t.x * (p + 2);
+    da += (int64_t)t.x * (p + 2);
+    db += (int64_t)t.x * (p + 2);
     double *t_sc = smem;                   // [2 nser] F_{p+1}, F_{p+2} series
     double *t_cnn = t_sc + 2 * nser;       // [p+2]
     double *t_ify = t_cnn + (p + 2);       // [p+2]
     double *t_da = t_ify + (p + 2);        // [p+1]
     double *t_db = t_da + (p + 1);         // [p+1]
-    const int lane = threadIdx.x, q4 = lane % LPL;
-    // leaf_list (optional): the leaves to serve, nleaf of them
-    const int64_t lidx = first + lane / LPL;
-    const bool leaf_ok = lidx < nleaf;
-    const int64_t li = leaf_ok ? (leaf_list ? (int64_t)leaf_list[lidx] : lidx) : 0;
-    const int64_t b = leaf_base + li;
+    const int lane = threadIdx.x, q4 = lane & 3;
+    const bool leaf_ok = (lane >> 2) < t.z;
+    const int64_t b = leaf_ok ? leaf_list[t.y + (lane >> 2)] : 0;
     for (int k = lane; k < 2 * nser; k += 64) t_sc[k] = sc[k];
     for (int k = lane; k < p + 2; k += 64) {
         t_cnn[k] = cnn[k];
@@ -326,21 +137,21 @@ __global__ __launch_bounds__(64) void k_p2m_quad(
     const double cx = bcx[b], cy = bcy[b];
     for (int set = 0; set < 2; ++set) {
         if ((set == 0 && !has_q) || (set == 1 && !has_d)) continue;
-        const int s0 = leaf_ok ? lrange[li * 6 + 2 * set] : 0;
-        const int e0 = leaf_ok ? lrange[li * 6 + 2 * set + 1] : 0;
+        const int s0 = leaf_ok ? lrange[b * 6 + 2 * set] : 0;
+        const int e0 = leaf_ok ? lrange[b * 6 + 2 * set + 1] : 0;
         // a lane without a point reads a point of its own set (weight 0
         // below): the leaf's first, else the set's first (index 0 or off1)
         auto clamp_j = [&](int j) { return j < e0 ? j : (e0 > s0 ? s0 : (set == 0 ? 0 : (int)off1)); };
         // the next point's coordinates are loaded one iteration ahead
         int jn = clamp_j(s0 + q4);
         double nx = px[jn], ny = py[jn];
-        for (int j0 = s0;; j0 += LPL) {
+        for (int j0 = s0;; j0 += 4) {
             const int j = j0 + q4;
             const bool valid = j < e0;
             if (!__any(valid)) break;
             const int jc = jn;
             const double cxp = nx, cyp = ny;
-            jn = clamp_j(j + LPL);
+            jn = clamp_j(j + 4);
             nx = px[jn];
             ny = py[jn];
             const double wx = (cxp - cx) * inv_alpha, wy = (cyp - cy) * inv_alpha;
@@ -407,21 +218,16 @@ __global__ __launch_bounds__(64) void k_p2m_quad(
             }
         }
     }
-    // sums over the leaf's lanes; lane q4 writes outputs q4, q4 + LPL, ...
+    // sums over the leaf's lanes; lane q4 writes outputs q4, q4 + 4, ...
 #pragma unroll
     for (int o = 0; o < P; ++o) {
         double v = acc[o];
-        if constexpr (LPL == 4) {
-            v += dpp_d<0xB1>(v);    // quad_perm [1,0,3,2]
-            v += dpp_d<0x4E>(v);    // quad_perm [2,3,0,1]
-        } else {
-#pragma unroll
-            for (int m = LPL / 2; m >= 1; m >>= 1) v += __shfl_xor(v, m, LPL);
-        }
-        if (leaf_ok && o % LPL == q4) M[b * Pp + o] = accumulate ? M[b * Pp + o] + v : v;
+        v += dpp_d<0xB1>(v);    // quad_perm [1,0,3,2]
+        v += dpp_d<0x4E>(v);    // quad_perm [2,3,0,1]
+        if (leaf_ok && o % 4 == q4) M[b * Pp + o] = v;
     }
-    if (leaf_ok && !accumulate)
-        for (int o = P + q4; o < Pp; o += LPL) M[b * Pp + o] = 0.0;
+    if (leaf_ok)
+        for (int o = P + q4; o < Pp; o += 4) M[b * Pp + o] = 0.0;
 }
 
 // Charges-only P2M in two halves of the orders: blockIdx.y = 0 takes orders
@@ -2667,8 +2473,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     sums.store(p, [&](int o, double v) { Lc[(int64_t)d * Pp + o] += v; });
 }
 
-// P2M, one wavefront per leaf (entry of leaf_list: leaf_base plus it is the
-// box), a lane per point: for few leaves, where k_p2m_quad's chains of points
+// P2M, one wavefront per leaf (entry of leaf_list, or every leaf: leaf_base plus
+// it is the box), a lane per point: for few leaves, where k_p2m_quad's chains of points
 // per lane leave the GPU idle and its unrolled code is fetched for a few
 // wavefronts only.  Per chunk of eight orders, the highest first: F_n further
 // down, then the terms with the powers of conj(z) from the chunk's first order
@@ -2694,7 +2500,7 @@ __global__ __launch_bounds__(64) void k_p2m_wave(
     int has_q, int has_d, double inv_alpha, P2MTables tb, int p, int Pp, double *__restrict__ M, int accumulate) {
     __shared__ double sh[kSumLds];
     const int lane = threadIdx.x;
-    const int64_t li = leaf_list[blockIdx.x], b = leaf_base + li;
+    const int64_t li = leaf_list ? leaf_list[blockIdx.x] : (int64_t)blockIdx.x, b = leaf_base + li;
     const int l = tb.blevel ? tb.blevel[b] : tb.lev;
     const double *ify = tb.invFY + (int64_t)l * (p + 2), *cnn = tb.cnn;
     const double *da = tb.da + (int64_t)l * (p + 2), *db = tb.db + (int64_t)l * (p + 2);
@@ -3200,9 +3006,9 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
         StageTimer tm(ctx, YK_STAGE_P2M);
         pl.mq_kept = false;
         const int64_t nl = pl.n_p2m;
-        auto quad4 = p == 8 ? k_p2m_quad<8, 4> : p == 12 ? k_p2m_quad<12, 4> : p == 16 ? k_p2m_quad<16, 4>
-                   : p == 20 ? k_p2m_quad<20, 4> : p == 24 ? k_p2m_quad<24, 4> : p == 28 ? k_p2m_quad<28, 4>
-                   : p == 31 ? k_p2m_quad<31, 4> : nullptr;
+        auto quad4 = p == 8 ? k_p2m_quad<8> : p == 12 ? k_p2m_quad<12> : p == 16 ? k_p2m_quad<16>
+                   : p == 20 ? k_p2m_quad<20> : p == 24 ? k_p2m_quad<24> : p == 28 ? k_p2m_quad<28>
+                   : p == 31 ? k_p2m_quad<31> : nullptr;
         YK_REQUIRE(quad4 != nullptr, "no P2M kernel for this order");
         if (nl > 0 && nl < kP2MWaveLeaves) {
             const P2MTables tb{pl.blevel.p, 0, pl.serc_lv.p, pl.nser_dev.p, pl.invR_lv.p, pl.invFY.p, pl.dipa.p,
@@ -3213,10 +3019,10 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
             check_launch(ctx, "k_p2m_wave");
         } else if (nl > 0) {
             const size_t tabs = (2 * (size_t)pl.nser_stride + 4 * (size_t)(p + 2)) * sizeof(double);
-            hipLaunchKernelGGL(quad4, dim3((unsigned)pl.n_p2m_tiles), dim3(64), tabs, ctx.stream, 0, nl, pl.alr.p,
-                               pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs, dns, pl.toff[1], has_q, has_d, inv_alpha, 0.0,
-                               pl.invFY.p, pl.dipa.p, pl.dipb.p, pl.cnn.p, pl.serc_lv.p, 0, p, Pp, pl.M.p,
-                               pl.p2m_list.p, 0, pl.p2m_tiles.p, pl.nser_dev.p, pl.invR_lv.p, 2 * pl.nser_stride);
+            hipLaunchKernelGGL(quad4, dim3((unsigned)pl.n_p2m_tiles), dim3(64), tabs, ctx.stream, pl.alr.p, pl.bcx.p,
+                               pl.bcy.p, pl.px.p, pl.py.p, qs, dns, pl.toff[1], has_q, has_d, inv_alpha, pl.invFY.p,
+                               pl.dipa.p, pl.dipb.p, pl.cnn.p, pl.serc_lv.p, Pp, pl.M.p, pl.p2m_list.p,
+                               pl.p2m_tiles.p, pl.nser_dev.p, pl.invR_lv.p, 2 * pl.nser_stride);
             check_launch(ctx, "k_p2m_quad");
         }
     }
@@ -3261,31 +3067,27 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
             check_launch(ctx, "k_p2m_apply");
             lc_clear = true;
         } else {
-        const size_t tabs = (2 * (size_t)pl.nser + 4 * (size_t)(p + 2)) * sizeof(double);
-        // four lanes per leaf for many leaves; sixteen (more parallelism per
-        // leaf, shorter chains) when the leaves are too few to fill the GPU
-        auto quad = pl.nleaf < 8192 ? nullptr
-                  : p == 8 ? k_p2m_quad<8, 4> : p == 12 ? k_p2m_quad<12, 4> : p == 16 ? k_p2m_quad<16, 4>
-                  : p == 20 ? k_p2m_quad<20, 4> : p == 24 ? k_p2m_quad<24, 4> : p == 28 ? k_p2m_quad<28, 4>
-                  : p == 31 ? k_p2m_quad<31, 4> : nullptr;
         auto half = p == 8 ? k_p2m_half<8> : p == 12 ? k_p2m_half<12> : p == 16 ? k_p2m_half<16>
                   : p == 20 ? k_p2m_half<20> : p == 24 ? k_p2m_half<24> : p == 28 ? k_p2m_half<28>
                   : p == 31 ? k_p2m_half<31> : nullptr;
-        // the leaves that hold dipoles (few, but their points are dense along
-        // the curves): 32 lanes per leaf; charges too unless add_only
-        auto dipole_leaves = [&](int with_q, int add_only) {
+        YK_REQUIRE(half != nullptr, "no P2M kernel for this order");
+        // a wavefront per leaf: all leaves when they are few, else (list) those
+        // that hold dipoles, whose points are dense along the curves; charges
+        // too unless add_only
+        const bool many = pl.nleaf >= 8192;
+        auto by_wave = [&](const int32_t *list, int64_t nl, int with_q, int with_d, int add_only) {
             const P2MTables tb{nullptr, L, pl.serc.p, nullptr, nullptr, pl.invFY.p, pl.dipa.p, pl.dipb.p, pl.cnn.p,
                                0, pl.nser, 1.0 / pl.lev[L].R};
-            hipLaunchKernelGGL(k_p2m_wave, dim3((unsigned)pl.n_dleaves), dim3(64), 0, ctx.stream, leaf_base,
-                               pl.dleaves.p, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs, dns, pl.toff[1],
-                               with_q, 1, inv_alpha, tb, p, Pp, pl.M.p, add_only);
+            hipLaunchKernelGGL(k_p2m_wave, dim3((unsigned)nl), dim3(64), 0, ctx.stream, leaf_base,
+                               list, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs, dns, pl.toff[1],
+                               with_q, with_d, inv_alpha, tb, p, Pp, pl.M.p, add_only);
         };
-        if (quad && half && keep_charge_m == 2 && pl.mq_kept && has_q) {
+        if (many && keep_charge_m == 2 && pl.mq_kept && has_q) {
             // the charges' leaf multipoles of the keeping pass are still in M:
             // the dipoles are added to them
-            if (has_d && pl.n_dleaves > 0) dipole_leaves(0, 1);
+            if (has_d && pl.n_dleaves > 0) by_wave(pl.dleaves.p, pl.n_dleaves, 0, 1, 1);
             pl.mq_kept = false;
-        } else if (quad && half) {
+        } else if (many) {
             // charges in two halves of the orders on the leaves without
             // dipoles (all leaves when there are none), then the leaves with
             // dipoles, charges and dipoles together
@@ -3300,21 +3102,9 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                                pl.nser, Pp, pl.M.p, split_d, pl.Lc.p, lc_len);
             lc_clear = true;
             if (keep_charge_m == 1 && has_q && !has_d) pl.mq_kept = true;
-            if (split_d) dipole_leaves(has_q, 0);
-        } else if (quad) {
-            hipLaunchKernelGGL(quad, dim3((unsigned)((pl.nleaf + 15) / 16)), dim3(64), tabs, ctx.stream,
-                               leaf_base, pl.nleaf, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs,
-                               dns, pl.toff[1], has_q, has_d, inv_alpha, 1.0 / pl.lev[L].R,
-                               pl.invFY.p + L * lvl, pl.dipa.p + L * lvl, pl.dipb.p + L * lvl, pl.cnn.p,
-                               pl.serc.p, pl.nser, p, Pp, pl.M.p, (const int32_t *)nullptr, 0, (const int4 *)nullptr,
-                               (const int32_t *)nullptr, (const double *)nullptr, 0);
+            if (split_d) by_wave(pl.dleaves.p, pl.n_dleaves, has_q, 1, 0);
         } else {
-            const size_t shp = ((size_t)(p + 2) * 64 + 4 * Pp) * sizeof(double) + tabs;
-            hipLaunchKernelGGL(k_p2m<0>, dim3((unsigned)((pl.nleaf + 3) / 4)), dim3(64), shp, ctx.stream,
-                               leaf_base, pl.nleaf, pl.lrange.p, pl.bcx.p, pl.bcy.p, pl.px.p, pl.py.p, qs,
-                               dns, pl.toff[1], has_q, has_d, inv_alpha, 1.0 / pl.lev[L].R,
-                               pl.invFY.p + L * lvl, pl.dipa.p + L * lvl, pl.dipb.p + L * lvl, pl.cnn.p,
-                               pl.serc.p, pl.nser, p, Pp, pl.M.p);
+            by_wave(nullptr, pl.nleaf, has_q, has_d, 0);
         }
         check_launch(ctx, "k_p2m");
         }
