@@ -293,41 +293,80 @@ __global__ void k_fft_twiddles(double *__restrict__ tw) {
 // long ones (one workgroup per curve), so they take more threads per stage
 constexpr int fft_threads(int logn) { return logn >= 11 ? 1024 : 256; }
 
-// The radix-2 stages of an in-place FFT of N = 2^LOGN points in LDS (input in
-// bit-reversed order, decimation in time) by NT threads, factors
-// e^{SIGN i pi k / half} from tw; each thread issues the loads of its
-// butterflies' factors of a stage together, before their LDS work
-template <int LOGN, int SIGN>
-__device__ __forceinline__ void fft_stages(double *re, double *im, const double *__restrict__ tw) {
-    constexpr int NT = fft_threads(LOGN), NBF = (1 << LOGN) / 2, BPT = (NBF + NT - 1) / NT;
-    for (int s = 1; s <= LOGN; ++s) {
-        const int half = 1 << (s - 1);
-        double cs[BPT], sn[BPT];
-#pragma unroll
-        for (int u = 0; u < BPT; ++u) {
-            // (k < half, so e < kTwHalf for every thread)
-            const int e = ((threadIdx.x + NT * u) & (half - 1)) << (kFftMaxLog - s);
-            cs[u] = tw[2 * e];
-            sn[u] = SIGN * tw[2 * e + 1];
-        }
-#pragma unroll
-        for (int u = 0; u < BPT; ++u) {
-            const int t = threadIdx.x + NT * u;
-            if (NBF % NT == 0 || t < NBF) {
-                const int k = t & (half - 1), i = ((t >> (s - 1)) << s) + k, j = i + half;
-                const double tr = re[j] * cs[u] - im[j] * sn[u], ti = re[j] * sn[u] + im[j] * cs[u];
-                re[j] = re[i] - tr;
-                im[j] = im[i] - ti;
-                re[i] += tr;
-                im[i] += ti;
-            }
-        }
-        __syncthreads();
+// LDS place of point j: the top bits of j change the lowest ones, so that the
+// bit-reversed input, whose consecutive points lie N/2, N/4, ... apart, and the
+// first stages' points do not fall on one bank
+template <int LOGN> __device__ __forceinline__ int fft_place(int j) {
+    if constexpr (LOGN > 6) {
+        constexpr int sh = LOGN >= 12 ? LOGN - 6 : 6;
+        return j ^ ((j >> sh) & 63);
+    } else {
+        return j;
     }
 }
 
+// R radix-2 stages s0 .. s0 + R - 1 of an in-place FFT of N = 2^LOGN points in
+// LDS by NT threads, factors e^{SIGN i pi k / half} from tw: a thread carries the
+// 2^R points that these stages combine through them in registers, with the
+// stages' factors loaded together before the points.
+template <int LOGN, int SIGN, int R>
+__device__ __forceinline__ void fft_pass(double *re, double *im, const double *__restrict__ tw, int s0) {
+    constexpr int NT = fft_threads(LOGN), NP = 1 << R, NG = (1 << LOGN) / NP;
+    const int h0 = 1 << (s0 - 1);
+    for (int t = threadIdx.x; t < NG; t += NT) {
+        const int k = t & (h0 - 1), first = ((t >> (s0 - 1)) << (s0 - 1 + R)) + k;
+        double cs[NP], sn[NP];   // stage q's factors at 2^q - 1 + m
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+#pragma unroll
+            for (int m = 0; m < (1 << q); ++m) {
+                // (k + m h0 < h0 2^q, so e < kTwHalf)
+                const int e = (k + m * h0) << (kFftMaxLog - s0 - q);
+                cs[(1 << q) - 1 + m] = tw[2 * e];
+                sn[(1 << q) - 1 + m] = SIGN * tw[2 * e + 1];
+            }
+        double a[NP], b[NP];
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            const int x = fft_place<LOGN>(first + m * h0);
+            a[m] = re[x];
+            b[m] = im[x];
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+#pragma unroll
+            for (int m = 0; m < NP; ++m)
+                if (!((m >> q) & 1)) {
+                    const int n = m + (1 << q), f = (1 << q) - 1 + (m & ((1 << q) - 1));
+                    const double tr = a[n] * cs[f] - b[n] * sn[f], ti = a[n] * sn[f] + b[n] * cs[f];
+                    a[n] = a[m] - tr;
+                    b[n] = b[m] - ti;
+                    a[m] += tr;
+                    b[m] += ti;
+                }
+#pragma unroll
+        for (int m = 0; m < NP; ++m) {
+            const int x = fft_place<LOGN>(first + m * h0);
+            re[x] = a[m];
+            im[x] = b[m];
+        }
+    }
+    __syncthreads();
+}
+
+// The stages of an in-place FFT (input in bit-reversed order, decimation in
+// time), three to a pass: one workgroup's LDS traffic and barriers bound the few
+// large transforms (8,192 points, a pass per stage: forward 35 us and shifted
+// inverse 62; three stages to a pass 23 and 51, of which the shifts' sines 28).
+template <int LOGN, int SIGN>
+__device__ __forceinline__ void fft_stages(double *re, double *im, const double *__restrict__ tw) {
+    constexpr int R0 = LOGN % 3;
+    if constexpr (R0 > 0) fft_pass<LOGN, SIGN, R0>(re, im, tw, 1);
+    for (int s = 1 + R0; s <= LOGN; s += 3) fft_pass<LOGN, SIGN, 3>(re, im, tw, s);
+}
+
 // Fourier coefficients c_k = (1/N) sum_j v_j e^{-2 pi i j k / N} of a curve
-// whose N = 2^LOGN, by an in-place radix-2 FFT in LDS (input in bit-reversed
+// whose N = 2^LOGN, by an in-place FFT in LDS (input in bit-reversed
 // order, decimation in time); one workgroup per (curve, field)
 template <int LOGN>
 __global__ __launch_bounds__(1024) void k_fft_coef(const int32_t *__restrict__ curves, const int64_t *__restrict__ off,
@@ -340,15 +379,16 @@ __global__ __launch_bounds__(1024) void k_fft_coef(const int32_t *__restrict__ c
     const double *v = blockIdx.y ? v1 : v0;
     double *cf = blockIdx.y ? c1 : c0;
     for (int i = threadIdx.x; i < N; i += blockDim.x) {
-        const int j = (int)(__brev((unsigned)i) >> (32 - LOGN));
+        const int j = fft_place<LOGN>((int)(__brev((unsigned)i) >> (32 - LOGN)));
         re[j] = v[base + i];
         im[j] = 0.0;
     }
     __syncthreads();
     fft_stages<LOGN, -1>(re, im, tw);
     for (int i = threadIdx.x; i < N; i += blockDim.x) {
-        cf[2 * (base + i)] = re[i] * (1.0 / N);
-        cf[2 * (base + i) + 1] = im[i] * (1.0 / N);
+        const int x = fft_place<LOGN>(i);
+        cf[2 * (base + i)] = re[x] * (1.0 / N);
+        cf[2 * (base + i) + 1] = im[x] * (1.0 / N);
     }
 }
 
@@ -368,7 +408,7 @@ __global__ __launch_bounds__(1024) void k_fft_fine(const int32_t *__restrict__ c
     const int cidx = blockIdx.x / kNearM, r = blockIdx.x - cidx * kNearM;
     const int64_t base = off[curves[cidx]];
     for (int k = threadIdx.x; k < N; k += blockDim.x) {
-        const int j = (int)(__brev((unsigned)k) >> (32 - LOGN));
+        const int j = fft_place<LOGN>((int)(__brev((unsigned)k) >> (32 - LOGN)));
         const double a = coef[2 * (base + k)], b = coef[2 * (base + k) + 1];
         if (2 * k == N) {
             re[j] = a * cospi((double)r / kNearM);
@@ -385,7 +425,7 @@ __global__ __launch_bounds__(1024) void k_fft_fine(const int32_t *__restrict__ c
     fft_stages<LOGN, 1>(re, im, tw);
     for (int j = threadIdx.x; j < N; j += blockDim.x) {
         const int64_t f = kNearM * base + (int64_t)kNearM * j + r;
-        const double sgm = fw[f] * re[j];
+        const double sgm = fw[f] * re[fft_place<LOGN>(j)];
         fdn[2 * f] = sgm * fnrm[2 * f];
         fdn[2 * f + 1] = sgm * fnrm[2 * f + 1];
     }
