@@ -66,7 +66,7 @@ def near_flops(info):
     return info.pairs_charge * fq + info.pairs_dipole * fd
 
 
-def rooflines(info, st, steps, fp32):
+def rooflines(info, st, steps, fp32, groups=0):
     """Per-kernel rooflines from the serialised per-stage event times.
 
     Near field (cached): algorithmic bytes = the interaction values read once
@@ -75,8 +75,10 @@ def rooflines(info, st, steps, fp32):
     writes; with the symmetric layout a charge value stands for two pairs
     (stored once per pair of neighbouring leaves).  Source strengths and
     outputs add under 3% and are not counted.
-    M2L: 2 P^2 flops per non-empty V-list translation (padding not credited),
-    against the dense matrix-core peak of the arithmetic type."""
+    M2L by groups of siblings (FP64, 64 padded coefficients): the multiply-adds
+    of the square's symmetry classes, SYM_GROUP_FLOPS per parent; else 2 P^2
+    flops per non-empty V-list translation (padding not credited); against the
+    dense matrix-core peak of the arithmetic type."""
     out = {}
     leaf_ms, leaf_calls = st["leaf"]
     if leaf_calls:
@@ -94,23 +96,25 @@ def rooflines(info, st, steps, fp32):
     if m2l_calls:
         t = m2l_ms / m2l_calls
         peak = PEAK_FP32_MFMA_TF if fp32 else PEAK_FP64_MFMA_TF
-        ach = m2l_flops(info) / (t * 1e-3) / 1e12
+        flops = SYM_GROUP_FLOPS * groups if groups else m2l_flops(info)
+        ach = flops / (t * 1e-3) / 1e12
         out["m2l"] = {"kernel": ("k_tile_gemm (M2L, all levels, FP32)" if fp32 else
-                                 "k_m2l_persist (M2L, all levels, one resident round)"),
+                                 "k_m2l_sym (M2L, all levels, by groups of siblings)" if groups else
+                                 "k_tile_gemm (M2L, all levels)"),
                       "bound": "mfma", "achieved": ach,
                       "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
-                      "traffic": None if fp32 else measured_traffic("k_m2l_persist"), "avg_launch_ms": t,
-                      "launches_per_pass": m2l_calls / steps, "algorithmic_flops": m2l_flops(info)}
+                      "traffic": None if fp32 else measured_traffic("k_m2l_sym"), "avg_launch_ms": t,
+                      "launches_per_pass": m2l_calls / steps, "algorithmic_flops": flops}
     # the upward and downward chain: 10 P flops per point for P2M and L2P
     # (the expansion's P terms, about ten operations each), 2 P^2 per
     # child-parent translation for M2M and L2L (one dense P x P product);
     # FP64 in both precision modes (P2M, M2M, L2P) or in FP64 mode (L2L),
     # against the FP64 peak; per pass (all launches of the stage)
     P = info.P
-    chain = {"p2m": ("P2M (k_p2m_half + k_p2m_quad, or cached rows on small trees)", 10.0 * P * info.p2m_points),
-             "m2m": ("M2M (k_tile_gemm on large levels, k_small_gemv on small ones)",
+    chain = {"p2m": ("P2M (k_p2m_half + k_p2m_wave, or cached rows on small trees)", 10.0 * P * info.p2m_points),
+             "m2m": ("M2M (k_m2m_wide on large levels, subtrees by k_m2m)",
                      2.0 * P * P * info.m2m_children),
-             "l2l": ("L2L (k_tile_gemm on large levels, k_small_gemv on small ones)",
+             "l2l": ("L2L (k_l2l_wide on large levels, subtrees by k_l2l)",
                      2.0 * P * P * info.l2l_children),
              "l2p": ("k_l2p (L2P, writes the outputs)", 10.0 * P * info.l2p_points)}
     for key, (kname, flops) in chain.items():
@@ -142,6 +146,19 @@ def measured_traffic(kernel):
     except OSError:
         pass
     return None
+
+
+# multiply-adds (times two) of a parent's M2L: the eight symmetry-adapted blocks of
+# the 4 x 64 target against the 32 x 64 source coefficients of its group
+SYM_GROUP_FLOPS = 2.0 * 98304
+
+
+def m2l_groups(yk, ctx, info):
+    """Groups of siblings that M2L serves: the parents of the boxes of levels lmin and finer."""
+    if info.Pp != 64 or info.m2l_sparse or info.lmin > info.leaf_level:
+        return 0
+    t = yk.yk_plan_tree_export(ctx, 0)
+    return len(np.unique(t["parent"][t["level_begin"][info.lmin]:]))
 
 
 def m2l_flops(info):
@@ -212,6 +229,7 @@ def run_fmm_bench(args, yk, torch, W, fp32=None, lite=False):
         opt.debug_flags, opt.near_cache_mb = 0, yk.yk_default_options().near_cache_mb
         yk.yk_set_options(ctx, opt)
         info = yk.yk_plan_info_get(ctx, 0)
+        groups = 0 if fp32 else m2l_groups(yk, ctx, info)
         ov = out_v.cpu().numpy()
         ob = out_b.cpu().numpy()
     finally:
@@ -238,7 +256,7 @@ def run_fmm_bench(args, yk, torch, W, fp32=None, lite=False):
     ms = total_ms / args.steps
     res = dict(cfg=cfg, n_pts=n_pts, ms=ms, first_ms=first_ms, info=info, stages=stages,
                stages_overlap=stages_overlap, near_build_ms=near_build_ms, stages_otf=stages_otf,
-               stages_full=stages_full, info_full=info_full, out=np.concatenate([ov, ob]))
+               stages_full=stages_full, info_full=info_full, m2l_groups=groups, out=np.concatenate([ov, ob]))
     return res
 
 
@@ -761,7 +779,7 @@ def main():
     res = run_fmm_bench(args, yk, torch, W)
     info, st = res["info"], res["stages"]
     value = res["n_pts"] / (res["ms"] * 1e-3) / 1e6
-    roofs = rooflines(info, st, args.steps, args.fp32)
+    roofs = rooflines(info, st, args.steps, args.fp32, res["m2l_groups"])
     # the on-the-fly near-field kernel (Bessel series per pair), FP64 vector units
     otf_ms, otf_calls = res["stages_otf"]["leaf"]
     if otf_calls and not args.fp32:

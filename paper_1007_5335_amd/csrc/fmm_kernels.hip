@@ -2836,8 +2836,9 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
     // the whole far field; large trees fill the GPU with either, and sharing it
     // was measured no faster than running the stages in turn.  (A density
     // solve on 28,672 nodes, 15 operator applications: 1.75 ms with the second
-    // stream, 1.63 in one launch; a step on 64^2 cells 1.41 and 1.10 ms; a pass
-    // over 4,096 + 1,536 points 66 and 65 us.)
+    // stream and 1.63 in one launch when that was introduced; now 1.53, the
+    // stages in turn 1.66; a step on 64^2 cells 0.89 and 0.94 ms; a pass over
+    // 4,096 + 1,536 points 61 and 72 us.)
     const bool merged = far && near_cached && p2m_cached && wide && !(ctx.opt.debug_flags & 2);
     const bool overlap = !merged && !(ctx.opt.debug_flags & 2) && pl.nleaf < 8192 && near_on;
 
