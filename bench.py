@@ -75,7 +75,7 @@ def rooflines(info, st, steps, fp32, groups=0):
     writes; with the symmetric layout a charge value stands for two pairs
     (stored once per pair of neighbouring leaves).  Source strengths and
     outputs add under 3% and are not counted.
-    M2L by groups of siblings (FP64, 64 padded coefficients): the multiply-adds
+    M2L by groups of siblings (64 padded coefficients, FP64 in both modes): the multiply-adds
     of the square's symmetry classes, SYM_GROUP_FLOPS per parent; else 2 P^2
     flops per non-empty V-list translation (padding not credited); against the
     dense matrix-core peak of the arithmetic type."""
@@ -95,12 +95,11 @@ def rooflines(info, st, steps, fp32, groups=0):
     m2l_ms, m2l_calls = st["m2l"]
     if m2l_calls:
         t = m2l_ms / m2l_calls
-        peak = PEAK_FP32_MFMA_TF if fp32 else PEAK_FP64_MFMA_TF
+        peak = PEAK_FP32_MFMA_TF if fp32 and not groups else PEAK_FP64_MFMA_TF
         flops = SYM_GROUP_FLOPS * groups if groups else m2l_flops(info)
         ach = flops / (t * 1e-3) / 1e12
-        out["m2l"] = {"kernel": ("k_tile_gemm (M2L, all levels, FP32)" if fp32 else
-                                 "k_m2l_sym (M2L, all levels, by groups of siblings)" if groups else
-                                 "k_tile_gemm (M2L, all levels)"),
+        out["m2l"] = {"kernel": ("k_m2l_sym (M2L, all levels, by groups of siblings, FP64)" if groups else
+                                 f"k_tile_gemm (M2L, all levels, {'FP32' if fp32 else 'FP64'})"),
                       "bound": "mfma", "achieved": ach,
                       "peak": peak, "unit": "TFLOP/s", "frac": ach / peak,
                       "traffic": None if fp32 else measured_traffic("k_m2l_sym"), "avg_launch_ms": t,
@@ -229,7 +228,7 @@ def run_fmm_bench(args, yk, torch, W, fp32=None, lite=False):
         opt.debug_flags, opt.near_cache_mb = 0, yk.yk_default_options().near_cache_mb
         yk.yk_set_options(ctx, opt)
         info = yk.yk_plan_info_get(ctx, 0)
-        groups = 0 if fp32 else m2l_groups(yk, ctx, info)
+        groups = m2l_groups(yk, ctx, info)
         ov = out_v.cpu().numpy()
         ob = out_b.cpu().numpy()
     finally:
@@ -812,8 +811,8 @@ def main():
     err, errmax, idx, ref = direct_check(args, res, yk, torch)
     fp32_pass = None
     if not args.fp32 and not args.no_fp32_pass:
-        # the same pass with FP32 sums (P2P and M2L in FP32, M2L on FP32 matrix
-        # cores) at the same expansion order; its error is set by FP32 rounding
+        # the same pass with FP32 sums (P2P in FP32; M2L by groups of siblings stays
+        # FP64) at the same expansion order; its error is set by FP32 rounding
         r32 = run_fmm_bench(args, yk, torch, W, fp32=True, lite=True)
         got = r32["out"][idx]
         fp32_pass = {
@@ -821,7 +820,7 @@ def main():
             "dtype": "f32", "p": r32["info"].p,
             "rel_err_l2_sampled": float(np.linalg.norm(got - ref) / np.linalg.norm(ref)),
             "stage_ms_per_step": {k: v[0] / args.steps for k, v in r32["stages"].items()},
-            "rooflines": rooflines(r32["info"], r32["stages"], args.steps, True)}
+            "rooflines": rooflines(r32["info"], r32["stages"], args.steps, True, r32["m2l_groups"])}
     err_oracle = cpu = None
     if not args.no_cpu:
         err_oracle, cpu = oracle_baseline(args, res, idx)

@@ -679,7 +679,7 @@ void box_potential(Context &ctx, const yk_grid &g, const double *B, double alpha
             check_launch(ctx, "k_box_p2m");
         }
         fmm_m2m(ctx, pl);
-        launch_fill(ctx, m2l_clear_len(pl, as, false), 0.0, pl.Lc.p);
+        launch_fill(ctx, m2l_clear_len(pl, as), 0.0, pl.Lc.p);
         fmm_m2l(ctx, pl, as, false);
         fmm_l2l(ctx, pl, as);
     }
@@ -921,7 +921,7 @@ void box_potential_adaptive(Context &ctx, const double root[3], int64_t n, const
             check_launch(ctx, "k_boxa_p2m");
         }
         fmm_m2m(ctx, pl);
-        launch_fill(ctx, m2l_clear_len(pl, as, false), 0.0, pl.Lc.p);
+        launch_fill(ctx, m2l_clear_len(pl, as), 0.0, pl.Lc.p);
         fmm_m2l(ctx, pl, as, false);
         if (pl.n_xbox > 0) {
             StageTimer tx(ctx, YK_STAGE_M2L);

@@ -290,7 +290,7 @@ void launch_m2m_group(Context &ctx, FmmPlan &pl, const ShiftGroup &gr);
 void launch_l2l_group(Context &ctx, FmmPlan &pl, ActiveSet &as, const ShiftGroup &gr);
 // leading entries of Lc that M2L adds to (to be cleared before it); it writes
 // the others
-int64_t m2l_clear_len(const FmmPlan &pl, const ActiveSet &as, bool f32);
+int64_t m2l_clear_len(const FmmPlan &pl, const ActiveSet &as);
 // terms of the near-field K0/K1 series for pairs with t = r^2/(4 alpha^2) <= tmax
 int near_series_terms(double tmax);
 // the adaptive tree's near-field items by the series they need: kind 0 also

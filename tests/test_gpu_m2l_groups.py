@@ -69,3 +69,34 @@ def test_sibling_groups_match_direct_sums(yk, c):
     # centres of a pair at least two sides apart: the ratio is below 0.547, and
     # the terms left out sum to 0.547^(p+1) / (1 - 0.547)
     assert np.max(np.abs(got[idx] - ref)) <= 0.547 ** (p + 1) / 0.453 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("n,alpha", [(700, 0.3), (20011, 0.02), (60013, 0.0045)])
+def test_sibling_groups_under_fp32_sums(yk, n, alpha):
+    """FP32 sums over the same trees (the groups serve them in FP64): a pass in
+    FP32, one in FP64 and another in FP32 in one context, whose dense tiles and
+    groups share the local expansions."""
+    import torch
+    rng = np.random.default_rng(29)
+    xy, q = rng.random((n, 2)), rng.standard_normal(n)
+    print(f"groups under fp32: {n} {alpha}", flush=True)
+    outs = []
+    ctx = yk.yk_create(leaf_size=16, p=31, tree=yk.YK_TREE_UNIFORM)
+    try:
+        for prec in (yk.YK_PREC_FP32, yk.YK_PREC_FP64, yk.YK_PREC_FP32):
+            opt = yk.yk_default_options()
+            opt.leaf_size, opt.p, opt.tree, opt.precision = 16, 31, yk.YK_TREE_UNIFORM, prec
+            yk.yk_set_options(ctx, opt)
+            out = torch.empty(n, dtype=torch.float64, device="cuda")
+            yk.yk_volume_potential(ctx, dev(xy), dev(q), None, alpha, out)
+            outs.append(host(out))
+    finally:
+        yk.yk_destroy(ctx)
+    idx = rng.choice(n, size=200, replace=False)
+    ref = oracle.volume_sum(xy, q, alpha, tgt_xy=xy[idx])
+    scale = np.max(np.abs(ref))
+    assert np.array_equal(outs[0], outs[2])
+    # the truncation bound above; FP32 values: a sum of at most some 4,000
+    # near-field terms of random sign, each within a few 2^-24 of itself
+    assert np.max(np.abs(outs[1][idx] - ref)) <= 0.547 ** 32 / 0.453 * scale
+    assert np.max(np.abs(outs[0][idx] - ref)) <= 64 * 16 * 2.0 ** -24 * scale
