@@ -94,14 +94,13 @@ __device__ __forceinline__ double dpp_d(double v) {
 // conj(z) upwards.
 template <int PO>
 __global__ __launch_bounds__(64) void k_p2m_quad(
-    const int32_t *__restrict__ lrange,
-    const double *__restrict__ bcx, const double *__restrict__ bcy, const double *__restrict__ px,
-    const double *__restrict__ py, const double *__restrict__ qs, const double *__restrict__ dns,
-    int64_t off1, int has_q, int has_d, double inv_alpha,
+    const int32_t *__restrict__ lrange, const double *__restrict__ bcx, const double *__restrict__ bcy,
+    const double *__restrict__ px, const double *__restrict__ py, const double *__restrict__ qs,
+    const double *__restrict__ dns, int64_t off1, int has_q, int has_d, double inv_alpha,
     const double *__restrict__ invFY, const double *__restrict__ da, const double *__restrict__ db,
-    const double *__restrict__ cnn, const double *__restrict__ sc, int Pp, double *__restrict__ M, const int32_t *__restrict__ leaf_list,
-    const int4 *__restrict__ tiles, const int32_t *__restrict__ nser_lv, const double *__restrict__ invR_lv,
-    int sc_stride) {
+    const double *__restrict__ cnn, const double *__restrict__ sc, int Pp, double *__restrict__ M,
+    const int32_t *__restrict__ leaf_list, const int4 *__restrict__ tiles, const int32_t *__restrict__ nser_lv,
+    const double *__restrict__ invR_lv, int sc_stride) {
     constexpr int p = PO, P = 2 * PO + 1;
     extern __shared__ double smem[];
     const int4 t = tiles[blockIdx.x];
@@ -3130,8 +3129,8 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                 // X lists: coarser leaves' sources straight into the local
                 // expansions (before L2L passes them down)
                 StageTimer tx(ctx, YK_STAGE_M2L);
-                hipLaunchKernelGGL(k_ad_p2l, dim3((unsigned)pl.n_xbox), dim3(64),
-                                   0, ctx.stream, pl.xbox.p, pl.xoff.p, pl.xl.p, pl.lrange.p, has_q, has_d, pl.blevel.p, pl.bcx.p, pl.bcy.p, pl.px.p,
+                hipLaunchKernelGGL(k_ad_p2l, dim3((unsigned)pl.n_xbox), dim3(64), 0, ctx.stream, pl.xbox.p, pl.xoff.p,
+                                   pl.xl.p, pl.lrange.p, has_q, has_d, pl.blevel.p, pl.bcx.p, pl.bcy.p, pl.px.p,
                                    pl.py.p, qs, dns, pl.toff[1], pl.rI.p, p, Pp, inv_alpha, pl.Lc.p);
                 check_launch(ctx, "k_ad_p2l");
             }
