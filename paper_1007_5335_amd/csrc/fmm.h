@@ -288,8 +288,9 @@ void launch_m2l_sym(Context &ctx, FmmPlan &pl, ActiveSet &as);
 void build_shift_ops(Context &ctx, FmmPlan &pl);
 void launch_m2m_group(Context &ctx, FmmPlan &pl, const ShiftGroup &gr);
 void launch_l2l_group(Context &ctx, FmmPlan &pl, ActiveSet &as, const ShiftGroup &gr);
-// leading entries of Lc that M2L adds to (to be cleared before it); it writes
-// the others
+// leading entries of Lc that M2L adds to (to be cleared before it); of the
+// others it writes the active boxes' whole rows, padding included: nothing that
+// a pass leaves in Lc reaches the next one
 int64_t m2l_clear_len(const FmmPlan &pl, const ActiveSet &as);
 // terms of the near-field K0/K1 series for pairs with t = r^2/(4 alpha^2) <= tmax
 int near_series_terms(double tmax);

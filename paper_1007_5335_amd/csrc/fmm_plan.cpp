@@ -856,8 +856,6 @@ void build_tables(Context &ctx, FmmPlan &pl, int p) {
     }
     pl.M.ensure((size_t)nb * Pp);
     pl.Lc.ensure((size_t)nb * Pp);
-    // (the padding entries of rows that M2L writes stay zero)
-    launch_fill(ctx, nb * (int64_t)Pp, 0.0, pl.Lc.p);
     build_sym_ops(ctx, pl);
     build_shift_ops(ctx, pl);
     YK_HIP(hipStreamSynchronize(ctx.stream));

@@ -464,7 +464,7 @@ __global__ __launch_bounds__(256, 2) void k_m2l_sym(const int4 *__restrict__ til
             if (b >= 0) {
                 double *o = out + (int64_t)b * kSymPP;
                 o[n == 0 ? 0 : 2 * n - 1] = x;
-                if (n > 0) o[2 * n] = y;
+                o[n == 0 ? kSymPP - 1 : 2 * n] = n == 0 ? 0.0 : y;   // (n = 0: the padding entry)
             }
         }
     }

@@ -11,6 +11,10 @@
 // order the lanes consume them and stream from L2 through a ring of registers.
 // Bound by latency: descriptor, coefficient rows, then per level a chain of 32
 // or more operator fragments from L2 and the matrix-core steps they feed.
+// A padding row of a product is 0 x the source: zero, or NaN where the source's
+// own row is not finite (setting it to zero in the stores took 1% of a pass over
+// 7,147 nodes and 50,021 targets).  It lasts for the pass: M2M writes its boxes'
+// rows whole, and M2L, or the clearing before it, those of L.
 // Measured (one launch per level before): the 28,672-node boundary tree's five
 // levels 27 us of M2M and 20 of L2L in ten launches, now 20 + 18 in four; 2^20
 // points 61 + 66 us, now 49 + 62 (the finest level 20 -> 20 and 29 -> 28: its
