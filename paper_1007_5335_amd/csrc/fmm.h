@@ -201,7 +201,8 @@ struct FmmPlan {
 
     // operators (double, column-major Pp x Pp blocks)
     DevBuf<double> m2m, l2l, m2l;      // [level][4][Pp*Pp], [level][4][Pp*Pp], [level][40][Pp*Pp]
-    DevBuf<float> m2lf;
+    DevBuf<float> m2lf;                // m2l in FP32, made by the first pass that reads it
+    bool m2lf_built = false;
     std::vector<ShiftGroup> m2m_groups;   // finest first
     DevBuf<int32_t> up_desc;
     DevBuf<double> up_op, down_op;     // M2M and L2L: operator fragments (shifts.hip)

@@ -2704,6 +2704,21 @@ int64_t m2l_clear_len(const FmmPlan &pl, const ActiveSet &as) {
     return as.n_sym_coarse > 0 ? 0 : pl.lev[as.sym_level].begin * (int64_t)pl.Pp;
 }
 
+// The M2L operators in FP32, for the routes that sum in it: sparse lists, or
+// fewer than 64 padded coefficients.  Made on first use: most trees never read
+// them (0.66 MB a level at 64 coefficients; converted and sent by the host with
+// every tree, 0.3 of the 23.8 ms that the tables of 4,096 points take).
+static const float *m2l_f32(Context &ctx, FmmPlan &pl) {
+    const int64_t n = (int64_t)(pl.L + 1) * kNumOff * pl.Pp * pl.Pp;
+    float *f = pl.m2lf.ensure(n);
+    if (!pl.m2lf_built) {
+        hipLaunchKernelGGL(k_to_float, dim3(nblk(n, 256)), dim3(256), 0, ctx.stream, n, pl.m2l.p, f);
+        check_launch(ctx, "k_to_float");
+        pl.m2lf_built = true;
+    }
+    return f;
+}
+
 // M2L of every level at once into the zeroed local expansions
 void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
     const int P = pl.P, Pp = pl.Pp;
@@ -2720,7 +2735,7 @@ void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
         slab.rows = as.csr_rows.p;
         if (as.m2l_sparse && f32)
             launch_tile_gemm<float, float>(ctx, P, Pp, as.n_ptiles, as.m2l_ptiles.p, 0, as.m2l_piota.p,
-                                           1, as.m2l_psrc.p, pl.iota40.p, pl.m2lf.p,
+                                           1, as.m2l_psrc.p, pl.iota40.p, m2l_f32(ctx, pl),
                                            (int64_t)kNumOff * Pp * Pp, 0, pl.Mf.p, 0, pl.Lc.p,
                                            as.m2l_ptgt.p, &slab, as.n_ptrans);
         else if (as.m2l_sparse)
@@ -2731,7 +2746,7 @@ void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
         else if (f32 && !use_sym(pl, as))
             launch_tile_gemm<float, float, 2>(ctx, P, Pp, as.n_tiles_w, as.m2l_tiles_w.p, 0,
                                               as.m2l_boxes.p, kNumV, pl.vlist.p, pl.slot_oid.p,
-                                              pl.m2lf.p, (int64_t)kNumOff * Pp * Pp, 0, pl.Mf.p, 0,
+                                              m2l_f32(ctx, pl), (int64_t)kNumOff * Pp * Pp, 0, pl.Mf.p, 0,
                                               pl.Lc.p, nullptr, &slab);
         else {
             // sibling groups at the levels they serve, the dense products by

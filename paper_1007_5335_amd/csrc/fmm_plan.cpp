@@ -850,10 +850,7 @@ void build_tables(Context &ctx, FmmPlan &pl, int p) {
     up(pl.m2m, m2m);
     up(pl.l2l, l2l);
     up(pl.m2l, m2l);
-    {
-        std::vector<float> f(m2l.begin(), m2l.end());
-        up(pl.m2lf, f);
-    }
+    pl.m2lf_built = false;
     pl.M.ensure((size_t)nb * Pp);
     pl.Lc.ensure((size_t)nb * Pp);
     build_sym_ops(ctx, pl);
