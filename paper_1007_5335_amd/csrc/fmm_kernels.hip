@@ -598,9 +598,8 @@ template <> struct Mfma<float> {
     static __device__ __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
 };
 
-// Generic form used for M2L (27 V-list slots per box), M2M (4 child slots per
-// parent) and L2L (1 parent slot per child):
-//   out[box] (+)= sum_s Op[level + level_shift][slot_op[cls][s]] * X[src[box][s]]
+// M2L by box, over its 27 V-list slots or (sparse) one translation at a time:
+//   out[box] += sum_s Op[level][slot_op[cls][s]] * X[src[box][s]]
 // Every box of a tile has the same level and parity class (so the same
 // operator per slot).  X is read in its own type TS and converted to T.
 //
@@ -628,8 +627,8 @@ __global__ __launch_bounds__(256) void k_tile_gemm(const int4 *__restrict__ tile
                                                    const int32_t *__restrict__ src,
                                                    const int32_t *__restrict__ slot_op,
                                                    const T *__restrict__ Op, int64_t op_stride,
-                                                   int level_shift, const TS *__restrict__ X,
-                                                   int assign, int nparts, double *__restrict__ out,
+                                                   const TS *__restrict__ X, int nparts,
+                                                   double *__restrict__ out,
                                                    const int32_t *__restrict__ tgt, double *__restrict__ slab) {
     constexpr bool SPLIT = SPLIT_REQ && PP > 16;   // (the host never asks for PP = 16)
     constexpr int NB = SPLIT ? PP / 16 - 1 : PP / 16;   // 16-row blocks on the matrix cores
@@ -650,10 +649,10 @@ __global__ __launch_bounds__(256) void k_tile_gemm(const int4 *__restrict__ tile
     __shared__ int32_t s_src[kMaxSlot * NC];
     using MF = Mfma<T>;
     // nparts > 1 (few tiles): the slots of a tile are shared among nparts
-    // workgroups (assign must be 0).  With tgt (sparse M2L) the tile's
-    // entries are translation indices: the source is src[entry], the target
-    // is row tgt[entry].  In both cases several workgroups contribute to one
-    // output row, so each stores its result in a row of its own of slab
+    // workgroups.  With tgt (sparse M2L) the tile's entries are translation
+    // indices: the source is src[entry], the target is row tgt[entry].  In both
+    // cases several workgroups contribute to one output row, so each stores its
+    // result in a row of its own of slab
     // (translation `entry`, or column j of workgroup bid: row bid * NC + j),
     // which k_slab_reduce_* then add to the outputs in a fixed order: the
     // sums do not depend on the order the workgroups run in.
@@ -692,7 +691,7 @@ __global__ __launch_bounds__(256) void k_tile_gemm(const int4 *__restrict__ tile
 #pragma unroll
             for (int q = 0; q < 4; ++q) colacc[c][r][q] = T(0);
     }
-    const T *Olev = Op + (int64_t)(level + level_shift) * op_stride;
+    const T *Olev = Op + (int64_t)level * op_stride;
     auto op_of = [&](int sl) -> const T2 * {
         return reinterpret_cast<const T2 *>(Olev + (size_t)slot_op[cls * nslot + sl] * PP * PP);
     };
@@ -821,9 +820,8 @@ __global__ __launch_bounds__(256) void k_tile_gemm(const int4 *__restrict__ tile
             rowacc[c] += __shfl_xor(rowacc[c], 32, 64);
         }
         if (colvalid[c]) {
-            const bool to_slab = slab != nullptr;
-            const int store = to_slab || assign;
-            double *o = to_slab ? slab + (tgt ? (int64_t)boxes[start + jb[c]] : (int64_t)bid * NC + jb[c]) * PP
+            const bool store = slab != nullptr;
+            double *o = store ? slab + (tgt ? (int64_t)boxes[start + jb[c]] : (int64_t)bid * NC + jb[c]) * PP
                                 : out + boxj[c] * PP;
 #pragma unroll
             for (int rt = 0; rt < NB; ++rt)
@@ -835,7 +833,7 @@ __global__ __launch_bounds__(256) void k_tile_gemm(const int4 *__restrict__ tile
                 }
             if constexpr (SPLIT) {
                 if (g == 0) o[SP] = store ? (double)rowacc[c] : o[SP] + (double)rowacc[c];
-                // padding entries SP + 1 .. PP - 1 stay zero for later readers
+                // padding entries SP + 1 .. PP - 1: the sums over the rows take them too
                 if (store)
                     for (int i = SP + 1 + g; i < PP; i += 4) o[i] = 0.0;
             }
@@ -1057,15 +1055,14 @@ struct SlabPlan {
 template <typename T, typename TS, int CB = 1>
 void launch_tile_gemm(Context &ctx, int P, int Pp, int ntiles, const int4 *tiles, int tile0,
                       const int32_t *boxes, int nslot, const int32_t *src, const int32_t *slot_op,
-                      const T *Op, int64_t op_stride, int level_shift, const TS *X, int assign,
-                      double *out, const int32_t *tgt = nullptr, const SlabPlan *slab = nullptr,
-                      int64_t ntrans = 0) {
+                      const T *Op, int64_t op_stride, const TS *X, double *out, const int32_t *tgt = nullptr,
+                      const SlabPlan *slab = nullptr, int64_t ntrans = 0) {
     if (ntiles <= 0) return;
     if (nslot < 1 || nslot > 27) throw Error{YK_ERR_INTERNAL, "tile GEMM supports 1..27 slots"};
     const bool split = Pp >= 32 && P == Pp - 15;
     // fewer tiles than compute units: share each tile's slots among up to 7
     // workgroups (about 4 slots each), whose partial rows are summed after
-    const int nparts = (!assign && slab && nslot >= 8 && ntiles < 256) ? std::min(kMaxParts, (512 + ntiles - 1) / ntiles) : 1;
+    const int nparts = (slab && nslot >= 8 && ntiles < 256) ? std::min(kMaxParts, (512 + ntiles - 1) / ntiles) : 1;
     const unsigned grid = (unsigned)ntiles * (unsigned)nparts;
     if (tgt && !slab) throw Error{YK_ERR_INTERNAL, "sparse tile GEMM needs a slab"};
     constexpr int NC = 64 * CB;
@@ -1077,11 +1074,11 @@ void launch_tile_gemm(Context &ctx, int P, int Pp, int ntiles, const int4 *tiles
         if (split)                                                                                 \
             hipLaunchKernelGGL((k_tile_gemm<T, TS, PPV, true, CB>), dim3(grid), dim3(256), 0,     \
                                ctx.stream, tiles, tile0, boxes, nslot, src, slot_op, Op, op_stride, \
-                               level_shift, X, assign, nparts, out, tgt, sl);                     \
+                               X, nparts, out, tgt, sl);                                          \
         else                                                                                       \
             hipLaunchKernelGGL((k_tile_gemm<T, TS, PPV, false, CB>), dim3(grid), dim3(256), 0,    \
                                ctx.stream, tiles, tile0, boxes, nslot, src, slot_op, Op, op_stride, \
-                               level_shift, X, assign, nparts, out, tgt, sl);                     \
+                               X, nparts, out, tgt, sl);                                          \
         break;
     switch (Pp) {
         YK_TILE_CASE(16)
@@ -2736,18 +2733,18 @@ void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
         if (as.m2l_sparse && f32)
             launch_tile_gemm<float, float>(ctx, P, Pp, as.n_ptiles, as.m2l_ptiles.p, 0, as.m2l_piota.p,
                                            1, as.m2l_psrc.p, pl.iota40.p, m2l_f32(ctx, pl),
-                                           (int64_t)kNumOff * Pp * Pp, 0, pl.Mf.p, 0, pl.Lc.p,
+                                           (int64_t)kNumOff * Pp * Pp, pl.Mf.p, pl.Lc.p,
                                            as.m2l_ptgt.p, &slab, as.n_ptrans);
         else if (as.m2l_sparse)
             launch_tile_gemm<double, double>(ctx, P, Pp, as.n_ptiles, as.m2l_ptiles.p, 0,
                                              as.m2l_piota.p, 1, as.m2l_psrc.p, pl.iota40.p, pl.m2l.p,
-                                             (int64_t)kNumOff * Pp * Pp, 0, pl.M.p, 0, pl.Lc.p,
+                                             (int64_t)kNumOff * Pp * Pp, pl.M.p, pl.Lc.p,
                                              as.m2l_ptgt.p, &slab, as.n_ptrans);
         else if (f32 && !use_sym(pl, as))
             launch_tile_gemm<float, float, 2>(ctx, P, Pp, as.n_tiles_w, as.m2l_tiles_w.p, 0,
                                               as.m2l_boxes.p, kNumV, pl.vlist.p, pl.slot_oid.p,
-                                              m2l_f32(ctx, pl), (int64_t)kNumOff * Pp * Pp, 0, pl.Mf.p, 0,
-                                              pl.Lc.p, nullptr, &slab);
+                                              m2l_f32(ctx, pl), (int64_t)kNumOff * Pp * Pp, pl.Mf.p, pl.Lc.p,
+                                              nullptr, &slab);
         else {
             // sibling groups at the levels they serve, the dense products by
             // box at the others (the leading tiles, which are level-major)
@@ -2766,7 +2763,7 @@ void fmm_m2l(Context &ctx, FmmPlan &pl, ActiveSet &as, bool f32) {
             } else
                 launch_tile_gemm<double, double, 1>(ctx, P, Pp, nt, as.m2l_tiles.p, 0, as.m2l_boxes.p, kNumV,
                                                     pl.vlist.p, pl.slot_oid.p, pl.m2l.p,
-                                                    (int64_t)kNumOff * Pp * Pp, 0, pl.M.p, 0, pl.Lc.p, nullptr,
+                                                    (int64_t)kNumOff * Pp * Pp, pl.M.p, pl.Lc.p, nullptr,
                                                     &slab);
         }
     }
