@@ -485,7 +485,7 @@ struct Strengths {
 // one block of four wavefronts per leaf, lanes over coefficients: wavefront w
 // sums the leaf's points w, w + 4, ... (two chains per lane) and the four
 // partial rows are added through LDS; the blocks also clear zero[0..nzero)
-constexpr int kRowStage = 256;   // strengths staged at a time (a multiple of 8)
+constexpr int kRowStage = 256;   // strengths staged at a time (a multiple of the 32 that the wavefronts take together)
 struct P2MApply {
     int64_t leaf_base, nleaf;
     const int32_t *lrange;
@@ -563,7 +563,7 @@ __device__ __forceinline__ void p2m_apply(int64_t li, const P2MApply &a, const S
     if (w == 0 && o < Pp)
         a.M[b * Pp + o] = o < a.P ? (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]) : 0.0;
 }
-constexpr int kP2MApplyLds = 256 + 2 * kRowStage + 64;   // doubles (64: read past the last stage's end)
+constexpr int kP2MApplyLds = 256 + 2 * kRowStage;   // doubles
 __global__ __launch_bounds__(256) void k_p2m_apply(P2MApply a, Strengths st, int64_t off1, int has_q, int has_d) {
     __shared__ double lds[kP2MApplyLds];
     p2m_apply(blockIdx.x, a, st, off1, has_q, has_d, lds);
