@@ -491,11 +491,17 @@ yk_status yk_ws_adam_step(yk_ws ws, const float *grad);
  * nodes and the near-boundary targets) and the work of its last evaluation:
  * near-field pairs and M2L translations.
  * yk_timing_enable: when on, every FMM stage is bracketed by HIP events on
- * the stream it runs on (the near field, YK_STAGE_LEAF, runs on a second
- * stream of the context concurrently with the far-field stages, unless
- * debug_flags bit 1 is set; its time then includes the sharing of the GPU); yk_timing_read returns the accumulated milliseconds
- * and launch counts per stage (YK_STAGE_*), resolving the events, and resets
- * the counters when `reset` is non-zero.  Reading synchronises the stream.
+ * the stream it runs on.  The near field, YK_STAGE_LEAF, runs in one of three
+ * ways.  On trees of fewer than 2,048 near-field items (up to 64 targets of a
+ * leaf) whose cached values and P2M rows fit near_cache_mb, it shares one launch
+ * with the gathers and P2M: YK_STAGE_LEAF is that launch, YK_STAGE_GATHER and
+ * YK_STAGE_P2M have no calls.  On other trees of fewer than 8,192 leaves it runs
+ * on a second stream of the context, concurrently with the far-field stages, and
+ * its time includes the sharing of the GPU.  On larger trees, and everywhere with
+ * debug_flags bit 1 set, the stages run in turn.  yk_timing_read returns the
+ * accumulated milliseconds and launch counts per stage (YK_STAGE_*), resolving
+ * the events, and resets the counters when `reset` is non-zero.  Reading
+ * synchronises the stream.
  */
 typedef struct {
     int32_t valid;            /* 0 when no tree is cached in the slot */

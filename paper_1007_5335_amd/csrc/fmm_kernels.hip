@@ -1551,10 +1551,17 @@ __device__ __forceinline__ void source_batches(int cn, int gs, Batch batch) {
     else batch(std::integral_constant<int, 2>(), std::false_type(), j0);
 }
 
-// Values of an item's block.  A large tree's are read from memory once per pass
-// (streaming: 200,003 points 147 us, 160 otherwise); a small tree's stay in
+// Values of an item's block, streamed past the caches or through them.  The line
+// lies where an item has one wavefront (2,048 items): fewer items' values stay in
 // cache between the passes of a solve (28,672 nodes, P2M and near field 26 us
-// streaming, 21 not; 1,536 nodes 18 and 13).
+// streaming, 21 not; 1,536 nodes 18 and 13), those of large trees are read from
+// memory once per pass (200,003 points, 739 MB: the near field 132 us, 149
+// otherwise; 400,000, 724 MB: 125 and 150; 120,000, 281 MB: 65 and 70).  What
+// decides is the values' size against the 256 MB of the last cache, so that
+// trees of 2,048 items and more with less than that lose by the rule: 70,000
+// points, 69 MB 40 and 32 us (the pass 107 and 105), 106 MB 34 and 27 (109 and
+// 107); 110,000 nodes, 120 MB 35 and 28 (222 and 215); 200,000 nodes, 197 MB 45
+// and 41 (330 both).
 template <bool kStream, typename T> __device__ __forceinline__ T near_value(const char *p) {
     if constexpr (kStream) return __builtin_nontemporal_load(reinterpret_cast<const T *>(p));
     else return *reinterpret_cast<const T *>(p);
@@ -2847,11 +2854,11 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
     // strengths through the permutation (k_p2m_near).  With more items the
     // near field outlasts P2M by so much that it goes to a second stream, under
     // the whole far field; large trees fill the GPU with either, and sharing it
-    // was measured no faster than running the stages in turn.  (A density
-    // solve on 28,672 nodes, 15 operator applications: 1.75 ms with the second
-    // stream and 1.63 in one launch when that was introduced; now 1.53, the
-    // stages in turn 1.66; a step on 64^2 cells 0.89 and 0.94 ms; a pass over
-    // 4,096 + 1,536 points 61 and 72 us.)
+    // was measured no faster than running the stages in turn.  (In one launch,
+    // and the stages in turn: a density solve on 28,672 nodes, 15 operator
+    // applications, 1.62 and 1.80 ms; right-hand side and step on 64^2 cells and
+    // 512 nodes 0.95 and 1.04 ms; a pass over 4,096 + 1,536 points 61 and 71 us.
+    // With the second stream the solve took 1.75 when one launch took 1.63.)
     const bool merged = far && near_cached && p2m_cached && wide && !(ctx.opt.debug_flags & 2);
     const bool overlap = !merged && !(ctx.opt.debug_flags & 2) && pl.nleaf < 8192 && near_on;
 

@@ -127,7 +127,7 @@ void parallel_for(int64_t n, F f) {
 
 int supported_order(int p) {
     // the orders the expansion kernels are instantiated for (P = 2p + 1 real
-    // coefficients padded to 16, 32, 48 or 64)
+    // coefficients padded to 32, 48 or 64)
     for (int q : kOrders)
         if (p <= q) return q;
     return kOrders[kNumOrders - 1];
