@@ -1143,27 +1143,31 @@ __device__ __forceinline__ double neg_half_log(double t, const double2 *__restri
     return __builtin_fma(de, h2_hi, c.y + __builtin_fma(de, h2_lo, s * r));
 }
 
-// (the forms for large arguments are called: inlined, the series of every loop
-// would share the registers with their constants)
-__device__ __attribute__((noinline)) double k0_large_c(double t) { return k0_large(2.0 * sqrt(t)); }
-__device__ __attribute__((noinline)) double k1oz4_large_c(double t) {
+// The forms for large arguments as calls (kCall): inlined, the series of every
+// loop share the registers with their constants.  Called wherever many wavefronts
+// hide what a call costs; see pick_leaf_kernel for the other case.
+__device__ __forceinline__ double k1oz4_large(double t) {
     const double z = 2.0 * sqrt(t);
     return 4.0 * k1_large(z) / z;
 }
-template <int NT, bool kSmallOnly>
+__device__ __attribute__((noinline)) double k0_large_c(double t) { return k0_large(2.0 * sqrt(t)); }
+__device__ __attribute__((noinline)) double k1oz4_large_c(double t) { return k1oz4_large(t); }
+template <int NT, bool kSmallOnly, bool kCall = true>
 __device__ __forceinline__ double near_k0(double t, const double2 *__restrict__ tab) {
     if (kSmallOnly || t <= 1.0)
         return __builtin_fma(neg_half_log(t, tab), horner_n<NT>(yk_ser_A, t), horner_n<NT>(yk_ser_B, t));
-    return k0_large_c(t);
+    if constexpr (kCall) return k0_large_c(t);
+    else return k0_large(2.0 * sqrt(t));
 }
 // 4 K1(z)/z with t = z^2/4
-template <int NT, bool kSmallOnly>
+template <int NT, bool kSmallOnly, bool kCall = true>
 __device__ __forceinline__ double near_k1oz4(double t, const double2 *__restrict__ tab) {
     if (kSmallOnly || t <= 1.0) {
         const double h2 = 2.0 * neg_half_log(t, tab);
         return fast_rcp(t) - __builtin_fma(h2, horner_n<NT>(yk_ser_C, t), horner_n<NT>(yk_ser_D, t));
     }
-    return k1oz4_large_c(t);
+    if constexpr (kCall) return k1oz4_large_c(t);
+    else return k1oz4_large(t);
 }
 
 template <int NT>
@@ -1194,18 +1198,18 @@ __device__ __forceinline__ float near_k1oz4_f(float t) {
 // Near-field accumulation policy: FP64 (series and sums in double) or FP32
 // (separations and the dipole dot product in double, the Bessel series, the
 // logarithm and the accumulation in float).
-template <int NT, bool kSmallOnly, bool kF32>
+template <int NT, bool kSmallOnly, bool kF32, bool kCall>
 struct Near {
     using acc_t = typename std::conditional<kF32, float, double>::type;
     static __device__ __forceinline__ acc_t charge(double q, double t, const double2 *tab) {
         if constexpr (kF32) return (float)q * near_k0_f<kSmallOnly>((float)t);
-        else return q * near_k0<NT, kSmallOnly>(t, tab);
+        else return q * near_k0<NT, kSmallOnly, kCall>(t, tab);
     }
     // dot = (x - y).(d n_y) in scaled coordinates; the caller multiplies the
     // sum by 1/(2 alpha), which turns dot * 4K1(z)/z into (1/alpha) K1(z) (x-y).(d n)/r
     static __device__ __forceinline__ acc_t dipole(double dot, double t, const double2 *tab) {
         if constexpr (kF32) return (float)dot * near_k1oz4_f<kSmallOnly>((float)t);
-        else return dot * near_k1oz4<NT, kSmallOnly>(t, tab);
+        else return dot * near_k1oz4<NT, kSmallOnly, kCall>(t, tab);
     }
 };
 
@@ -1238,7 +1242,7 @@ struct LeafArgs {
     double *outs;
 };
 // one item by the calling wavefront (sync: over the wavefront; the log table is ready after the first)
-template <int NT, bool kSmallOnly, bool kF32, typename Sync>
+template <int NT, bool kSmallOnly, bool kF32, bool kCall = true, typename Sync>
 __device__ __forceinline__ void leaf_item(const int2 item, const LeafArgs &A, LeafLds &S,
                                           const double2 *__restrict__ s_log, Sync sync) {
     const int li = item.x;
@@ -1288,7 +1292,7 @@ __device__ __forceinline__ void leaf_item(const int2 item, const LeafArgs &A, Le
     // first would round each coordinate, which costs digits in (x - y).n for
     // the nearly tangential pairs of densely sampled, tightly curved curves
     const double xs = A.px[t], ys = A.py[t];
-    using NearT = Near<NT, kSmallOnly, kF32>;
+    using NearT = Near<NT, kSmallOnly, kF32, kCall>;
     typename NearT::acc_t near_q = 0, near_d = 0;
     for (int set = 0; set < 2; ++set) {
         const int ntot_s = S.end[set][kLeafU - 1];
@@ -1353,14 +1357,14 @@ __device__ __forceinline__ void leaf_item(const int2 item, const LeafArgs &A, Le
     }
 }
 
-template <int NT, bool kSmallOnly, bool kF32 = false>
+template <int NT, bool kSmallOnly, bool kF32 = false, bool kCall = true>
 __global__ __launch_bounds__(64) void k_leaf(LeafArgs A) {
     __shared__ LeafLds S;
     __shared__ double2 s_log[YK_LOG_TAB];
     if constexpr (!kF32)
         for (int i = threadIdx.x; i < YK_LOG_TAB; i += 64)
             s_log[i] = make_double2(yk_log_tab[2 * i], yk_log_tab[2 * i + 1]);
-    leaf_item<NT, kSmallOnly, kF32>(A.items[xcd_remap(blockIdx.x, gridDim.x)], A, S, s_log, [] { __syncthreads(); });
+    leaf_item<NT, kSmallOnly, kF32, kCall>(A.items[xcd_remap(blockIdx.x, gridDim.x)], A, S, s_log, [] { __syncthreads(); });
 }
 
 // The adaptive tree's items in one launch: the items are ordered by the series
@@ -2661,7 +2665,17 @@ __global__ __launch_bounds__(256) void k_ad_l2p(
     pt.store(v, bx != nullptr, out0, out1, out2);
 }
 
-LeafKernel pick_leaf_kernel(int nt, bool small_only, bool f32) {
+// Pairs beyond the series, FP64: up to some number of items the forms for large
+// arguments are inlined, for a wavefront's own chain of pairs is what there is to
+// shorten; more items take the calls, which leave registers for more wavefronts.
+// Near field, called and inlined, boxes of 3 or 4 alpha: 1,024 leaves of some 20
+// points 166 and 135 us, 4,096 of 61 1,193 and 1,088, 8,239 of 40 1,121 and
+// 1,063, 12,289 of 40 1,547 and 1,543, 16,384 of 60 3,262 and 3,321, 65,536 of 15
+// 960 and 1,055.  Boxes of up to alpha, few of whose pairs are beyond the series:
+// 1,024 leaves equal, 4,096 of 15 82 and 67, 5,085 of 40 402 and 403, of 60 635
+// and 662, 6,735 of 15 80 and 89.
+LeafKernel pick_leaf_kernel(int nt, double tmax, bool f32, int64_t items) {
+    const bool small_only = tmax <= 1.0;
     if (f32) return small_only ? k_leaf<8, true, true> : k_leaf<8, false, true>;
     if (small_only) {
         if (nt <= 5) return k_leaf<5, true>;
@@ -2670,7 +2684,7 @@ LeafKernel pick_leaf_kernel(int nt, bool small_only, bool f32) {
         if (nt <= 10) return k_leaf<10, true>;
         return k_leaf<14, true>;
     }
-    return k_leaf<14, false>;
+    return items <= (tmax <= 2.0 ? 4608 : 12288) ? k_leaf<14, false, false, false> : k_leaf<14, false>;
 }
 
 }  // namespace
@@ -2992,8 +3006,8 @@ void fmm_run(Context &ctx, FmmPlan &pl, const double *q, const double *dn, doubl
                 LeafArgs la{as.leaf_items.p, pl.lrange.p, pl.ulist_off.p, pl.ulist.p, pl.px.p, pl.py.p, qs, dns,
                             pl.toff[1], has_q, has_d, mask, 0.5 * inv_alpha, 0.5 * inv_alpha, outs};
                 if (!pl.adaptive) {
-                    hipLaunchKernelGGL(pick_leaf_kernel(pl.near_terms, small_only, f32), dim3(as.n_items), dim3(64), 0,
-                                       near_stream, la);
+                    hipLaunchKernelGGL(pick_leaf_kernel(pl.near_terms, pl.near_tmax, f32, as.n_items),
+                                       dim3(as.n_items), dim3(64), 0, near_stream, la);
                 } else if (f32) {
                     // the kind with large arguments, then the others (one series serves them)
                     const int n_large = as.item_kind[1];

@@ -36,8 +36,8 @@ def _corners(rng, xy, m):
     return np.clip((np.round(m * xy) + 0.002 * (rng.random(xy.shape) - 0.5)) / m, 0.0, 1.0 - 2.0 ** -40)
 
 
-def _check(sums, got, perm, sample):
-    """Per target: at most 8 roundings of the terms' absolute values (a sum of many terms of either sign rounds by
+def _check(sums, got, perm, sample, roundings=8):
+    """Per target: at most 8 (or `roundings`) roundings of the terms' absolute values (a sum of many terms of either sign rounds by
     about one rounding of its absolute sum; some 30 such stages, P2M, shifts at up to 11 levels each way, M2L, L2P and
     the near field, each of either sign: the root of their number, and a little) and 4 of a position (a centre's
     coordinate rounds twice, at both ends of a translation: the root of four, and the 1.7 sides^-1 by which that
@@ -45,7 +45,7 @@ def _check(sums, got, perm, sample):
     worst = 0.0
     for j in sample:
         v, mag, pos = sums.at_sorted(int(j))
-        tol = U * (8 * mag + 4 * pos)
+        tol = U * (roundings * mag + 4 * pos)
         worst = max(worst, float(abs(got[perm[j]] - v) / tol))
     print(f"  largest error: {worst:.1e} of the bound", flush=True)
     assert worst <= 1.0
@@ -191,3 +191,39 @@ def test_siblings_shares_stay_apart(yk, ratio):
         err.append(float(abs(got[i] - v) / v))
     print(f"  largest error {max(err):.1e} of the target's own sum, median {np.median(err):.1e}", flush=True)
     assert max(err) <= 64 * U * np.exp(2.24 * ratio)
+
+
+# leaves (4^level, all filled) on either side of the items that choose the kernel (4,608 for boxes of up to alpha,
+# 12,288 for others); items of a few targets and of several wavefronts'
+@pytest.mark.parametrize("n,leaf,level,ratio", [(300, 16, 3, 1.2), (900, 200, 2, 4.0), (40000, 16, 6, 0.9),
+                                                (40000, 16, 6, 3.0), (200000, 16, 7, 0.9), (200000, 16, 7, 3.0),
+                                                (200000, 16, 7, 12.0)])
+def test_near_field_beyond_the_series(yk, n, leaf, level, ratio):
+    """The near field evaluated on the fly at arguments beyond its series, coincident points among the pairs.  An
+    argument of z rounds to z roundings of exp(-z), and the pairs reach z = 2 sqrt(2) ratio <= 34."""
+    import torch
+    from oracle import expansions as E
+    rng = np.random.default_rng(53)
+    alpha = 2.0 ** -level / ratio
+    xy = rng.random((n, 2))
+    xy[10:20] = xy[:10]
+    nodes = 200
+    th = 2 * np.pi * np.arange(nodes) / nodes
+    nrm = np.stack([np.cos(th), np.sin(th)], 1)
+    bxy, ones = 0.5 + 0.3 * nrm, np.ones(nodes)
+    q, d = rng.standard_normal(n), rng.standard_normal(nodes)
+    print(f"rounding, large arguments: {n} {leaf} {ratio}", flush=True)
+    ctx = yk.yk_create(leaf_size=leaf, p=31, tree=yk.YK_TREE_UNIFORM, near_cache_mb=0, direct=0)
+    try:
+        bd = yk.Boundary(bxy, nrm, ones, ones, [0, nodes])
+        ov = torch.empty(n, dtype=torch.float64, device="cuda")
+        ob = torch.empty(nodes, dtype=torch.float64, device="cuda")
+        yk.yk_fmm_potential(ctx, dev(xy), dev(q), bd, dev(d), alpha, ov, ob)
+        t = _tree(yk, ctx, 0, False)
+    finally:
+        yk.yk_destroy(ctx)
+    print(f"  level {t['leaf_level']}, {len(t['leaf_range'])} leaves", flush=True)
+    assert t["leaf_level"] == level and (len(t["leaf_range"]) > 12288) == (n > 100000)
+    place = np.argsort(t["perm"][:n])
+    sample = np.concatenate([place[:20], rng.choice(n, 40, replace=False)])
+    _check(E.Sums(t, alpha, 31, xy, q, bxy, nrm, d), host(ov), t["perm"], sample, roundings=8 + 34)
